@@ -8,12 +8,14 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspense.so")
-SOURCES = ["spense_api.cpp", "spense_gemm.hip", "spense_compress.hip", "spense_quant.hip", "spense_index.hip", "spense_obs.hip",
+SOURCES = ["spense_api.cpp", "spense_gemm.hip", "spense_gemm_big2.hip", "spense_compress.hip", "spense_quant.hip",
+           "spense_index.hip", "spense_obs.hip",
            "spense_noalloc.hip"]
 ARCH = "gfx950"
 
@@ -50,8 +52,7 @@ def toolchain() -> tuple[str, str]:
 def build(verbose: bool = False) -> str:
     objdir = os.path.join(ROOT, "_build", "spense")
     os.makedirs(objdir, exist_ok=True)
-    objs = []
-    for src in SOURCES:
+    def compile_one(src: str) -> str:
         obj = os.path.join(objdir, src + ".o")
         lang = ["-x", "hip"]
         cmd = [hipcc()] + HIP_FLAGS + lang + ["-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, src),
@@ -64,7 +65,10 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError(f"hipcc failed for {src}:\n{err}")
         if verbose and err.strip():
             print(err, file=sys.stderr)
-        objs.append(obj)
+        return obj
+
+    with ThreadPoolExecutor(max_workers=4) as pool:
+        objs = list(pool.map(compile_one, SOURCES))
     tmp = LIB + f".tmp{os.getpid()}"
     cmd = [hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}"] + objs + ["-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -39,85 +39,10 @@
 // All loads are range-checked buffer loads: a lane whose chunk lies past the end of its
 // range gets an out-of-range offset and reads zeros, so the loops have no divergent
 // branches.
-#include <mutex>
-
-#include "spense_internal.h"
+#include "spense_gemm_device.h"
 
 namespace spense {
 namespace {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v16bf __attribute__((ext_vector_type(16)));
-
-constexpr uint32_t kOOB = 0x80000000u;  // any offset past every buffer extent
-// Cache policy of the weight loads.  Measured on MI355X: for rows read as 16 x 64-byte
-// segments per instruction the default policy streams ~15% faster than non-temporal;
-// for the tiled layout (1 KB contiguous per instruction) non-temporal is 5-9% faster.
-constexpr int kNT = 0;
-constexpr int kTiledNT = 2;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-// voffset: per-lane byte offset; soffset: wave-uniform byte offset (scalar register)
-template <int AUX>
-__device__ __forceinline__ v4i bl16(__amdgpu_buffer_rsrc_t r, uint32_t off, int soff = 0) {
-  return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, soff, AUX));
-}
-template <int AUX>
-__device__ __forceinline__ int bl4(__amdgpu_buffer_rsrc_t r, uint32_t off, int soff = 0) {
-  return (int)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, soff, AUX);
-}
-__device__ __forceinline__ v8i cat8(v4i a, v4i b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
-__device__ __forceinline__ uint32_t sel(bool ok, uint32_t off) { return ok ? off : kOOB; }
-
-// Matrix-core results are written several cycles after the instruction issues (up to
-// about a dozen wait states for the 8-pass fp8 instruction), and the hardware does not
-// interlock a later non-matrix read (or a matrix read of a different register) against
-// that write.  Where such a read sits in another basic block than the producing matrix
-// instruction (loop exits, the 2:4 -> dense switch, the epilogue), the compiler's own
-// padding was measured to fall short on gfx950, so these points get 20 explicit wait
-// states.  The scheduling barriers keep instructions from moving across them.
-__device__ __forceinline__ void xdl_fence() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-template <int DT>
-struct Traits;
-template <>
-struct Traits<kFP8> {
-  static constexpr int KS = 128;  // logical K per sparse instruction
-  static constexpr int KD = 128;  // K per dense instruction
-  static constexpr int ES = 1;
-};
-template <>
-struct Traits<kBF16> {
-  static constexpr int KS = 64;
-  static constexpr int KD = 32;
-  static constexpr int ES = 2;
-};
-
-__device__ __forceinline__ v4f mma_sparse(v4i a, v8i b, v4f c, int idx, std::integral_constant<int, kFP8>) {
-  return __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(a, b, c, idx, 0, 0);
-}
-__device__ __forceinline__ v4f mma_sparse(v4i a, v8i b, v4f c, int idx, std::integral_constant<int, kBF16>) {
-  return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v16bf, b), c,
-                                                   idx, 0, 0);
-}
-__device__ __forceinline__ v4f mma_dense(v8i a, v8i b, v4f c, std::integral_constant<int, kFP8>) {
-  // fp8 e4m3 for both operands (format selectors 0), no block scales
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
-}
-__device__ __forceinline__ v4f mma_dense(v8i a, v8i b, v4f c, std::integral_constant<int, kBF16>) {
-  const v4i a4 = {a[0], a[1], a[2], a[3]}, b4 = {b[0], b[1], b[2], b[3]};
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a4), __builtin_bit_cast(v8bf, b4), c, 0,
-                                                 0, 0);
-}
 
 // ---------------------------------------------------------------- pipeline stages
 // One stage = U instruction steps of one wave.  Offsets are byte offsets into the
@@ -296,145 +221,6 @@ __device__ __forceinline__ void run_stages(v4f (&acc)[RT][CT], int k0, int kend,
     mma_stage(acc, st);
   }
   xdl_fence();
-}
-
-// ---------------------------------------------------------------- epilogue
-__device__ __forceinline__ uint32_t bf16_bits(float v) {
-  __bf16 h = (__bf16)v;  // round to nearest even
-  return (uint32_t)__builtin_bit_cast(uint16_t, h);
-}
-
-// Epilogue of 4 consecutive output rows n0.. of token m: (acc * w_scale[n]) * x_scale[m],
-// bf16 (round to nearest even) or fp32, one vector store where allowed.
-// Y[m, n0 + r] = v[r] for r < 4 (rows before rowend), bf16 RNE or fp32 per a.out_f32.
-__device__ __forceinline__ void put4(void* Y, int64_t ldy, int vec_store, const GemmArgs& a, const float (&v)[4], int m,
-                                     int n0, int rowend) {
-  if (a.out_f32) {
-    float* yp = reinterpret_cast<float*>(Y) + (int64_t)m * ldy + n0;
-    if (vec_store && n0 + 3 < rowend) {
-      *reinterpret_cast<v4f*>(yp) = (v4f){v[0], v[1], v[2], v[3]};
-    } else {
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (n0 + r < rowend) yp[r] = v[r];
-    }
-  } else {
-    uint16_t* yp = reinterpret_cast<uint16_t*>(Y) + (int64_t)m * ldy + n0;
-    const uint32_t b0 = bf16_bits(v[0]), b1 = bf16_bits(v[1]), b2 = bf16_bits(v[2]), b3 = bf16_bits(v[3]);
-    if (vec_store && n0 + 3 < rowend) {
-      typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-      *reinterpret_cast<u2*>(yp) = (u2){b0 | (b1 << 16), b2 | (b3 << 16)};
-    } else {
-      const uint32_t bb[4] = {b0, b1, b2, b3};
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (n0 + r < rowend) yp[r] = (uint16_t)bb[r];
-    }
-  }
-}
-
-// The epilogue of one output quad: Y[m, n0 + r] = (acc[r] * w_scale[n]) * x_scale[m]
-// (each factor only where given), fp32, then put4.
-__device__ __forceinline__ void store4(void* Y, int64_t ldy, const float* sw, int vec_store, const GemmArgs& a,
-                                       v4f acc, int m, int n0, int rowend) {
-  const float xs = a.sx ? a.sx[m] : 1.0f;
-  float v[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int n = n0 + r < rowend ? n0 + r : rowend - 1;
-    float y = acc[r];
-    if (sw) y = y * sw[n];
-    v[r] = y * xs;
-  }
-  put4(Y, ldy, vec_store, a, v, m, n0, rowend);
-}
-
-// The scales of one wave's RT x CT output quads (rows n0 + 16 t + [0, 4), token m0 +
-// 16 c), loaded together before any output store: read next to each store, a scale load
-// would follow stores that may alias it and wait for their acknowledgement, one memory
-// round trip per quad.  Rows past the region and tokens past M read the last valid one
-// (their stores are skipped); a missing scale reads as 1.
-template <int RT, int CT>
-struct EpiScales {
-  float w[RT][4];
-  float x[CT];
-};
-
-template <int RT, int CT>
-__device__ __forceinline__ void epi_scales(EpiScales<RT, CT>& e, const float* sw, const float* sx, int M, int n0, int m0,
-                                           int rowend) {
-#pragma unroll
-  for (int t = 0; t < RT; ++t)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) e.w[t][r] = sw ? sw[min(n0 + 16 * t + r, rowend - 1)] : 1.0f;
-#pragma unroll
-  for (int c = 0; c < CT; ++c) e.x[c] = sx ? sx[min(m0 + 16 * c, M - 1)] : 1.0f;
-}
-
-// store4 of quad (t, c) with its scales from epi_scales: the same arithmetic, bit for bit.
-template <int RT, int CT>
-__device__ __forceinline__ void store4e(void* Y, int64_t ldy, bool wscaled, int vec_store, const GemmArgs& a,
-                                        const EpiScales<RT, CT>& e, int t, int c, v4f acc, int m, int n0, int rowend) {
-  float v[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    float y = acc[r];
-    if (wscaled) y = y * e.w[t][r];
-    v[r] = y * e.x[c];
-  }
-  put4(Y, ldy, vec_store, a, v, m, n0, rowend);
-}
-
-__device__ __forceinline__ void store4(const GemmArgs& a, v4f acc, int m, int n0, int rowend) {
-  store4(a.Y, a.ldy, a.sw, a.vec_store, a, acc, m, n0, rowend);
-}
-
-// A large-M workgroup's bf16 output tile through LDS, so that it leaves as whole token
-// rows: stored straight from the accumulators, each instruction would write 16 token rows
-// 32 bytes apiece, four times the write requests of whole rows (measured on the 256 x 256
-// kernel: about 9 us of store issue per tile against 2).  Token row r of the tile (NB
-// 16-byte blocks of eight outputs) sits at byte r * 16 NB, its block b stored at block
-// b ^ (r % NB), so that neither the quad writes nor the row reads meet in a bank.
-// out_tile_write: a wave's RT x CT quads (rows 16 (RT wr + t) + 4 lq + [0, 4) of the tile,
-// token 16 (CT wc + c) + li), scaled and rounded as store4e does.
-template <int RT, int CT, int NB>
-__device__ __forceinline__ void out_tile_write(uint8_t* ot, const v4f (&acc)[RT][CT], const EpiScales<RT, CT>& es,
-                                               bool wscaled, int wr, int wc, int li, int lq) {
-  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-  for (int t = 0; t < RT; ++t)
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      float v[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float y = acc[t][c][r];
-        if (wscaled) y = y * es.w[t][r];
-        v[r] = y * es.x[c];
-      }
-      const int r = 16 * (CT * wc + c) + li, n = 16 * (RT * wr + t) + 4 * lq;
-      *reinterpret_cast<u2*>(ot + r * (16 * NB) + (((n >> 3) ^ (r % NB)) << 4) + (n & 7) * 2) =
-          (u2){bf16_bits(v[0]) | (bf16_bits(v[1]) << 16), bf16_bits(v[2]) | (bf16_bits(v[3]) << 16)};
-    }
-}
-
-// out_tile_store: the tile's first ntok token rows to Y (tile row 0 = output row rblk,
-// token 0 = m0), 16 bytes per thread; Y 16-byte aligned, ldy and rblk multiples of 8.
-template <int NB, int NTHR>
-__device__ __forceinline__ void out_tile_store(const uint8_t* ot, int ntok, int m0, int M, int rblk, int rowend, void* Y,
-                                               int64_t ldy) {
-  for (int q = threadIdx.x; q < ntok * NB; q += NTHR) {
-    const int r = q / NB, b = q % NB;
-    const int m = m0 + r, n = rblk + 8 * b;
-    if (m >= M || n >= rowend) continue;
-    const v4i d = *reinterpret_cast<const v4i*>(ot + r * (16 * NB) + ((b ^ (r % NB)) << 4));
-    uint16_t* yp = reinterpret_cast<uint16_t*>(Y) + (int64_t)m * ldy + n;
-    if (n + 8 <= rowend) {
-      *reinterpret_cast<v4i*>(yp) = d;
-    } else {
-      for (int e = 0; e < rowend - n; ++e) yp[e] = (uint16_t)((uint32_t)d[e >> 1] >> (16 * (e & 1)));
-    }
-  }
 }
 
 // ---------------------------------------------------------------- kernel
@@ -764,26 +550,6 @@ __device__ __forceinline__ void mma_chunk(v4f (&acc)[RT][CT], const WChunk (&W)[
         }
     }
   }
-}
-
-// Workgroup barrier that first waits until at most N of this wave's vector-memory
-// operations are outstanding (loads complete in issue order, so every older one is
-// done).  The wait is the builtin, which the compiler's own wait insertion takes into
-// account; the barrier's memory clobber keeps LDS accesses from moving across it.
-template <int N>
-__device__ __forceinline__ void barrier_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  // s_waitcnt fields: vmcnt[3:0] and [15:14], expcnt [6:4] and lgkmcnt [11:8] left at max
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-  asm volatile("s_barrier" ::: "memory");
-}
-
-// As barrier_vm, and also wait for this wave's LDS accesses (lgkmcnt(0)).
-template <int N>
-__device__ __forceinline__ void barrier_vm_lgkm0() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
-  asm volatile("s_barrier" ::: "memory");
 }
 
 // Pipeline with NS register slots and NS LDS buffers, D = NS-1 chunks ahead (per wave,
@@ -1369,16 +1135,6 @@ struct BigStage {
   __device__ static __forceinline__ int xaddr(int r, int b) { return r * 128 + ((b ^ ((r >> 1) & 7)) << 4); }
 };
 
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>()), ...);
-}
-// f(integral_constant<int, i>) for i = 0 .. N-1, each index a compile-time constant.
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>());
-}
-
 // Where the loads of one step go and what they cover.
 struct BigStepLd {
   uint8_t* st;                 // stage buffer
@@ -1664,342 +1420,6 @@ __global__ __launch_bounds__(64 * WV) void spense_gemm_big_kernel(GemmArgs a) {
       const int n0 = rblk + 16 * (RPW * wr + t) + 4 * lq;
       if (m < a.M && n0 < rowend) store4e(a.Y, a.ldy, a.sw != nullptr, a.vec_store, a, es, t, c, acc[t][c], m, n0, rowend);
     }
-}
-
-// ---------------------------------------------------------------- large-M kernel, 256 x 256 tiles
-// Both operands through LDS as in spense_gemm_big_kernel, with twice the rows per
-// workgroup and per wave: a workgroup computes 256 weight rows x 256 tokens, its 8 waves a
-// grid of 2 row halves x 4 token quarters, each wave 128 rows (8 row tiles) x 64 tokens (4
-// token tiles, 128 accumulators).  Each B fragment read from LDS feeds 8 MMAs, each A
-// fragment 4.  Tiled weight layout only.
-//
-// The CU's load path moves about 57 bytes per clock from L2 with 16-byte-per-lane loads,
-// into registers or straight into LDS alike, but a load instruction costs at least ~18
-// clocks however few bytes it moves (a 4-byte-per-lane load moves 256 bytes in ~32; all
-// measured on MI355X).  So every load here moves 1 KB: per 128-column step a wave issues 4
-// activation blocks and, for its 2 row tiles, the 2:4 value blocks or both dense halves;
-// a 2:4 step's metadata (256 bytes per row tile) takes 4 more loads, one on each of waves
-// 0-3, each gathering the pieces of 4 row tiles.  6.5 loads per 2:4 step (52 KB per
-// workgroup) against ~1.07k clocks of its 256 MMAs.
-//
-// Per-wave timelines showed every wave waiting at the barrier for the loads when they had
-// one step to land in, so the 2:4 steps run three stages deep (loads two steps ahead; a
-// stage is 52 KB: activations, values, metadata) and the dense steps, whose stage is 64 KB
-// and whose MMAs take twice as long, two.  Within a step the loads go out early: the
-// activation blocks before the first group of 4 MMAs, the weight blocks before the third.
-// An input-split weight switches from the first layout to the second once, after a
-// barrier.  The per-lane offsets are loop-invariant; the step's offset travels in the
-// scalar offset.  The barrier at the start of a step waits for this wave's loads of the
-// step and for its LDS reads of the previous step.
-constexpr int kB2Rows = 256, kB2Tokens = 256, kB2RowTiles = 16;
-constexpr int kB2XSlot = kB2Tokens * 128;                                      // activations of one step
-constexpr int kB2SStage = kB2XSlot + kB2RowTiles * 1024 + kB2RowTiles * 256;  // + 2:4 values, metadata
-constexpr int kB2DStage = kB2XSlot + kB2RowTiles * 2048;                       // + both dense halves
-constexpr int kB2Lds = 3 * kB2SStage > 2 * kB2DStage ? 3 * kB2SStage : 2 * kB2DStage;
-
-template <int AUX>
-__device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, uint8_t* dst, uint32_t voff, int soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voff, soff, 0, AUX);
-}
-
-// GR: a grouped launch (several weights sharing X and K): up to kMaxRegions regions, each
-// reading its weight's buffers, output and scales from a.mat[R.mat].
-template <bool GR>
-__global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
-  constexpr int WV = 8, NT = kB2RowTiles, RPW = 8, TC = 4;
-  constexpr int TU = NT / WV;                // row tiles whose weights a wave copies
-  constexpr int XI = kB2XSlot / 1024 / WV;  // 1 KB activation blocks per wave per step
-  constexpr int MW = NT * 256 / 1024;       // waves that copy a 2:4 step's metadata
-  static_assert(XI + 2 * TU == RPW, "eight loads per dense step");
-  static_assert(XI == 4 && TU == 2 && MW <= WV, "load schedule");
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int li = lane & 15, lq = lane >> 4;
-  const int wr = wave & 1, wc = wave >> 1;
-  // Workgroups [0, hg0): 256 x 256 tiles, in the XCD-aware order when it is on.  From
-  // hg0 on (dispatched last, so that they fill the tail of the grid): the row blocks
-  // hrb0 .. of the last region as 256 x 128 tiles, hper per row block; their waves of
-  // token quarters 2 and 3 only copy and take part in the barriers.
-  int g = blockIdx.x, ri, rb, m0;
-  bool half = false;
-  if (g < a.hg0) {
-    if (a.xgt > 0 && g < a.xg1) {  // XCD-aware order, as in spense_gemm_big_kernel
-      const int T = a.tblocks, GT = a.xgt, RC = a.xrc, TGc = T / GT;
-      const int x = g & 7, l = g >> 3, tg = x % TGc, rc = x / TGc;
-      g = ((l / GT) * RC + rc) * T + tg * GT + l % GT;
-    }
-    ri = 0;
-    if constexpr (GR) {
-      for (int i = 1; i < a.nreg; ++i)
-        if (g >= a.reg[i].wg0) ri = i;
-    } else {
-      ri = (a.nreg > 1 && g >= a.reg[1].wg0) ? 1 : 0;
-    }
-    rb = (g - a.reg[ri].wg0) / a.tblocks;
-    m0 = (g - a.reg[ri].wg0) % a.tblocks * (a.btok > 0 ? a.btok : kB2Tokens);
-  } else {
-    const int h = g - a.hg0;
-    ri = a.nreg - 1;
-    rb = a.hrb0 + h / a.hper;
-    m0 = h % a.hper * (kB2Tokens / 2);
-    half = true;
-  }
-  const Region& R = a.reg[ri];
-  const int rowend = R.row0 + R.rows;
-  const int rblk = R.row0 + rb * kB2Rows;
-  // tokens of this tile: 256, or 192 (full tiles of a 192-token block), or 128 (half tiles)
-  const int ntok = half ? kB2Tokens / 2 : (a.btok > 0 ? a.btok : kB2Tokens);
-  const int K = R.kend, kbound = R.kbound;
-
-  extern __shared__ __attribute__((aligned(1024))) uint8_t big_lds[];
-  const MatDesc& MD = a.mat[GR ? R.mat : 0];
-  const __amdgpu_buffer_rsrc_t rx = rsrc(a.X, a.x_bytes),
-                               rv = GR ? rsrc(MD.values, MD.v_bytes) : rsrc(a.values, a.v_bytes),
-                               rm = GR ? rsrc(MD.meta, MD.m_bytes) : rsrc(a.meta, a.m_bytes),
-                               rd = GR ? rsrc(MD.dense, MD.d_bytes) : rsrc(a.dense, a.d_bytes);
-  v4f acc[RPW][TC];
-#pragma unroll
-  for (int t = 0; t < RPW; ++t)
-#pragma unroll
-    for (int c = 0; c < TC; ++c) acc[t][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-
-  const int n_sp = (kbound + 127) / 128, n_de = (K - kbound + 127) / 128, nst = n_sp + n_de;
-  const int nch_sp = (n_sp + 3) / 4, nch_de = (n_de + 3) / 4;
-
-  // loop-invariant per-lane offsets (kOOB for rows past M or row tiles past the region)
-  uint32_t xo[XI];
-  int xb[XI];  // the column (bytes) of this lane's 16-byte block inside the step
-#pragma unroll
-  for (int i = 0; i < XI; ++i) {
-    const int blk = wave * XI + i;
-    const int r = 8 * blk + (lane >> 3), b = (lane & 7) ^ ((r >> 1) & 7);
-    const int m = m0 + r;
-    xb[i] = 16 * b;
-    xo[i] = m < a.M && r < ntok ? (uint32_t)((int64_t)m * a.ldx_b + 16 * b) : kOOB;
-  }
-  uint32_t vo[TU], dlo[TU];
-#pragma unroll
-  for (int u = 0; u < TU; ++u) {
-    const int r0 = rblk + 16 * (TU * wave + u);
-    const bool ok = r0 < rowend;
-    vo[u] = ok ? (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 4096u + 16u * lane : kOOB;
-    dlo[u] = ok && r0 >= R.dense_row_off ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
-                                          : kOOB;
-  }
-  // a 2:4 step's metadata: wave w < MW copies the 256-byte pieces of row tiles 4w .. 4w + 3
-  // (lane l: 16 bytes of tile 4w + l / 16); a tile's piece for step s sits 256 s bytes into
-  // its metadata
-  uint32_t mo1 = kOOB;
-  if (wave < MW) {
-    const int r0 = rblk + 16 * (4 * wave + (lane >> 4));
-    if (r0 < rowend) mo1 = (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 1024u + 16u * li;
-  }
-
-  // Load j of this wave for 2:4 step sn into stage stg: activation blocks (j < 4), the value
-  // blocks of its two row tiles (j = 4, 5), the metadata gather (j = 6, waves 0-3).
-  auto sp_load = [&](auto j_const, int sn, uint8_t* stg) __attribute__((always_inline)) {
-    constexpr int j = decltype(j_const)::value;
-    if (sn >= n_sp) return;  // uniform
-    if constexpr (j < XI) {
-      const int ks = 128 * sn;
-      uint32_t off = xo[j];
-      if (ks + 128 > kbound) off = ks + xb[j] < kbound ? off : kOOB;  // the region's last, partial step
-      lds_load16<0>(rx, stg + (wave * XI + j) * 1024, off, ks);
-    } else if constexpr (j < XI + TU) {
-      constexpr int u = j - XI;
-      lds_load16<kTiledNT>(rv, stg + kB2XSlot + (TU * wave + u) * 1024, vo[u], 1024 * sn);
-    } else {
-      if (wave < MW) lds_load16<kTiledNT>(rm, stg + kB2XSlot + NT * 1024 + wave * 1024, mo1, 256 * sn);
-    }
-  };
-  // Load j of this wave for dense step sn into stage stg: activation blocks (j < 4), then
-  // the two halves of its two row tiles.
-  auto de_load = [&](auto j_const, int sn, uint8_t* stg) __attribute__((always_inline)) {
-    constexpr int j = decltype(j_const)::value;
-    if (sn >= nst) return;  // uniform
-    if constexpr (j < XI) {
-      const int ks = kbound + 128 * (sn - n_sp);
-      uint32_t off = xo[j];
-      if (ks + 128 > K) off = ks + xb[j] < K ? off : kOOB;
-      lds_load16<0>(rx, stg + (wave * XI + j) * 1024, off, ks);
-    } else {
-      constexpr int u = (j - XI) % TU, half = (j - XI) / TU;
-      lds_load16<kTiledNT>(rd, stg + kB2XSlot + (TU * wave + u) * 2048 + 1024 * half, dlo[u],
-                           2048 * (sn - n_sp) + 1024 * half);
-    }
-  };
-
-  // B fragments of the wave's 4 token tiles from a stage
-  auto read_b = [&](v8i (&bq)[TC], const uint8_t* xs) __attribute__((always_inline)) {
-#pragma unroll
-    for (int c = 0; c < TC; ++c) {
-      const int r = 16 * (TC * wc + c) + li;
-      bq[c] = cat8(*reinterpret_cast<const v4i*>(xs + r * 128 + ((lq ^ ((r >> 1) & 7)) << 4)),
-                   *reinterpret_cast<const v4i*>(xs + r * 128 + (((4 + lq) ^ ((r >> 1) & 7)) << 4)));
-    }
-  };
-
-  // 2:4 step s from stage cur; the loads of step s + 2 go to stage nxt.  Per row tile t the
-  // A fragment of tile t + 1 is read (other register set) before the 4 MMAs of tile t.
-  // ACT = false: a wave without tokens (token quarters past a 128- or 192-token tile) only copies.
-  auto sp_step = [&](auto act_const, int s, const uint8_t* cur, uint8_t* nxt) __attribute__((always_inline)) {
-    constexpr bool ACT = decltype(act_const)::value;
-    // this wave's loads of step s have landed once at most those of step s + 1 are pending
-    if (s + 1 < n_sp) {
-      if (wave < MW)
-        barrier_vm_lgkm0<XI + TU + 1>();
-      else
-        barrier_vm_lgkm0<XI + TU>();
-    } else {
-      barrier_vm_lgkm0<0>();
-    }
-    v8i bq[TC];
-    const uint8_t* vl = cur + kB2XSlot + (RPW * wr) * 1024 + 16 * lane;
-    const uint8_t* ml = cur + kB2XSlot + NT * 1024 + (RPW * wr) * 256 + 16 * li + 4 * lq;
-    v4i av[2];
-    int aix[2];
-    if constexpr (ACT) {
-      read_b(bq, cur);
-      av[0] = *reinterpret_cast<const v4i*>(vl);
-      aix[0] = *reinterpret_cast<const int*>(ml);
-    }
-    static_for<RPW>([&](auto t_const) {
-      constexpr int t = decltype(t_const)::value;
-      constexpr int q = t & 1;
-      if constexpr (ACT && t + 1 < RPW) {
-        av[1 - q] = *reinterpret_cast<const v4i*>(vl + (t + 1) * 1024);
-        aix[1 - q] = *reinterpret_cast<const int*>(ml + (t + 1) * 256);
-      }
-      if constexpr (t == 0) static_for<XI>([&](auto j) { sp_load(j, s + 2, nxt); });
-      if constexpr (t == 2) {
-        sp_load(std::integral_constant<int, XI>(), s + 2, nxt);
-        sp_load(std::integral_constant<int, XI + 1>(), s + 2, nxt);
-        sp_load(std::integral_constant<int, XI + 2>(), s + 2, nxt);
-      }
-      if constexpr (ACT) {
-#pragma unroll
-        for (int c = 0; c < TC; ++c)
-          acc[t][c] = mma_sparse(av[q], bq[c], acc[t][c], aix[q], std::integral_constant<int, kFP8>());
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    });
-  };
-
-  // dense step s from stage cur; the loads of step s + 1 go to stage nxt
-  auto de_step = [&](auto act_const, int s, const uint8_t* cur, uint8_t* nxt) __attribute__((always_inline)) {
-    constexpr bool ACT = decltype(act_const)::value;
-    barrier_vm_lgkm0<0>();
-    v8i bq[TC];
-    const uint8_t* wl = cur + kB2XSlot + (RPW * wr) * 2048 + 16 * lane;
-    v4i alo[2], ahi[2];
-    if constexpr (ACT) {
-      read_b(bq, cur);
-      alo[0] = *reinterpret_cast<const v4i*>(wl);
-      ahi[0] = *reinterpret_cast<const v4i*>(wl + 1024);
-    }
-    static_for<RPW>([&](auto t_const) {
-      constexpr int t = decltype(t_const)::value;
-      constexpr int q = t & 1;
-      if constexpr (ACT && t + 1 < RPW) {
-        alo[1 - q] = *reinterpret_cast<const v4i*>(wl + (t + 1) * 2048);
-        ahi[1 - q] = *reinterpret_cast<const v4i*>(wl + (t + 1) * 2048 + 1024);
-      }
-      if constexpr (t == 0 || t == 2) {
-        de_load(std::integral_constant<int, 2 * t>(), s + 1, nxt);
-        de_load(std::integral_constant<int, 2 * t + 1>(), s + 1, nxt);
-        de_load(std::integral_constant<int, 2 * t + 2>(), s + 1, nxt);
-        de_load(std::integral_constant<int, 2 * t + 3>(), s + 1, nxt);
-      }
-      if constexpr (ACT) {
-#pragma unroll
-        for (int c = 0; c < TC; ++c)
-          acc[t][c] = mma_dense(cat8(alo[q], ahi[q]), bq[c], acc[t][c], std::integral_constant<int, kFP8>());
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    });
-  };
-
-  auto run = [&](auto act_const) __attribute__((always_inline)) {
-    int s = 0;
-    if (n_sp > 0) {
-      static_for<XI + TU + 1>([&](auto j) { sp_load(j, 0, big_lds); });
-      static_for<XI + TU + 1>([&](auto j) { sp_load(j, 1, big_lds + kB2SStage); });
-      int k = 0;  // stage of step s
-      for (; s < n_sp; ++s) {
-        const int k2 = k == 0 ? 2 : k - 1;  // stage of step s + 2
-        sp_step(act_const, s, big_lds + k * kB2SStage, big_lds + k2 * kB2SStage);
-        k = k == 2 ? 0 : k + 1;
-      }
-      xdl_fence();
-    }
-    if (n_de > 0) {
-      if (n_sp > 0) barrier_vm_lgkm0<0>();  // every wave is done with the 2:4 stages
-      static_for<RPW>([&](auto j) { de_load(j, s, big_lds); });
-      for (; s < nst; ++s) {
-        const int k = (s - n_sp) & 1;
-        de_step(act_const, s, big_lds + k * kB2DStage, big_lds + (1 - k) * kB2DStage);
-      }
-      xdl_fence();
-    }
-  };
-  // bf16 output with 16-byte aligned rows leaves through LDS as whole token rows
-  // (out_tile_write); the waves of token quarters past the tile's tokens (2 and 3 of a 256
-  // x 128 tile, 3 of a 256 x 192 one) then only help with the stores
-  const bool idle = wc * (kB2Tokens / 4) >= ntok;
-  const bool via_lds = !a.out_f32 && ((uintptr_t)MD.Y % 16 == 0) && (MD.ldy % 8 == 0) && (rblk % 8 == 0);
-  if (idle) {
-    run(std::false_type());
-    if (!via_lds) return;
-  } else {
-    run(std::true_type());
-  }
-  EpiScales<RPW, TC> es;
-  if (!idle) epi_scales(es, MD.sw, a.sx, a.M, rblk + 16 * RPW * wr + 4 * lq, m0 + 16 * TC * wc + li, rowend);
-  if (!via_lds) {
-#pragma unroll
-    for (int t = 0; t < RPW; ++t)
-#pragma unroll
-      for (int c = 0; c < TC; ++c) {
-        const int m = m0 + 16 * (TC * wc + c) + li;
-        const int n0 = rblk + 16 * (RPW * wr + t) + 4 * lq;
-        if (m < a.M && n0 < rowend) store4e(MD.Y, MD.ldy, MD.sw != nullptr, MD.vec_store, a, es, t, c, acc[t][c], m, n0, rowend);
-      }
-    return;
-  }
-  barrier_vm_lgkm0<0>();  // every wave's last operand reads and copies are done
-  if (!idle) out_tile_write<RPW, TC, kB2Rows / 8>(big_lds, acc, es, MD.sw != nullptr, wr, wc, li, lq);
-  barrier_vm_lgkm0<0>();
-  out_tile_store<kB2Rows / 8, 512>(big_lds, ntok, m0, a.M, rblk, rowend, MD.Y, MD.ldy);
-}
-
-// The large-M kernels' dynamic LDS above the default limit is a per-device function
-// attribute: set once per (device, kernel instance), under std::call_once, so that host
-// threads making their first large-M call together do not race.
-constexpr int kMaxDevices = 64;
-std::once_flag g_big_lds_once[kMaxDevices][2][4];  // [device][tiled][kernel instance]
-hipError_t g_big_lds_rc[kMaxDevices][2][4];
-
-template <typename KernelT>
-hipError_t set_big_lds(KernelT k, int tiled, int which, int lds) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::call_once(g_big_lds_once[dev][tiled][which], [&] {
-    g_big_lds_rc[dev][tiled][which] =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  });
-  return g_big_lds_rc[dev][tiled][which];
-}
-
-hipError_t launch_big2(const GemmArgs& a, hipStream_t s) {
-  static_assert(kB2Lds <= 160 * 1024, "LDS of a CU");
-  if (!a.tiled) return hipErrorInvalidValue;  // the planner sends row-major weights to the 128 x 256 kernel
-  const bool gr = a.nmat > 1;
-  auto k = gr ? spense_gemm_big2_kernel<true> : spense_gemm_big2_kernel<false>;
-  hipError_t e = set_big_lds(k, 1, gr ? 3 : 2, kB2Lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3(a.groups), dim3(512), kB2Lds, s, a);
-  return hipGetLastError();
 }
 
 template <int WV>

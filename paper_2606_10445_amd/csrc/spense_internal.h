@@ -109,6 +109,9 @@ struct LaunchShape {
   int xres;     // row-split kernel, one token tile: >0 = the activations of all xres chunks stay in LDS
 };
 
+// The 256 x 256 large-M kernel (LaunchShape::big == 2).
+hipError_t launch_big2(const GemmArgs& a, hipStream_t s);
+
 hipError_t launch_gemm(int dtype, const LaunchShape& ls, const GemmArgs& a, hipStream_t s);
 
 // Record an error message for spense_last_error (printf format) and return code.
