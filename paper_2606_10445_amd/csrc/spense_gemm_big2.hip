@@ -11,43 +11,46 @@ namespace {
 // token tiles, 128 accumulators).  Each B fragment read from LDS feeds 8 MMAs, each A
 // fragment 4.  Tiled weight layout only.
 //
-// The CU's load path moves about 57 bytes per clock from L2 with 16-byte-per-lane loads,
-// into registers or straight into LDS alike, but a load instruction costs at least ~18
-// clocks however few bytes it moves (a 4-byte-per-lane load moves 256 bytes in ~32; all
-// measured on MI355X).  So every load here moves 1 KB: per 128-column step a wave issues 4
-// activation blocks and, for its 2 row tiles, the 2:4 value blocks or both dense halves;
-// a 2:4 step's metadata (256 bytes per row tile) takes 4 more loads, one on each of waves
-// 0-3, each gathering the pieces of 4 row tiles.  6.5 loads per 2:4 step (52 KB per
-// workgroup) against ~1.07k clocks of its 256 MMAs.
+// What bounds a step (all measured on MI355X): the CU's load path moves about 57 bytes per
+// clock from L2 and a load instruction costs at least ~18 clocks however few bytes it moves,
+// so every copy moves 1 KB; a wave reads LDS at ~25 bytes per clock (16 bytes a lane) alone on
+// its SIMD and two at ~45 together; copies into LDS and reads from it do not slow each other;
+// the matrix cores take ~24 clocks per 2:4 and ~45 per dense instruction on random data with
+// every CU busy (17 and 32 on zeros: the clock gives way).  A step's copies, reads and MMAs
+// are each close to its MMA time, so they have to run at once, and the two kinds of steps do
+// that in two ways:
+//   - 2:4 steps (52 KB of copies, 147 KB of reads, 256 MMAs): every wave reads the next
+//     step's B fragments into a second register set and the A fragments two row tiles ahead
+//     between its MMAs, and spreads its copies over the step; one barrier per step, early in
+//     it.  With copies and B reads bunched in the second half of the step it took 0.85 us on
+//     5120 x 25600 at M = 2048, spread 0.80 (0.95 with all reads at the start of the step).
+//   - dense steps (64 KB, 192 KB, 256 MMAs of twice the length): no registers for a second B
+//     set and whole A tiles, so the waves of a SIMD take turns: waves 4-7 run one slot behind
+//     waves 0-3, and while one half issues the 32 MMAs of a step back to back, the other reads
+//     its fragments and issues its copies.  gate/up with every row dense, M = 2048: 259 ->
+//     231 us, 2.3 PFLOP/s, in a step the random-data MMA rate above; M = 300 66 -> 54 us.
+// Measured, before (both kinds: reads one row tile ahead, copies in two bunches) -> after, us:
+// gate/up M = 300 / 512 / 2048 64 / 69 / 211 -> 51 / 59 / 206, down M = 2048 212 -> 189, o
+// 76 -> 69, q 75 -> 66.
 //
-// Per-wave timelines showed every wave waiting at the barrier for the loads when they had
-// one step to land in, so the 2:4 steps run three stages deep (loads two steps ahead; a
-// stage is 52 KB: activations, values, metadata) and the dense steps, whose stage is 64 KB
-// and whose MMAs take twice as long, two.  Within a step the loads go out early: the
-// activation blocks before the first group of 4 MMAs, the weight blocks before the third.
-// An input-split weight switches from the first layout to the second once, after a
-// barrier.  The per-lane offsets are loop-invariant; the step's offset travels in the
-// scalar offset.  The barrier at the start of a step waits for this wave's loads of the
-// step and for its LDS reads of the previous step.
+// The activations have two stages (the B fragments of a step are in registers before its
+// MMAs, so its stage is free again half a step in), the weights four (2:4, 20 KB each) or
+// three (dense, 32 KB): they come from HBM or the MALL and need the longer lead.
 constexpr int kB2Rows = 256, kB2Tokens = 256, kB2RowTiles = 16;
-constexpr int kB2XSlot = kB2Tokens * 128;                                      // activations of one step
-constexpr int kB2SStage = kB2XSlot + kB2RowTiles * 1024 + kB2RowTiles * 256;  // + 2:4 values, metadata
-constexpr int kB2DStage = kB2XSlot + kB2RowTiles * 2048;                       // + both dense halves
-constexpr int kB2Lds = 3 * kB2SStage > 2 * kB2DStage ? 3 * kB2SStage : 2 * kB2DStage;
+constexpr int kB2XSlot = kB2Tokens * 128;                            // activations of one step
+constexpr int kB2SWgt = kB2RowTiles * 1024 + kB2RowTiles * 256;      // 2:4 values, metadata of one step
+constexpr int kB2DWgt = kB2RowTiles * 2048;                          // both dense halves of one step
+constexpr int kB2Lds = 2 * kB2XSlot + (4 * kB2SWgt > 3 * kB2DWgt ? 4 * kB2SWgt : 3 * kB2DWgt);
 
 // GR: a grouped launch (several weights sharing X and K): up to kMaxRegions regions, each
 // reading its weight's buffers, output and scales from a.mat[R.mat].
 template <bool GR>
 __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
-  constexpr int WV = 8, NT = kB2RowTiles, RPW = 8, TC = 4;
-  constexpr int TU = NT / WV;                // row tiles whose weights a wave copies
-  constexpr int XI = kB2XSlot / 1024 / WV;  // 1 KB activation blocks per wave per step
-  constexpr int MW = NT * 256 / 1024;       // waves that copy a 2:4 step's metadata
-  static_assert(XI + 2 * TU == RPW, "eight loads per dense step");
-  static_assert(XI == 4 && TU == 2 && MW <= WV, "load schedule");
+  constexpr int RPW = 8, TC = 4;  // row tiles and token tiles of a wave
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int li = lane & 15, lq = lane >> 4;
-  const int wr = wave & 1, wc = wave >> 1;
+  const bool late = wave >= 4;  // dense steps: the half of the waves that runs one slot behind
+  const int w4 = wave & 3, wr = wave >> 2, wc = w4 ^ (2 * wr);
   // Workgroups [0, hg0): 256 x 256 tiles, in the XCD-aware order when it is on.  From
   // hg0 on (dispatched last, so that they fill the tail of the grid): the row blocks
   // hrb0 .. of the last region as 256 x 128 tiles, hper per row block; their waves of
@@ -95,184 +98,231 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
 #pragma unroll
     for (int c = 0; c < TC; ++c) acc[t][c] = (v4f){0.f, 0.f, 0.f, 0.f};
 
-  const int n_sp = (kbound + 127) / 128, n_de = (K - kbound + 127) / 128, nst = n_sp + n_de;
+  const int n_sp = (kbound + 127) / 128, n_de = (K - kbound + 127) / 128;
   const int nch_sp = (n_sp + 3) / 4, nch_de = (n_de + 3) / 4;
 
-  // loop-invariant per-lane offsets (kOOB for rows past M or row tiles past the region)
-  uint32_t xo[XI];
-  int xb[XI];  // the column (bytes) of this lane's 16-byte block inside the step
-#pragma unroll
-  for (int i = 0; i < XI; ++i) {
-    const int blk = wave * XI + i;
-    const int r = 8 * blk + (lane >> 3), b = (lane & 7) ^ ((r >> 1) & 7);
-    const int m = m0 + r;
-    xb[i] = 16 * b;
-    xo[i] = m < a.M && r < ntok ? (uint32_t)((int64_t)m * a.ldx_b + 16 * b) : kOOB;
-  }
-  uint32_t vo[TU], dlo[TU];
-#pragma unroll
-  for (int u = 0; u < TU; ++u) {
-    const int r0 = rblk + 16 * (TU * wave + u);
-    const bool ok = r0 < rowend;
-    vo[u] = ok ? (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 4096u + 16u * lane : kOOB;
-    dlo[u] = ok && r0 >= R.dense_row_off ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
-                                          : kOOB;
-  }
-  // a 2:4 step's metadata: wave w < MW copies the 256-byte pieces of row tiles 4w .. 4w + 3
-  // (lane l: 16 bytes of tile 4w + l / 16); a tile's piece for step s sits 256 s bytes into
-  // its metadata
-  uint32_t mo1 = kOOB;
-  if (wave < MW) {
-    const int r0 = rblk + 16 * (4 * wave + (lane >> 4));
-    if (r0 < rowend) mo1 = (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 1024u + 16u * li;
-  }
+  uint8_t* const sx = big_lds;                 // two activation stages
+  uint8_t* const sw = big_lds + 2 * kB2XSlot;  // weight stages: values then metadata (four), or both dense halves (three)
 
-  // Load j of this wave for 2:4 step sn into stage stg: activation blocks (j < 4), the value
-  // blocks of its two row tiles (j = 4, 5), the metadata gather (j = 6, waves 0-3).
-  auto sp_load = [&](auto j_const, int sn, uint8_t* stg) __attribute__((always_inline)) {
-    constexpr int j = decltype(j_const)::value;
-    if (sn >= n_sp) return;  // uniform
-    if constexpr (j < XI) {
-      const int ks = 128 * sn;
-      uint32_t off = xo[j];
-      if (ks + 128 > kbound) off = ks + xb[j] < kbound ? off : kOOB;  // the region's last, partial step
-      lds_load16<0>(rx, stg + (wave * XI + j) * 1024, off, ks);
-    } else if constexpr (j < XI + TU) {
-      constexpr int u = j - XI;
-      lds_load16<kTiledNT>(rv, stg + kB2XSlot + (TU * wave + u) * 1024, vo[u], 1024 * sn);
-    } else {
-      if (wave < MW) lds_load16<kTiledNT>(rm, stg + kB2XSlot + NT * 1024 + wave * 1024, mo1, 256 * sn);
-    }
-  };
-  // Load j of this wave for dense step sn into stage stg: activation blocks (j < 4), then
-  // the two halves of its two row tiles.
-  auto de_load = [&](auto j_const, int sn, uint8_t* stg) __attribute__((always_inline)) {
-    constexpr int j = decltype(j_const)::value;
-    if (sn >= nst) return;  // uniform
-    if constexpr (j < XI) {
-      const int ks = kbound + 128 * (sn - n_sp);
-      uint32_t off = xo[j];
-      if (ks + 128 > K) off = ks + xb[j] < K ? off : kOOB;
-      lds_load16<0>(rx, stg + (wave * XI + j) * 1024, off, ks);
-    } else {
-      constexpr int u = (j - XI) % TU, half = (j - XI) / TU;
-      lds_load16<kTiledNT>(rd, stg + kB2XSlot + (TU * wave + u) * 2048 + 1024 * half, dlo[u],
-                           2048 * (sn - n_sp) + 1024 * half);
-    }
-  };
+  const uint8_t* const xr = sx + (16 * TC * wc + li) * 128;  // (r >> 1) & 7 of the wave's rows r is (li >> 1) & 7
+  const int xc0 = (lq ^ ((li >> 1) & 7)) << 4, xc1 = ((4 + lq) ^ ((li >> 1) & 7)) << 4;
 
-  // B fragments of the wave's 4 token tiles from a stage
-  auto read_b = [&](v8i (&bq)[TC], const uint8_t* xs) __attribute__((always_inline)) {
-#pragma unroll
-    for (int c = 0; c < TC; ++c) {
-      const int r = 16 * (TC * wc + c) + li;
-      bq[c] = cat8(*reinterpret_cast<const v4i*>(xs + r * 128 + ((lq ^ ((r >> 1) & 7)) << 4)),
-                   *reinterpret_cast<const v4i*>(xs + r * 128 + (((4 + lq) ^ ((r >> 1) & 7)) << 4)));
-    }
-  };
-
-  // 2:4 step s from stage cur; the loads of step s + 2 go to stage nxt.  Per row tile t the
-  // A fragment of tile t + 1 is read (other register set) before the 4 MMAs of tile t.
-  // ACT = false: a wave without tokens (token quarters past a 128- or 192-token tile) only copies.
-  auto sp_step = [&](auto act_const, int s, const uint8_t* cur, uint8_t* nxt) __attribute__((always_inline)) {
+  // The 2:4 steps.  ACT = false (both run functions): a wave without tokens (token quarters
+  // past a 128- or 192-token tile) only copies and keeps the barriers.
+  auto run_sparse = [&](auto act_const) __attribute__((always_inline)) {
     constexpr bool ACT = decltype(act_const)::value;
-    // this wave's loads of step s have landed once at most those of step s + 1 are pending
-    if (s + 1 < n_sp) {
-      if (wave < MW)
-        barrier_vm_lgkm0<XI + TU + 1>();
+    constexpr int NW = 4, AQ = 4, AD = 2, TB = 2;  // weight stages, A register sets, row tiles read ahead, barrier
+    // This wave's copies (loop-invariant per-lane offsets, kOOB for rows past M or row tiles
+    // past the region): activation blocks 4 wave .. 4 wave + 3 (8 tokens each), the values of
+    // row tiles 2 wave and 2 wave + 1 and, waves 0-3, the metadata pieces of row tiles 4 wave
+    // .. 4 wave + 3 (lane l: 16 bytes of tile 4 wave + l / 16, 256 s bytes in for step s).
+    const int xb = 16 * ((lane & 7) ^ (lane >> 4));  // column of this lane's 16 bytes in a step; odd blocks xb ^ 64
+    uint32_t xo[4], wo[2], mo = kOOB;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 32 * wave + 8 * i + (lane >> 3), m = m0 + r;
+      xo[i] = m < a.M && r < ntok ? (uint32_t)((int64_t)m * a.ldx_b + (xb ^ (64 * (i & 1)))) : kOOB;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r0 = rblk + 16 * (2 * wave + u);
+      wo[u] = r0 < rowend ? (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 4096u + 16u * lane : kOOB;
+    }
+    if (wave < 4) {
+      const int r0 = rblk + 16 * (4 * wave + (lane >> 4));
+      if (r0 < rowend) mo = (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 1024u + 16u * li;
+    }
+    // A copy past the last step reads (and writes) zeros, so that every step issues the same
+    // number of loads.
+    auto x_copy = [&](auto i_const, int s, int st) __attribute__((always_inline)) {
+      constexpr int i = decltype(i_const)::value;
+      uint32_t off = xo[i];
+      if (128 * s + 128 > kbound) off = 128 * s + (xb ^ (64 * (i & 1))) < kbound ? off : kOOB;
+      lds_load16<0>(rx, sx + st * kB2XSlot + (4 * wave + i) * 1024, off, 128 * s);
+    };
+    auto w_copy = [&](auto u_const, int s, int k) __attribute__((always_inline)) {
+      constexpr int u = decltype(u_const)::value;
+      lds_load16<kTiledNT>(rv, sw + k * kB2SWgt + (2 * wave + u) * 1024, s < n_sp ? wo[u] : kOOB, 1024 * s);
+    };
+    auto m_copy = [&](int s, int k) __attribute__((always_inline)) {
+      if (wave < 4)
+        lds_load16<kTiledNT>(rm, sw + k * kB2SWgt + kB2RowTiles * 1024 + wave * 1024, s < n_sp ? mo : kOOB, 256 * s);
+    };
+    auto wait_w = [&](auto n_const) __attribute__((always_inline)) {  // all but the last n steps' weight copies
+      constexpr int n = decltype(n_const)::value;
+      if (wave < 4)
+        wait_vm<3 * n>();
       else
-        barrier_vm_lgkm0<XI + TU>();
-    } else {
-      barrier_vm_lgkm0<0>();
-    }
-    v8i bq[TC];
-    const uint8_t* vl = cur + kB2XSlot + (RPW * wr) * 1024 + 16 * lane;
-    const uint8_t* ml = cur + kB2XSlot + NT * 1024 + (RPW * wr) * 256 + 16 * li + 4 * lq;
-    v4i av[2];
-    int aix[2];
+        wait_vm<2 * n>();
+    };
+    v8i bq[2][TC];
+    v4i av[AQ];
+    int aix[AQ];
+    auto read_b = [&](v8i& b, int st, int c) __attribute__((always_inline)) {
+      const uint8_t* p = xr + st * kB2XSlot + c * 2048;
+      b = cat8(*reinterpret_cast<const v4i*>(p + xc0), *reinterpret_cast<const v4i*>(p + xc1));
+    };
+    auto read_a = [&](auto q_const, int t, int k) __attribute__((always_inline)) {
+      constexpr int q = decltype(q_const)::value;
+      av[q] = *reinterpret_cast<const v4i*>(sw + k * kB2SWgt + (RPW * wr + t) * 1024 + 16 * lane);
+      aix[q] = *reinterpret_cast<const int*>(sw + k * kB2SWgt + kB2RowTiles * 1024 + (RPW * wr + t) * 256 + 16 * li + 4 * lq);
+    };
+    static_for<4>([&](auto i) { x_copy(i, 0, 0); });
+    static_for<2>([&](auto u) { w_copy(u, 0, 0); });
+    m_copy(0, 0);
+    static_for<4>([&](auto i) { x_copy(i, 1, 1); });
+    static_for<2>([&](auto u) { w_copy(u, 1, 1); });
+    m_copy(1, 1);
+    static_for<2>([&](auto u) { w_copy(u, 2, 2); });
+    if (wave < 4)
+      wait_vm<4 + 3 + 2>();
+    else
+      wait_vm<4 + 2 + 2>();
+    barrier_lgkm0();
     if constexpr (ACT) {
-      read_b(bq, cur);
-      av[0] = *reinterpret_cast<const v4i*>(vl);
-      aix[0] = *reinterpret_cast<const int*>(ml);
+      static_for<TC>([&](auto c) { read_b(bq[0][decltype(c)::value], 0, decltype(c)::value); });
+      static_for<AD>([&](auto t) { read_a(t, decltype(t)::value, 0); });
     }
-    static_for<RPW>([&](auto t_const) {
-      constexpr int t = decltype(t_const)::value;
-      constexpr int q = t & 1;
-      if constexpr (ACT && t + 1 < RPW) {
-        av[1 - q] = *reinterpret_cast<const v4i*>(vl + (t + 1) * 1024);
-        aix[1 - q] = *reinterpret_cast<const int*>(ml + (t + 1) * 256);
-      }
-      if constexpr (t == 0) static_for<XI>([&](auto j) { sp_load(j, s + 2, nxt); });
-      if constexpr (t == 2) {
-        sp_load(std::integral_constant<int, XI>(), s + 2, nxt);
-        sp_load(std::integral_constant<int, XI + 1>(), s + 2, nxt);
-        sp_load(std::integral_constant<int, XI + 2>(), s + 2, nxt);
-      }
-      if constexpr (ACT) {
+    int k = 0;  // weight stage of step s
+    // Step s with the B fragments of set P (its activation stage too).  Before row tile TB, a
+    // barrier: the next step's blocks have landed for every wave, and the stages of this
+    // step's activations and the last step's weights are free.  After it the next step's B
+    // fragments are read between the MMAs, and the copies of step s + 2 (activations) and
+    // s + 3 (weights) go out, spread over the step.
+    auto step = [&](auto p_const, const int s) __attribute__((always_inline)) {
+      constexpr int P = decltype(p_const)::value;
+      const int kn = k == NW - 1 ? 0 : k + 1, kp = k == 0 ? NW - 1 : k - 1;
+      static_for<RPW>([&](auto t_const) {
+        constexpr int t = decltype(t_const)::value;
+        if constexpr (t == 0) m_copy(s + 2, k < 2 ? k + 2 : k - 2);
+        if constexpr (t == TB) {
+          wait_w(std::integral_constant<int, 1>());
+          asm volatile("s_barrier" ::: "memory");
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (ACT) {
+          typedef std::integral_constant<int, (t + AD) % AQ> Q;
+          if constexpr (t + AD < RPW)
+            read_a(Q(), t + AD, k);
+          else
+            read_a(Q(), t + AD - RPW, kn);
+          if constexpr (t >= 3 && t < 3 + TC) read_b(bq[1 - P][t - 3], 1 - P, t - 3);
+        }
+        if constexpr (t >= TB && t < TB + 4) x_copy(std::integral_constant<int, t - TB>(), s + 2, P);
+        if constexpr (t >= 6) w_copy(std::integral_constant<int, t - 6>(), s + 3, kp);
+        if constexpr (ACT) {
+          constexpr int q = t % AQ;
 #pragma unroll
-        for (int c = 0; c < TC; ++c)
-          acc[t][c] = mma_sparse(av[q], bq[c], acc[t][c], aix[q], std::integral_constant<int, kFP8>());
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    });
+          for (int c = 0; c < TC; ++c)
+            acc[t][c] = mma_sparse(av[q], bq[P][c], acc[t][c], aix[q], std::integral_constant<int, kFP8>());
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      k = kn;
+    };
+    int s = 0;
+    for (; s + 2 <= n_sp; s += 2) {
+      step(std::integral_constant<int, 0>(), s);
+      step(std::integral_constant<int, 1>(), s + 1);
+    }
+    if (s < n_sp) step(std::integral_constant<int, 0>(), s);
+    xdl_fence();
+    barrier_vm_lgkm0<0>();  // every wave is done with the stages, and no copy is in flight
   };
 
-  // dense step s from stage cur; the loads of step s + 1 go to stage nxt
-  auto de_step = [&](auto act_const, int s, const uint8_t* cur, uint8_t* nxt) __attribute__((always_inline)) {
+  // The dense steps.  Waves 0-3 copy the activations (eight blocks each, of tokens [64 w4,
+  // 64 w4 + 64)), waves 4-7 the weights (both halves of row tiles 4 w4 .. 4 w4 + 3).
+  auto run_dense = [&](auto act_const) __attribute__((always_inline)) {
     constexpr bool ACT = decltype(act_const)::value;
-    barrier_vm_lgkm0<0>();
-    v8i bq[TC];
-    const uint8_t* wl = cur + kB2XSlot + (RPW * wr) * 2048 + 16 * lane;
-    v4i alo[2], ahi[2];
-    if constexpr (ACT) {
-      read_b(bq, cur);
-      alo[0] = *reinterpret_cast<const v4i*>(wl);
-      ahi[0] = *reinterpret_cast<const v4i*>(wl + 1024);
-    }
-    static_for<RPW>([&](auto t_const) {
-      constexpr int t = decltype(t_const)::value;
-      constexpr int q = t & 1;
-      if constexpr (ACT && t + 1 < RPW) {
-        alo[1 - q] = *reinterpret_cast<const v4i*>(wl + (t + 1) * 2048);
-        ahi[1 - q] = *reinterpret_cast<const v4i*>(wl + (t + 1) * 2048 + 1024);
-      }
-      if constexpr (t == 0 || t == 2) {
-        de_load(std::integral_constant<int, 2 * t>(), s + 1, nxt);
-        de_load(std::integral_constant<int, 2 * t + 1>(), s + 1, nxt);
-        de_load(std::integral_constant<int, 2 * t + 2>(), s + 1, nxt);
-        de_load(std::integral_constant<int, 2 * t + 3>(), s + 1, nxt);
-      }
-      if constexpr (ACT) {
+    const int xb = 16 * ((lane & 7) ^ (lane >> 4));
+    uint32_t lo[8];
 #pragma unroll
-        for (int c = 0; c < TC; ++c)
-          acc[t][c] = mma_dense(cat8(alo[q], ahi[q]), bq[c], acc[t][c], std::integral_constant<int, kFP8>());
+    for (int i = 0; i < 8; ++i) {
+      if (late) {
+        const int r0 = rblk + 16 * (4 * w4 + (i >> 1));
+        lo[i] = r0 < rowend && r0 >= R.dense_row_off
+                    ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
+                    : kOOB;
+      } else {
+        const int r = 64 * w4 + 8 * i + (lane >> 3), m = m0 + r;
+        lo[i] = m < a.M && r < ntok ? (uint32_t)((int64_t)m * a.ldx_b + kbound + (xb ^ (64 * (i & 1)))) : kOOB;
+      }
+    }
+    auto x_copy = [&](int s) __attribute__((always_inline)) {
+      static_for<8>([&](auto i_const) {
+        constexpr int i = decltype(i_const)::value;
+        uint32_t off = lo[i];
+        if (kbound + 128 * s + 128 > K) off = kbound + 128 * s + (xb ^ (64 * (i & 1))) < K ? off : kOOB;
+        lds_load16<0>(rx, sx + (s & 1) * kB2XSlot + (8 * w4 + i) * 1024, off, 128 * s);
+      });
+    };
+    auto w_copy = [&](int s, int k) __attribute__((always_inline)) {
+      static_for<8>([&](auto i_const) {
+        constexpr int i = decltype(i_const)::value;
+        lds_load16<kTiledNT>(rd, sw + k * kB2DWgt + (8 * w4 + i) * 1024, lo[i], 2048 * s + 1024 * (i & 1));
+      });
+    };
+    if (!late) {
+      x_copy(0);
+      wait_vm<0>();
+    } else {
+      w_copy(0, 0);
+      if (n_de > 1) {
+        w_copy(1, 1);
+        wait_vm<8>();
+      } else {
+        wait_vm<0>();
+      }
+    }
+    barrier_lgkm0();
+    if (late) barrier_lgkm0();
+    int k = 0;  // weight stage of step s (activation stage s % 2)
+    for (int s = 0; s < n_de; ++s) {
+      v8i bq[TC], av[RPW];
+      if constexpr (ACT) {
+        const uint8_t* wl = sw + k * kB2DWgt + (RPW * wr) * 2048 + 16 * lane;
+#pragma unroll
+        for (int c = 0; c < TC; ++c) {
+          const uint8_t* p = xr + (s & 1) * kB2XSlot + c * 2048;
+          bq[c] = cat8(*reinterpret_cast<const v4i*>(p + xc0), *reinterpret_cast<const v4i*>(p + xc1));
+        }
+#pragma unroll
+        for (int t = 0; t < RPW; ++t)
+          av[t] = cat8(*reinterpret_cast<const v4i*>(wl + t * 2048), *reinterpret_cast<const v4i*>(wl + t * 2048 + 1024));
       }
       __builtin_amdgcn_sched_barrier(0);
-    });
+      // activations of step s + 1 (awaited after this step's MMAs), weights of step s + 2
+      if (!late) {
+        if (s + 1 < n_de) x_copy(s + 1);
+      } else if (s + 2 < n_de) {
+        w_copy(s + 2, k == 0 ? 2 : k - 1);
+        wait_vm<8>();
+      } else {
+        wait_vm<0>();
+      }
+      barrier_lgkm0();
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (ACT) {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int t = 0; t < RPW; ++t)
+#pragma unroll
+          for (int c = 0; c < TC; ++c)
+            acc[t][c] = mma_dense(av[t], bq[c], acc[t][c], std::integral_constant<int, kFP8>());
+        __builtin_amdgcn_s_setprio(0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (!late) wait_vm<0>();
+      barrier_lgkm0();
+      k = k == 2 ? 0 : k + 1;
+    }
+    if (!late) barrier_lgkm0();
+    xdl_fence();
   };
 
   auto run = [&](auto act_const) __attribute__((always_inline)) {
-    int s = 0;
-    if (n_sp > 0) {
-      static_for<XI + TU + 1>([&](auto j) { sp_load(j, 0, big_lds); });
-      static_for<XI + TU + 1>([&](auto j) { sp_load(j, 1, big_lds + kB2SStage); });
-      int k = 0;  // stage of step s
-      for (; s < n_sp; ++s) {
-        const int k2 = k == 0 ? 2 : k - 1;  // stage of step s + 2
-        sp_step(act_const, s, big_lds + k * kB2SStage, big_lds + k2 * kB2SStage);
-        k = k == 2 ? 0 : k + 1;
-      }
-      xdl_fence();
-    }
-    if (n_de > 0) {
-      if (n_sp > 0) barrier_vm_lgkm0<0>();  // every wave is done with the 2:4 stages
-      static_for<RPW>([&](auto j) { de_load(j, s, big_lds); });
-      for (; s < nst; ++s) {
-        const int k = (s - n_sp) & 1;
-        de_step(act_const, s, big_lds + k * kB2DStage, big_lds + (1 - k) * kB2DStage);
-      }
-      xdl_fence();
-    }
+    if (n_sp > 0) run_sparse(act_const);
+    if (n_de > 0) run_dense(act_const);
   };
   // bf16 output with 16-byte aligned rows leaves through LDS as whole token rows
   // (out_tile_write); the waves of token quarters past the tile's tokens (2 and 3 of a 256

@@ -233,6 +233,19 @@ __device__ __forceinline__ void barrier_vm() {
   asm volatile("s_barrier" ::: "memory");
 }
 
+// Wait until at most N of this wave's vector-memory operations are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// Workgroup barrier after this wave's LDS accesses; vector-memory operations stay in flight.
+__device__ __forceinline__ void barrier_lgkm0() {
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8));
+  asm volatile("s_barrier" ::: "memory");
+}
+
 // As barrier_vm, and also wait for this wave's LDS accesses (lgkmcnt(0)).
 template <int N>
 __device__ __forceinline__ void barrier_vm_lgkm0() {
