@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspense.so")
-SOURCES = ["spense_api.cpp", "spense_gemm.hip", "spense_gemm_big2.hip", "spense_compress.hip", "spense_quant.hip",
+SOURCES = ["spense_api.cpp", "spense_gemm.hip", "spense_gemm_big2.hip", "spense_gemm_mid.hip", "spense_compress.hip", "spense_quant.hip",
            "spense_index.hip", "spense_obs.hip",
            "spense_noalloc.hip"]
 ARCH = "gfx950"

@@ -511,7 +511,11 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
                               ? ceil_div(dense_begin, 256) + ceil_div(N - dense_begin, 256)
                               : ceil_div(N, 256);
     const int64_t tb256 = ceil_div(M, 256);
-    if (rb256 * tb256 >= 160) big = 2;
+    // With the step pipelines of now the line is where the 128 x 256 grid needs a second
+    // round: 5120 x 8192 at M = 1700 (140 tiles) 101 -> 71; at 128 and 120 tiles that grid
+    // stays ahead (8192 x 5120 at M = 1024 44 against 51, 5120 x 25600 at M = 1300 158
+    // against 178).
+    if (rb256 * tb256 > 128) big = 2;
   }
   // Two 64-token halves per row-split workgroup (spense_gemm_rows2_kernel: 128 tokens a
   // block, four token tiles, one row tile, eight waves).  Each weight chunk
@@ -579,6 +583,51 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   if (ov.kernel == 1 || ov.kernel == 2 || rows2) big = 0;
   if (ov.kernel == 3) big = 1;  // fp8 (checked by read_override)
   if (ov.kernel == 4) big = tiled ? 2 : 1;  // the 256 x 256 kernel reads the tiled layout
+  // 128 x 128 tiles (spense_gemm_mid_kernel, tiled fp8), one round of workgroups: about 8 us
+  // + 0.43 us per 128 columns (measured from K = 2048 to 25600 and 1024 to 12288 rows).
+  // Without K slices it wins where the weight and M give 144 to 256 tiles (176 at two token
+  // blocks, 112 above 1536 tokens), measured (us, before -> this kernel): 8192 x 5120 at M =
+  // 288 / 352 / 448 / 512 (192, 192, 256, 256 tiles) 31 / 31 / 37 / 40 -> 28 / 28 / 27 / 29,
+  // at M = 160 / 224 (128) 22 / 26 against 27 / 27; 5120 x 8192 at M = 352 (120) 29 against
+  // 34, 448 / 640 / 768 (160-240) 37 / 46 / 45 -> 34 / 35 / 38; 12288 x 4096 at M = 200 (192)
+  // 26 -> 22; 10240 x 5120 at M = 224 (160, two blocks) 27 against 28, 288 (240) 33 -> 29;
+  // 3072 x 3072 at M = 400 (96) 14 against 17, 800 (168) 24 -> 17; 1024 x 5120 at M = 1536 /
+  // 2048 (96, 128) 22 against 29 and 35 -> 29; a second round always loses (8192 x 5120 at
+  // M = 640, 320 tiles: 38 against 48).  With fewer tiles and a long K (28 chunks of 512) it
+  // runs in K slices, the number that a model of the slices' steps and the partial sums'
+  // round trip (3 us + 0.65 us per MB) makes cheapest: 5120 x 25600 at M = 80 / 128 / 224 /
+  // 288 36 / 39 / 57 / 75 -> 30 / 35 / 49 / 64; 4096 x 14336 at M = 100 / 200 26 / 32 -> 24 /
+  // 28.  Not at 129-192 tokens (5120 x 25600 at M = 160: 51 against 52) nor on shorter K (5120
+  // x 8192 at M = 128 / 256: 20 / 24 against 23 / 27).  The partial
+  // sums never need more than spense_gemm_noalloc's scratch.
+  int mid_ks = 0;  // K slices of the 128 x 128 kernel, 0: not used
+  if (ov.kernel == 0 && !ov.rt && !ov.waves && !ov.ct && ov.ksplit <= 1 && !ov.wused && !ov.wused_d && !ov.wused_s &&
+      !ov.u8 && !ov.xres && tiled && dtype == SPENSE_FP8_E4M3FN && M > 64) {
+    const int64_t rb = split == SPENSE_SPLIT_OUTPUT ? ceil_div(dense_begin, 128) + ceil_div(N - dense_begin, 128)
+                                                    : ceil_div(N, 128);
+    const int64_t tb = ceil_div(M, 128), wgs = rb * tb, steps = ceil_div(K, 128);
+    if (tb >= 2 && K >= 2048 && wgs <= kCUs && wgs >= (tb == 2 ? 176 : (M > 1536 ? 112 : 144))) {
+      mid_ks = 1;
+    } else if (ov.ksplit < 1 && wgs >= 16 && wgs < 144 && ceil_div(K, 512) >= 28 && M <= 320 && (M <= 128 || M > 192)) {
+      double best = 0;
+      for (int64_t S = 2; S <= 8 && S * wgs <= kCUs; ++S) {
+        const double bytes = 4.0 * (double)S * (double)M * (double)N;
+        if (bytes > (double)SPENSE_NOALLOC_SCRATCH_BYTES || S * wgs < 144) continue;
+        const double t = 0.43 * (double)ceil_div(steps, S) + 0.65e-6 * bytes;
+        if (mid_ks == 0 || t < best) {
+          best = t;
+          mid_ks = (int)S;
+        }
+      }
+    }
+  }
+  const bool mid = mid_ks > 0;
+  if (mid) {
+    // the two-half kernel's place (128 tokens a block there too), or the large-M kernels'
+    pl->ls.halves = rows2 || mid_ks > 1;
+    rows2 = false;
+    big = 3;
+  }
   pl->ls.big = big;
   if (rows2) {
     pl->ls.ct = 4;
@@ -587,8 +636,8 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
     pl->ls.waves = 8;
   }
   const int big_rows = big == 2 ? 256 : 128;  // rows of a large-M workgroup tile
-  if (big) pl->ls.waves = (big == 1 && ov.waves == 4) ? 4 : 8;
-  const int64_t tblocks = ceil_div(M, 256);
+  if (big) pl->ls.waves = (big == 1 && ov.waves == 4) ? 4 : (mid ? 12 : 8);
+  const int64_t tblocks = ceil_div(M, mid ? 128 : 256);
 
   Region regs[2];
   int nreg = 0;
@@ -654,6 +703,15 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
       if (wide || ov.xres == 2) pl->ls.xres = (int)chunks;
     }
   }
+  if (mid) {
+    int64_t chunks = 0;
+    for (int i = 0; i < nreg; ++i) chunks = std::max(chunks, ceil_div(regs[i].kbound, 512) + ceil_div(K - regs[i].kbound, 512));
+    ksplit = (int)std::max<int64_t>(1, std::min<int64_t>(mid_ks, chunks));
+    for (int i = 0; i < nreg; ++i) {
+      slice_cuts(regs[i], ksplit, 512, es, sparse_cost);
+      regs[i].nrb *= ksplit;
+    }
+  }
   // 256 x 256 kernel: the last row blocks of the last region may run as 256 x 128 tiles
   // after every 256 x 256 tile, to fill the grid's last round
   int64_t half_rb = 0, rbl = 0;
@@ -700,7 +758,7 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
     const int64_t T = tblocks;
     const int64_t GT = xcd_token_group(T);
     int64_t rbtot = -half_rb;  // row blocks of the full-size tiles
-    for (int i = 0; i < nreg; ++i) rbtot += ceil_div(regs[i].rows, big_rows);
+    for (int i = 0; i < nreg; ++i) rbtot += ceil_div(regs[i].rows, big_rows) * ksplit;
     if (GT > 0) {
       const int64_t RC = 8 / (T / GT), rbx = rbtot / RC * RC;
       if (rbx > 0) {
@@ -753,6 +811,7 @@ __attribute__((constructor)) void read_log_env() {
 
 const char* kernel_name(const spense::LaunchShape& ls) {
   if (ls.big == 2) return "large-M 256x256";
+  if (ls.big == 3) return ls.halves ? "row-split, two 64-token halves" : "large-M 128x128";
   if (ls.big == 1) return "large-M 128x256";
   if (ls.glu) return "row-split, gate/up paired";
   if (ls.rows == 2) return "row-split, two 64-token halves";
@@ -768,7 +827,7 @@ void log_plan(const char* what, int32_t dtype, int64_t M, int64_t N, int32_t spl
           what, dtype == SPENSE_FP8_E4M3FN ? "fp8" : "bf16", (long long)M, (long long)N, (long long)K,
           split == SPENSE_SPLIT_OUTPUT ? "output" : "input", (long long)dense_begin, tiled ? "tiled" : "row-major",
           kernel_name(ls), ls.ct, ls.rt, ls.waves, ls.big ? a.tblocks : ls.mblocks,
-          ls.big == 2 ? (a.btok > 0 ? a.btok : 256) : (ls.big ? 256 : (ls.rows == 2 ? 128 : 16 * ls.ct)), a.groups,
+          ls.big == 2 ? (a.btok > 0 ? a.btok : 256) : (ls.big == 3 ? 128 : ls.big ? 256 : (ls.rows == 2 ? 128 : 16 * ls.ct)), a.groups,
           a.nreg, a.nreg > 0 ? a.reg[0].ksplit : 1,
           ls.xres, ls.big == 2 ? a.groups - a.hg0 : 0, ws_bytes);
 }

@@ -1435,6 +1435,7 @@ hipError_t launch_big_wv(const GemmArgs& a, hipStream_t s) {
 
 hipError_t launch_big(const LaunchShape& ls, const GemmArgs& a, hipStream_t s) {
   if (ls.big == 2) return launch_big2(a, s);
+  if (ls.big == 3) return launch_mid(a, s);
   return ls.waves == 4 ? launch_big_wv<4>(a, s) : launch_big_wv<8>(a, s);
 }
 

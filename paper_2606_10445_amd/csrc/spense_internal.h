@@ -104,13 +104,17 @@ struct LaunchShape {
   int mblocks;  // grid.y
   int u8;       // eight instruction steps per batch of loads (single activation tile only)
   int rows;     // row-split workgroups with activations staged in LDS
-  int big;      // large-M kernels (fp8): 1 = 128-row x 256-token workgroup tiles, 2 = 256 x 256
+  int big;      // large-M kernels (fp8): 1 = 128-row x 256-token workgroup tiles, 2 = 256 x 256,
+                // 3 = 128 x 128 (tiled weights, K slices)
+  int halves;   // big == 3 where the two-half row-split kernel would otherwise run (the log's name for it)
   int glu;      // row-split kernel, gate and up paired: waves 0-3 gate tiles, 4-7 the same up tiles
   int xres;     // row-split kernel, one token tile: >0 = the activations of all xres chunks stay in LDS
 };
 
 // The 256 x 256 large-M kernel (LaunchShape::big == 2).
 hipError_t launch_big2(const GemmArgs& a, hipStream_t s);
+// The 128 x 128 kernel (LaunchShape::big == 3).
+hipError_t launch_mid(const GemmArgs& a, hipStream_t s);
 
 hipError_t launch_gemm(int dtype, const LaunchShape& ls, const GemmArgs& a, hipStream_t s);
 

@@ -1,0 +1,71 @@
+"""The 128 x 128 GEMM kernel (tiled fp8 between decode and the 256 x 256 grid) as the
+planner chooses it: bit for bit the row-split kernel's results on exact-integer data (their
+sums are exact in any order), and repeatable on random data."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def S():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2606_10445_amd as S
+    return S
+
+
+# (axis, M, N, K, dense_begin): 144 to 256 tiles without K slices, ragged rows, tokens and
+# columns, partial last steps of both kinds, all-2:4 and all-dense; then K slices (fewer
+# tiles, K from 28 chunks of 512), which may end on either side of the boundary.
+CASES = [(1, 257, 6500, 2080, 1056), (0, 385, 5000, 2048, 3000), (1, 513, 4608, 2048, 2048), (0, 300, 6528, 2048, 0),
+         (1, 640, 5120, 2112, 32), (0, 256, 11300, 2048, 8432), (1, 1537, 1100, 2304, 1728),
+         (1, 100, 2410, 14368, 10016), (1, 250, 1100, 14336, 14336), (0, 70, 2304, 14336, 1200), (1, 128, 2435, 15000, 96)]
+CASES = [(a, M, N, K // 32 * 32, db) for a, M, N, K, db in CASES]
+
+
+@pytest.mark.parametrize("axis,M,N,K,db", CASES)
+def test_planned_tiles_exact(S, axis, M, N, K, db, capfd):
+    print(f"[128x128] axis={axis} M={M} N={N} K={K} db={db}", file=sys.stderr, flush=True)
+    W, mask, X, sw, sx = gen.make_exact_int(41, M, M, N, K, gen.OUTPUT if axis == 0 else gen.INPUT, db, gen.FP8)
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    X, sw, sx = dev(X), dev(sw), dev(sx)
+    pw = S.tile(S.compress(dev(W), dev(mask), axis, db))
+    ref = S.gemm(X, pw, sw, sx, out_f32=True, plan=S.plan_override(kernel=2, ksplit=1))
+    prev = S.spense_set_log(1)
+    capfd.readouterr()
+    try:
+        y = S.gemm(X, pw, sw, sx, out_f32=True)
+        torch.cuda.synchronize()
+    finally:
+        S.spense_set_log(prev)
+    log = capfd.readouterr().err.strip().splitlines()[-1]
+    assert "waves=12" in log and "block_tokens=128" in log, log
+    assert torch.equal(y, ref)
+    for pad in (8, 3):  # whole-row stores, scalar stores; the padding is untouched
+        big = torch.full((M, N + pad), 7.0, dtype=torch.bfloat16, device="cuda")
+        S.gemm(X, pw, sw, sx, out=big[:, :N])
+        torch.cuda.synchronize()
+        assert torch.equal(big[:, :N], ref.bfloat16()), pad
+        assert torch.all(big[:, N:] == 7.0)
+
+
+@pytest.mark.parametrize("axis,M,N,K,db", [CASES[0], CASES[7]])
+def test_planned_tiles_repeatable(S, axis, M, N, K, db):
+    """Random data: the same bits every time, and within the fp32 sums' reordering (K
+    slices) of the row-split kernel: both are within 2^-12 of sum |x w| (the fp8
+    instructions' ~13 fraction bits), checked on the norm."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    draw = lambda *s: (torch.randn(s, generator=g, device="cuda") * 8).to(torch.float8_e4m3fn).view(torch.uint8)  # noqa: E731
+    W, X = draw(N, K), draw(M, K)
+    mask = torch.from_numpy(gen.random_mask_24(np.random.default_rng(3), N, K, gen.OUTPUT if axis == 0 else gen.INPUT, db)).cuda()
+    pw = S.tile(S.compress(W, mask, axis, db))
+    ref = S.gemm(X, pw, out_f32=True, plan=S.plan_override(kernel=2, ksplit=1))
+    first = S.gemm(X, pw, out_f32=True)
+    for _ in range(5):
+        assert torch.equal(S.gemm(X, pw, out_f32=True), first)
+    assert (first - ref).norm() <= 2.0 ** -12 * ref.norm()
