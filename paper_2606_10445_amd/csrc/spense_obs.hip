@@ -12,8 +12,8 @@
 //     triangular inverse of the reversed matrix, then a reversal back.  Both are blocked
 //     (64-wide diagonal blocks factored and inverted in LDS, everything else as fp32
 //     matrix-core products).
-//  2. The sweep, 64 columns at a time: a thread per row keeps the row's 64 weights of
-//     the block in registers and processes the columns in order (2:4 choice at each
+//  2. The sweep, 64 columns at a time: four lanes per row keep the row's 64 weights of
+//     the block in registers and process the columns in order (2:4 choice at each
 //     group's first column by the OBS error w^2 / U_mm^2, then the compensation inside
 //     the block); the block's scaled errors E then update every later column at once,
 //     W[:, j0+64:] -= E U[j0:j0+64, j0+64:], on the matrix cores.
@@ -68,7 +68,10 @@ struct GemmF32 {
 
 template <int BT, bool TB, bool LOWER, int TRI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int vec) {
-  constexpr int P = BT + 4;        // LDS row pitch (floats)
+  // LDS row pitch (floats): the four rows an operand read takes (k = 4 q + lane / 16) start
+  // 16 banks apart.  Columns of row kk sit at column ^ 16 (kk / 4 % 4), so that the rows 4
+  // apart that a transposing store writes do too.
+  constexpr int P = BT + 16;
   constexpr int TW = BT / 32;      // MFMA tiles per wave and dimension
   constexpr int NQ = BT / 64;      // 16-byte pieces per thread and operand per step
   __shared__ float As[2][16][P];   // As[kk][i]
@@ -107,8 +110,32 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int vec) {
     for (int c = 0; c < 4; ++c)
       if (!keep(kq + c)) out[c] = 0.0f;
   };
+  // Steps whose 16 columns lie inside every operand and off the triangular edges take plain
+  // 16-byte loads from pointers that advance by a step; the bounds and masks of the others
+  // cost more instructions than the step's 64 matrix instructions leave room for.
+  const bool inside = vec && i0 + BT <= g.m && j0 + BT <= g.n;
+  const float* pa[NQ];
+  const float* pb[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int slot = t + 256 * q;
+    pa[q] = g.A + (i0 + (slot >> 2)) * g.lda + (slot & 3) * 4;
+    pb[q] = TB ? g.B + (j0 + (slot >> 2)) * g.ldb + (slot & 3) * 4
+               : g.B + (int64_t)(slot / (BT / 4)) * g.ldb + j0 + (slot % (BT / 4)) * 4;
+  }
   auto load = [&](int s) __attribute__((always_inline)) {
     const int64_t k0 = (int64_t)s * 16;
+    if (inside && k0 >= klo && k0 + 16 <= khi && (!(TRI & 1) || k0 + 15 <= i0) && (!(TRI & 2) || k0 + 15 <= j0) &&
+        (!(TRI & 4) || k0 >= j0 + BT - 1)) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const float4 x = *reinterpret_cast<const float4*>(pa[q] + k0);
+        const float4 y = *reinterpret_cast<const float4*>(pb[q] + (TB ? k0 : k0 * g.ldb));
+        ra[q][0] = x.x, ra[q][1] = x.y, ra[q][2] = x.z, ra[q][3] = x.w;
+        rb[q][0] = y.x, rb[q][1] = y.y, rb[q][2] = y.z, rb[q][3] = y.w;
+      }
+      return;
+    }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int slot = t + 256 * q;
@@ -146,12 +173,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int vec) {
     for (int q = 0; q < NQ; ++q) {
       const int slot = t + 256 * q;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) As[buf][(slot & 3) * 4 + c][slot >> 2] = ra[q][c];
+      for (int c = 0; c < 4; ++c) As[buf][(slot & 3) * 4 + c][(slot >> 2) ^ (16 * (slot & 3))] = ra[q][c];
       if (TB) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) Bs[buf][(slot & 3) * 4 + c][slot >> 2] = rb[q][c];
+        for (int c = 0; c < 4; ++c) Bs[buf][(slot & 3) * 4 + c][(slot >> 2) ^ (16 * (slot & 3))] = rb[q][c];
       } else {
-        *reinterpret_cast<float4*>(&Bs[buf][slot / (BT / 4)][(slot % (BT / 4)) * 4]) =
+        const int kr = slot / (BT / 4);
+        *reinterpret_cast<float4*>(&Bs[buf][kr][((slot % (BT / 4)) * 4) ^ (16 * ((kr >> 2) & 3))]) =
             make_float4(rb[q][0], rb[q][1], rb[q][2], rb[q][3]);
       }
     }
@@ -176,9 +204,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int vec) {
       const int kk = q * 4 + (lane >> 4);
       float av[TW], bv[TW];
 #pragma unroll
-      for (int a = 0; a < TW; ++a) av[a] = As[buf][kk][wi + a * 16 + (lane & 15)];
+      for (int a = 0; a < TW; ++a) av[a] = As[buf][kk][(wi + a * 16 + (lane & 15)) ^ (16 * q)];
 #pragma unroll
-      for (int b = 0; b < TW; ++b) bv[b] = Bs[buf][kk][wj + b * 16 + (lane & 15)];
+      for (int b = 0; b < TW; ++b) bv[b] = Bs[buf][kk][(wj + b * 16 + (lane & 15)) ^ (16 * q)];
 #pragma unroll
       for (int a = 0; a < TW; ++a)
 #pragma unroll
@@ -187,28 +215,40 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int vec) {
     if (s + 1 < s1) store(buf ^ 1);
     __syncthreads();
   }
+  // C is read ahead of the stores, a row of tiles at a time: read next to its store, each
+  // element would wait for the store before it, which may alias (64 round trips a tile)
 #pragma unroll
-  for (int a = 0; a < TW; ++a)
+  for (int a = 0; a < TW; ++a) {
+    float c[TW][4];
 #pragma unroll
-    for (int b = 0; b < TW; ++b) {
-      const int64_t j = j0 + wj + b * 16 + (lane & 15);
+    for (int b = 0; b < TW; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t i = i0 + wi + a * 16 + 4 * (lane >> 4) + r;
-        if (i < g.m && j < g.n) {
-          float* c = g.C + i * g.ldc + j;
-          const float v = g.alpha * acc[a][b][r];
-          *c = g.beta == 0.0f ? v : g.beta * *c + v;
-        }
+        const int64_t i = i0 + wi + a * 16 + 4 * (lane >> 4) + r, j = j0 + wj + b * 16 + (lane & 15);
+        c[b][r] = g.beta != 0.0f && i < g.m && j < g.n ? g.C[i * g.ldc + j] : 0.0f;
       }
-    }
+#pragma unroll
+    for (int b = 0; b < TW; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t i = i0 + wi + a * 16 + 4 * (lane >> 4) + r, j = j0 + wj + b * 16 + (lane & 15);
+        const float v = g.alpha * acc[a][b][r];
+        if (i < g.m && j < g.n) g.C[i * g.ldc + j] = g.beta == 0.0f ? v : g.beta * c[b][r] + v;
+      }
+  }
 }
+
+// Output tiles of 128 from which they are used instead of 64: a workgroup takes ~0.9 us per
+// 16 columns of k on a 128 tile and a quarter of that on a 64 one, so 64 is faster until both
+// fill the CUs several times over (the factor at K = 5120: 128 tiles from 1 / 300 / 1024 on
+// 11.0 / 7.1 / 6.6 ms); beyond, 128 reads its operands half as often.
+constexpr int64_t kWideTiles = 1024;
 
 template <bool TB, bool LOWER, int TRI>
 hipError_t gemm_f32(const GemmF32& g, hipStream_t st) {
   if (g.m <= 0 || g.n <= 0) return hipSuccess;
   const int vec = (g.lda % 4 == 0) && (g.ldb % 4 == 0) && ((uintptr_t)g.A % 16 == 0) && ((uintptr_t)g.B % 16 == 0);
-  if (g.m >= 128 && g.n >= 128) {
+  if ((int64_t)((g.m + 127) / 128) * ((g.n + 127) / 128) >= kWideTiles) {
     const dim3 grid((unsigned)((g.n + 127) / 128), (unsigned)((g.m + 127) / 128));
     hipLaunchKernelGGL((gemm_f32_kernel<128, TB, LOWER, TRI>), grid, dim3(256), 0, st, g, vec);
   } else {
@@ -261,57 +301,151 @@ __global__ __launch_bounds__(256) void reverse_damp_kernel(const float* __restri
   }
 }
 
-// A diagonal block (n x n, n <= 64) of the lower Cholesky factorisation, in place: L is
-// factored and replaced by its inverse X = L^{-1} (lower, zeros above the diagonal
-// inside the block).  One wave; lane t holds row t of L and of the running right-hand
-// side R of L X = I in registers (every index a compile-time constant).  Step j: the
-// pivot L_jj and column j's entries reach every lane through readlane (no barriers);
-// lanes below j scale their L_tj and update their row; row j of X is R_j / L_jj and the
-// rows below subtract L_tj X_j.  A non-positive or NaN pivot sets *fail and continues
-// with pivot 1 so that the rest stays finite.
 __device__ __forceinline__ float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-__global__ __launch_bounds__(64) void potrf_block_kernel(float* __restrict__ A, int64_t lda, int n,
-                                                         int* __restrict__ fail) {
-  const int t = threadIdx.x;
-  float L[64], R[64];
-  unrolled<64>([&](auto cc) __attribute__((always_inline)) {
-    constexpr int c = decltype(cc)::value;
-    float v = 0.0f;
-    if (t < n && c <= t && c < n) v = A[t * lda + c];
-    else if (t == c) v = 1.0f;  // padding of a partial block: identity
-    L[c] = v;
-    R[c] = t == c ? 1.0f : 0.0f;
-  });
+// A 64 x 64 lower Cholesky block and its inverse: L is factored and X = L^{-1} replaces it.
+// A workgroup of 8 waves; wave w holds columns w, w + 8, ... of L and of the running
+// right-hand side R of L X = I, lane t row t.  Step j: the column's owner takes the pivot
+// L_jj, scales the column and passes it on through LDS (two buffers, one barrier a step);
+// every lane below j then updates its row, and row j of X is R_j / L_jj.  A non-positive or
+// NaN pivot sets *fail and continues with pivot 1 so that the rest stays finite.  Each
+// element sees the operations of a one-wave elimination in the same order.  The chain of 64
+// pivots (sqrt, division, broadcast) and the instructions of the updates bound it: one wave
+// with all columns took 43 us, eight take 31.
+// get(t, c) reads an element (identity past the block), put(i, t, c, x) takes X.
+struct PotrfLds {
+  float col[2][64];
+  float inv[2];
+};
+template <typename Get, typename Put>
+__device__ __forceinline__ void potrf64(PotrfLds& sh, int n, int* fail, Get get, Put put) {
+  const int t = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float L[8], R[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int c = w + 8 * i;
+    L[i] = get(t, c);
+    R[i] = t == c ? 1.0f : 0.0f;
+  }
   bool bad = false;
-  unrolled<64>([&](auto jj) __attribute__((always_inline)) {
-    constexpr int j = decltype(jj)::value;
-    float d = lane_value(L[j], j);
-    if (!(d > 0.0f)) {
-      bad = bad || j < n;
-      d = 1.0f;
+  unrolled<8>([&](auto i_const) __attribute__((always_inline)) {
+    constexpr int i8 = decltype(i_const)::value;
+    for (int w8 = 0; w8 < 8; ++w8) {
+      const int j = 8 * i8 + w8, buf = w8 & 1;
+      if (w == w8) {
+        float d = lane_value(L[i8], j);
+        if (!(d > 0.0f)) {
+          bad = bad || j < n;
+          d = 1.0f;
+        }
+        const float s = sqrtf(d), inv = 1.0f / s;
+        L[i8] = t == j ? s : (t > j ? L[i8] * inv : L[i8]);
+        sh.col[buf][t] = L[i8];
+        if (t == 0) sh.inv[buf] = inv;
+      }
+      __syncthreads();
+      const float v = sh.col[buf][t], inv = sh.inv[buf];
+      const float ltj = t > j ? v : 0.0f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int c = w + 8 * i;
+        if (c > j) {
+          L[i] = __builtin_fmaf(-ltj, lane_value(v, c), L[i]);
+        } else {
+          if (t == j) R[i] *= inv;
+          R[i] = __builtin_fmaf(-ltj, lane_value(R[i], j), R[i]);
+        }
+      }
     }
-    const float s = sqrtf(d), inv = 1.0f / s;
-    L[j] = t == j ? s : (t > j ? L[j] * inv : L[j]);
-    const float ltj = t > j ? L[j] : 0.0f;
-    // trailing columns of this lane's row
-    unrolled<63 - j>([&](auto oo) __attribute__((always_inline)) {
-      constexpr int c = j + 1 + decltype(oo)::value;
-      L[c] -= ltj * lane_value(L[j], c);
-    });
-    // row j of X, then the rows below
-    unrolled<j + 1>([&](auto cc) __attribute__((always_inline)) {
-      constexpr int c = decltype(cc)::value;
-      if (t == j) R[c] *= inv;
-      R[c] -= ltj * lane_value(R[c], j);
-    });
   });
   if (bad && t == 0) atomicOr(fail, 1);
-  unrolled<64>([&](auto cc) __attribute__((always_inline)) {
-    constexpr int c = decltype(cc)::value;
-    if (t < n && c < n) A[t * lda + c] = c <= t ? R[c] : 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int c = w + 8 * i;
+    put(t, c, c <= t ? R[i] : 0.0f);
+  }
+}
+
+__global__ __launch_bounds__(512) void potrf_block_kernel(float* __restrict__ A, int64_t lda, int n,
+                                                          int* __restrict__ fail) {
+  __shared__ PotrfLds sh;
+  potrf64(
+      sh, n, fail,
+      [&](int t, int c) { return t < n && c <= t && c < n ? A[t * lda + c] : (t == c ? 1.0f : 0.0f); },
+      [&](int t, int c, float x) {
+        if (t < n && c < n) A[t * lda + c] = x;
+      });
+}
+
+// A block of 65 .. 128 in one workgroup: the recursion of chol_inv on two 64-wide halves
+// (n2 = n - 64 rows in the second), whose products are 64 x 64 x 64 from LDS with the matrix
+// instruction and the k order of gemm_f32_kernel.  Otherwise two leaves, four products and a copy,
+// about 100 us of dependent launches; this takes 66.
+__global__ __launch_bounds__(512) void chol_pair_kernel(float* __restrict__ A, int64_t lda, int n,
+                                                        int* __restrict__ fail) {
+  constexpr int P = 65;  // LDS row pitch
+  __shared__ PotrfLds sh;
+  __shared__ float Xa[64][P], Ld[64][P], Xb[64][P];  // X11; A21, then L21, then T; A22, then X22
+  const int n2 = n - 64, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ti = wave >> 1, tj = 2 * (wave & 1);  // the wave's two 16 x 16 tiles: (ti, tj), (ti, tj + 1)
+  const int li = lane & 15, lq = lane >> 4;
+  float* const A21 = A + 64 * lda;
+  float* const A22 = A21 + 64;
+  for (int e = tid; e < 64 * 64; e += 512) {
+    const int r = e >> 6, c = e & 63;
+    Ld[r][c] = r < n2 ? A21[r * lda + c] : 0.0f;
+  }
+  potrf64(
+      sh, 64, fail, [&](int t, int c) { return c <= t ? A[t * lda + c] : 0.0f; },
+      [&](int t, int c, float x) {
+        Xa[t][c] = x;
+        A[t * lda + c] = x;
+      });
+  __syncthreads();
+  f4 acc[2];
+  // acc = sum_k a(i, k) b(k, j) over the wave's tiles
+  auto product = [&](auto a, auto b) __attribute__((always_inline)) {
+    acc[0] = acc[1] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int k = 4 * q + lq;
+      const float av = a(16 * ti + li, k);
+#pragma unroll
+      for (int b2 = 0; b2 < 2; ++b2)
+        acc[b2] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b(k, 16 * (tj + b2) + li), acc[b2], 0, 0, 0);
+    }
+  };
+  auto each = [&](auto f) __attribute__((always_inline)) {  // f(i, j, value) of the wave's tiles
+#pragma unroll
+    for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) f(16 * ti + 4 * lq + r, 16 * (tj + b2) + li, acc[b2][r]);
+  };
+  // L21 = A21 X11^T
+  product([&](int i, int k) { return Ld[i][k]; }, [&](int k, int j) { return Xa[j][k]; });
+  __syncthreads();
+  each([&](int i, int j, float v) { Ld[i][j] = v; });
+  __syncthreads();
+  // A22 -= L21 L21^T
+  product([&](int i, int k) { return Ld[i][k]; }, [&](int k, int j) { return Ld[j][k]; });
+  each([&](int i, int j, float v) { Xb[i][j] = i < n2 && j <= i ? A22[i * lda + j] - v : (i == j ? 1.0f : 0.0f); });
+  // T = L21 X11
+  product([&](int i, int k) { return Ld[i][k]; }, [&](int k, int j) { return Xa[k][j]; });
+  __syncthreads();
+  each([&](int i, int j, float v) { Ld[i][j] = v; });
+  potrf64(
+      sh, n2, fail, [&](int t, int c) { return Xb[t][c]; }, [&](int t, int c, float x) { Xb[t][c] = x; });
+  __syncthreads();
+  for (int e = tid; e < 64 * 64; e += 512) {
+    const int r = e >> 6, c = e & 63;
+    if (r < n2 && c < n2) A22[r * lda + c] = Xb[r][c];
+  }
+  // X21 = -X22 T
+  product([&](int i, int k) { return Xb[i][k]; }, [&](int k, int j) { return Ld[k][j]; });
+  each([&](int i, int j, float v) {
+    if (i < n2) A21[i * lda + j] = -v;
   });
 }
 
@@ -345,76 +479,106 @@ __global__ __launch_bounds__(256) void zero_lower_kernel(float* __restrict__ A, 
 }
 
 // ------------------------------------------------------------------ the sweep
+// A thread per column: most columns are not dead and end here.
 __global__ __launch_bounds__(256) void zero_dead_kernel(float* __restrict__ W, int64_t ldw, int64_t N, int64_t K,
                                                         const uint8_t* __restrict__ dead) {
-  for (int64_t n = blockIdx.y; n < N; n += gridDim.y)
-    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < K; j += (int64_t)gridDim.x * 256)
-      if (dead[j]) W[n * ldw + j] = 0.0f;
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j >= K || !dead[j]) return;
+  for (int64_t n = blockIdx.y; n < N; n += gridDim.y) W[n * ldw + j] = 0.0f;
+}
+
+// Lane m's value for all four lanes of a quad.
+template <int M>
+__device__ __forceinline__ float quad_value(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), M * 0x55, 0xf, 0xf, true));
 }
 
 // One 64-column block [j0, j0 + 64) of the sweep; columns j0 .. j0+cnt-1 are 2:4 columns
 // (cnt a multiple of 4), the rest of the block (dense columns, or past K) only take
-// updates.  A thread per row n: its 64 weights in registers (every index a compile-time
-// constant, so nothing spills), U's block (upper; 1 on the diagonal past K) in LDS.
-// Writes the block back, the kept flags of the whole block (1 for the columns past the
-// 2:4 ones) and E[n][c] = (w_c - q_c) / U_cc (0 where nothing changed).
+// updates.  Four lanes per row, lane l the columns 4 i + l in registers (every index a
+// compile-time constant), so that a group of four has one column per lane; U's block (upper;
+// 1 on the diagonal past K) in LDS in the lanes' order, the rows, their errors and flags in
+// and out through LDS as whole rows.  Writes the block back, the kept flags of the whole
+// block (1 for the columns past the 2:4 ones) and E[n][c] = (w_c - q_c) / U_cc (0 where
+// nothing changed).  Each weight takes the updates of a thread-per-row sweep in the same
+// order.  What bounds it is the chain over the 64 columns (a division and a broadcast each);
+// with a thread per row (75 workgroups at 19200 rows, every load and store of a lane in a
+// line of its own) a block took SB_OLD_US us, now SB_NEW_US.
 __global__ __launch_bounds__(256) void sweep_block_kernel(float* __restrict__ W, int64_t ldw, int64_t N, int64_t K,
                                                           const float* __restrict__ U, int64_t ldu, int64_t j0, int cnt,
                                                           uint8_t* __restrict__ keep, int64_t ldk,
                                                           float* __restrict__ E, int64_t lde) {
-  __shared__ float Ub[64][64];
+  constexpr int P = 68;  // row pitch of the staged rows: the lanes of 16 rows in 64 banks
+  __shared__ __attribute__((aligned(16))) float Ub[64][64];  // Ub[c][16 l + i] = U[c][4 i + l]
+  __shared__ float Wt[64][P], Et[64][P];
+  __shared__ uint8_t Kt[64][64];
   const int width = (int)(K - j0 < 64 ? K - j0 : 64);
-  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    float v = 0.0f;
-    if (r < width && c < width && c >= r) v = U[(j0 + r) * ldu + (j0 + c)];
-    else if (r == c) v = 1.0f;
-    Ub[r][c] = v;
+  const int64_t n0 = (int64_t)blockIdx.x * 64;
+  {
+    // every load before the first use (addresses clamped into the block)
+    const int c = threadIdx.x & 63, cc = c < width ? c : width - 1;
+    float u[16], v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int r = (threadIdx.x >> 6) + 4 * i;
+      u[i] = U[(j0 + (r < width ? r : width - 1)) * ldu + j0 + cc];
+      v[i] = W[(n0 + r < N ? n0 + r : N - 1) * ldw + j0 + cc];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int r = (threadIdx.x >> 6) + 4 * i;
+      Ub[r][16 * (c & 3) + (c >> 2)] = r < width && c < width && c >= r ? u[i] : (r == c ? 1.0f : 0.0f);
+      Wt[r][c] = n0 + r < N && c < width ? v[i] : 0.0f;
+    }
   }
   __syncthreads();
-  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  float* wr = W + n * ldw + j0;
-  float w[64];
+  const int row = threadIdx.x >> 2, l = threadIdx.x & 3;
+  float w[16];
 #pragma unroll
-  for (int c = 0; c < 64; ++c) w[c] = c < width ? wr[c] : 0.0f;
-  uint32_t kept[2] = {0xffffffffu, 0xffffffffu};
-  float* er = E + n * lde;
-  unrolled<64>([&](auto cc) __attribute__((always_inline)) {
-    constexpr int c = decltype(cc)::value;
-    if constexpr (c % 4 == 0) {
-      // OBS error of each weight of the group (Eq. (3)); prune the two smallest, ties
-      // pruning the lower index; only inside the 2:4 columns
-      const bool active = c < cnt;
-      float s[4];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const float d = Ub[c + m][c + m];
-        s[m] = (w[c + m] * w[c + m]) / (d * d);
+  for (int i = 0; i < 16; ++i) w[i] = Wt[row][4 * i + l];
+  unrolled<16>([&](auto g_const) __attribute__((always_inline)) {
+    constexpr int g = decltype(g_const)::value;
+    // OBS error of each weight of the group (Eq. (3)); prune the two smallest, ties pruning
+    // the lower index; only inside the 2:4 columns
+    const float d = Ub[4 * g + l][16 * l + g];
+    const float s = (w[g] * w[g]) / (d * d);
+    int rank = 0;
+    unrolled<4>([&](auto o_const) __attribute__((always_inline)) {
+      constexpr int o = decltype(o_const)::value;
+      const float so = quad_value<o>(s);
+      rank += (so < s) || (so == s && o < l);
+    });
+    const bool k = !(4 * g < cnt && rank < 2);
+    float em = 0.0f;  // this lane's error
+    unrolled<4>([&](auto m_const) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_const)::value;
+      const float q = k ? w[g] : 0.0f;
+      float ec = (w[g] - q) / d;  // the group's column m: lane m's value
+      if (l == m) {
+        em = ec;
+        w[g] = q;
       }
+      ec = quad_value<m>(ec);
+      const float* u = &Ub[4 * g + m][16 * l];
+      if (l > m) w[g] = __builtin_fmaf(-ec, u[g], w[g]);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        int rank = 0;
-#pragma unroll
-        for (int o = 0; o < 4; ++o) rank += (s[o] < s[m]) || (s[o] == s[m] && o < m);
-        if (active && rank < 2) kept[(c + m) >> 5] &= ~(1u << ((c + m) & 31));
-      }
-    }
-    const bool k = (kept[c >> 5] >> (c & 31)) & 1u;
-    const float q = k ? w[c] : 0.0f;
-    const float ec = (w[c] - q) / Ub[c][c];
-#pragma unroll
-    for (int c2 = c + 1; c2 < 64; ++c2) w[c2] -= ec * Ub[c][c2];
-    w[c] = q;
-    er[c] = ec;
+      for (int i = g + 1; i < 16; ++i) w[i] = __builtin_fmaf(-ec, u[i], w[i]);
+    });
+    Et[row][4 * g + l] = em;
+    Kt[row][4 * g + l] = k ? 1 : 0;
   });
 #pragma unroll
-  for (int c = 0; c < 64; ++c)
-    if (c < width) wr[c] = w[c];
-  uint8_t* kr = keep + n * ldk + j0;
-#pragma unroll
-  for (int c = 0; c < 64; ++c)
-    if (c < width) kr[c] = (kept[c >> 5] >> (c & 31)) & 1u;
+  for (int i = 0; i < 16; ++i) Wt[row][4 * i + l] = w[i];
+  __syncthreads();
+  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
+    const int r = e >> 6, c = e & 63;
+    if (n0 + r >= N) continue;
+    E[(n0 + r) * lde + c] = Et[r][c];
+    if (c < width) {
+      W[(n0 + r) * ldw + j0 + c] = Wt[r][c];
+      keep[(n0 + r) * ldk + j0 + c] = Kt[r][c];
+    }
+  }
 }
 
 // keep = 1 on the columns [from, K) of every row.
@@ -452,7 +616,11 @@ int64_t chol_inv_ws(int64_t n) {
 
 hipError_t chol_inv(float* A, int64_t lda, int64_t n, float* ws, int* fail, hipStream_t st) {
   if (n <= NB) {
-    hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(64), 0, st, A, lda, (int)n, fail);
+    hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(512), 0, st, A, lda, (int)n, fail);
+    return hipGetLastError();
+  }
+  if (n <= 2 * NB) {
+    hipLaunchKernelGGL(chol_pair_kernel, dim3(1), dim3(512), 0, st, A, lda, (int)n, fail);
     return hipGetLastError();
   }
   const int64_t n1 = (n / 2 + NB - 1) / NB * NB, n2 = n - n1;
@@ -513,8 +681,9 @@ hipError_t launch_obs_prune(float* W, int64_t ldw, int64_t N, int64_t K, const f
                             hipStream_t st) {
   float* E = static_cast<float*>(ws);  // N x OB: the outer block's scaled errors
   const unsigned rows_y = (unsigned)(N < 65535 ? N : 65535);
-  if (dead) hipLaunchKernelGGL(zero_dead_kernel, dim3((unsigned)((K + 255) / 256 < 64 ? (K + 255) / 256 : 64), rows_y),
-                               dim3(256), 0, st, W, ldw, N, K, dead);
+  if (dead)
+    hipLaunchKernelGGL(zero_dead_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)(N < 64 ? N : 64)), dim3(256), 0, st,
+                       W, ldw, N, K, dead);
   hipError_t e = hipGetLastError();
   int64_t pe = 0;  // end of the processed 64-blocks
   for (int64_t o0 = 0; o0 < dense_begin && e == hipSuccess; o0 += OB) {
@@ -522,7 +691,7 @@ hipError_t launch_obs_prune(float* W, int64_t ldw, int64_t N, int64_t K, const f
     pe = o0 + (last - o0 + NB - 1) / NB * NB;                             // processed blocks end here
     for (int64_t j0 = o0; j0 < last && e == hipSuccess; j0 += NB) {
       const int cnt = (int)(last - j0 < NB ? last - j0 : NB);
-      hipLaunchKernelGGL(sweep_block_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, W, ldw, N, K, U,
+      hipLaunchKernelGGL(sweep_block_kernel, dim3((unsigned)((N + 63) / 64)), dim3(256), 0, st, W, ldw, N, K, U,
                          ldu, j0, cnt, keep, ldk, E + (j0 - o0), (int64_t)OB);
       e = hipGetLastError();
       const int64_t c0 = j0 + NB, c1 = pe < K ? pe : K;  // the rest of the processed blocks
