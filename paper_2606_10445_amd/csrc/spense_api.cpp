@@ -621,6 +621,32 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
       }
     }
   }
+  // bf16 above 64 tokens: the same kernel on row-major weights (64 columns a step) against the
+  // row-split kernel, which streams the weight once per 64 tokens.  Models of both, fitted
+  // low for the one and high for the other (us): the row-split kernel 0.34e-3 (0.42e-3 to 256
+  // tokens) per 64-token block, 16-row tile and 64 columns; this one 8 + 0.55 per step and
+  // round, in slices 3 + 0.65 per MB of partial sums more.  Measured, before -> this kernel:
+  // 8192 x 5120 at M = 256 / 512 / 1024 / 2048 70 / 115 / 217 / 470 -> 42 / 51 / 95 / 190,
+  // 25600 x 5120 at M = 65 / 128 / 256 / 1024 107 / 113 / 209 / 739 -> 56 / 62 / 105 / 342,
+  // 5120 x 8192 at M = 256 (2 slices) / 517 / 2048 56 / 124 / 408 -> 45 / 62 / 202, 5120 x
+  // 25600 at M = 256 (3 slices) 180 -> 108, 1024 x 5120 at M = 2048 (2 slices) 76 -> 35; the
+  // row-split kernel stays at 1024 x 5120 up to M = 512 (13 at M = 128 against 19).
+  if (ov.kernel == 0 && !ov.rt && !ov.waves && !ov.ct && ov.ksplit <= 1 && !ov.wused && !ov.wused_d && !ov.wused_s &&
+      !ov.u8 && !ov.xres && ov.order < 0 && dtype == SPENSE_BF16 && M > 64) {
+    const int64_t rb = split == SPENSE_SPLIT_OUTPUT ? ceil_div(dense_begin, 128) + ceil_div(N - dense_begin, 128)
+                                                    : ceil_div(N, 128);
+    const int64_t wgs = rb * ceil_div(M, 128), steps = ceil_div(K, 64);
+    double best = 0.9 * (M <= 256 ? 0.42e-3 : 0.34e-3) * (double)ceil_div(M, 64) * (double)ceil_div(N, 16) * (double)steps;
+    for (int64_t S = 1; S <= (ov.ksplit < 1 ? 8 : 1) && 4 * S <= std::max<int64_t>(steps, 4); ++S) {
+      const double bytes = S > 1 ? 4.0 * (double)S * (double)M * (double)N : 0;
+      if (bytes > (double)SPENSE_NOALLOC_SCRATCH_BYTES) break;
+      const double t = 8 + 0.55 * (double)ceil_div(wgs * S, kCUs) * (double)ceil_div(steps, S) + (S > 1 ? 3 + 0.65e-6 * bytes : 0);
+      if (t < best) {
+        best = t;
+        mid_ks = (int)S;
+      }
+    }
+  }
   const bool mid = mid_ks > 0;
   if (mid) {
     // the two-half kernel's place (128 tokens a block there too), or the large-M kernels'
@@ -705,10 +731,11 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   }
   if (mid) {
     int64_t chunks = 0;
-    for (int i = 0; i < nreg; ++i) chunks = std::max(chunks, ceil_div(regs[i].kbound, 512) + ceil_div(K - regs[i].kbound, 512));
+    const int64_t kc = 512 / es;  // four steps
+    for (int i = 0; i < nreg; ++i) chunks = std::max(chunks, ceil_div(regs[i].kbound, kc) + ceil_div(K - regs[i].kbound, kc));
     ksplit = (int)std::max<int64_t>(1, std::min<int64_t>(mid_ks, chunks));
     for (int i = 0; i < nreg; ++i) {
-      slice_cuts(regs[i], ksplit, 512, es, sparse_cost);
+      slice_cuts(regs[i], ksplit, kc, es, sparse_cost);
       regs[i].nrb *= ksplit;
     }
   }

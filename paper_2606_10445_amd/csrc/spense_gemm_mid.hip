@@ -4,9 +4,10 @@
 namespace spense {
 namespace {
 
-// Between decode and the 256 x 256 grid: a workgroup computes 128 weight rows x 128 tokens,
-// optionally over a slice of K (fp32 partial sums, added by splitk_reduce_kernel).  Tiled
-// weight layout only, one or several weights (MatDesc).
+// Between decode and the 256 x 256 grid, and for bf16 every many-token shape: a workgroup
+// computes 128 weight rows x 128 tokens, optionally over a slice of K (fp32 partial sums,
+// added by splitk_reduce_kernel).  fp8 weights in the tiled layout (one or several, MatDesc),
+// bf16 weights row-major.
 //
 // Eight waves compute, the rows split over four of them and the tokens in two 64-token halves
 // (32 rows x 64 tokens each), and four (one per SIMD) only copy.  A wave that issues a copy into LDS is held there until
@@ -15,7 +16,10 @@ namespace {
 // each other (measured: 32 KB copied in 606 clocks and 64 KB read in 690 at once, 585 and 687
 // alone).  With every wave copying its share, a 128-column step took 1370 clocks.
 //
-// Steps of 128 columns go through a ring of NS stages in LDS that 2:4 and dense steps share
+// A step is 128 bytes of every token: 128 columns in fp8, 64 in bf16, whose operand layouts
+// are the same in bytes (16 bytes of kept values per lane of a 16-row tile; activations and
+// dense weights bytes [16 q, 16 q + 16) and [64 + 16 q, 64 + 16 q + 16) for lane group q).
+// Steps go through a ring of NS stages in LDS that 2:4 and dense steps share
 // (a stage: the activations, and 16 KB for the row tiles' values and metadata or dense
 // halves), so an input-split weight runs across its boundary without draining the ring.
 // Per step one barrier; after it every computing wave holds the step's fragments in
@@ -32,7 +36,11 @@ namespace {
 constexpr int kMidRows = 128, kMidTok = 128, kMidX = kMidTok * 128, kMidStage = kMidX + 16384;
 constexpr int kMidStages = 5, kMidLds = kMidStages * kMidStage;
 
+template <int DT>
 __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
+  constexpr bool TL = DT == kFP8;  // tiled weights; bf16 reads the row-major layout
+  constexpr int ES = Traits<DT>::ES;
+  typedef std::integral_constant<int, DT> Dt;
   constexpr int RPW = 2, TC = 4;  // row tiles and token tiles of a wave
   constexpr int NS = kMidStages, XB = kMidX, SB = kMidStage;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -54,7 +62,7 @@ __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
   const int rb = rs / S, slice = rs - rb * S;
   const int m0 = (g - R.wg0) % a.tblocks * kMidTok;
   const int rowend = R.row0 + R.rows, rblk = R.row0 + rb * kMidRows;
-  const int K = R.kend, kbound = R.kbound;
+  const int K = R.kend * ES, kbound = R.kbound * ES;  // bytes of an activation row
   const int n_sp = (kbound + 127) / 128, n_de = (K - kbound + 127) / 128;
   const int nch_sp = (n_sp + 3) / 4, nch_de = (n_de + 3) / 4;
   // this slice's steps: 2:4 steps [s0, s0 + ns), then dense steps [d0, d0 + nd)
@@ -79,23 +87,44 @@ __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
   auto run_copies = [&]() __attribute__((always_inline)) {
     constexpr int XL = 4;
     const int xb = 16 * ((lane & 7) ^ (lane >> 4));  // column of this lane's 16 bytes in a step; odd blocks xb ^ 64
-    uint32_t xo[XL], vo[2], dof[2], mo = kOOB;  // loop-invariant per-lane offsets, kOOB past M or the region
+    uint32_t xo[XL], vo[2], dof[4], mo = kOOB;  // loop-invariant per-lane offsets, kOOB past M or the region
+    int vc = 0;  // row-major values: the byte of this lane's piece inside the step
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
       const int m = m0 + 8 * (XL * cw + i) + (lane >> 3);
       xo[i] = m < a.M ? (uint32_t)((int64_t)m * a.ldx_b + (xb ^ (64 * (i & 1)))) : kOOB;
     }
+    if constexpr (TL) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int r0 = rblk + 16 * (2 * cw + u);
-      vo[u] = r0 < rowend ? (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 4096u + 16u * lane : kOOB;
-      dof[u] = r0 < rowend && r0 >= R.dense_row_off
-                   ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
-                   : kOOB;
-    }
-    {
+      for (int u = 0; u < 2; ++u) {
+        const int r0 = rblk + 16 * (2 * cw + u);
+        vo[u] = r0 < rowend ? (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 4096u + 16u * lane : kOOB;
+        dof[2 * u] = r0 < rowend && r0 >= R.dense_row_off
+                         ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
+                         : kOOB;
+        dof[2 * u + 1] = dof[2 * u];
+      }
       const int r0 = rblk + 16 * (4 * cw + (lane >> 4));
       if (cw < 2 && r0 < rowend) mo = (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 1024u + 16u * li;
+    } else {
+      // values: lane l the 16-byte piece (l % 4) ^ (row / 4 % 4) of row l / 4 of the tile, so
+      // that the four lane groups' reads of 16 rows meet in no bank; dense rows like the
+      // activations, eight per block; metadata: lane l word l % 2 of row l / 2 of 32
+      vc = 16 * ((lane & 3) ^ ((lane >> 4) & 3));
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int r = rblk + 16 * (2 * cw + u) + (lane >> 2);
+        vo[u] = r < rowend ? (uint32_t)(r * a.v_ld_b + vc) : kOOB;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = rblk + 32 * cw + 8 * u + (lane >> 3);
+        dof[u] = r < rowend && r >= R.dense_row_off
+                     ? (uint32_t)((r - R.dense_row_off) * a.d_ld_b + (kbound - R.dense_col_off * ES) + (xb ^ (64 * (u & 1))))
+                     : kOOB;
+      }
+      const int r = rblk + 32 * cw + (lane >> 1);
+      if (r < rowend) mo = (uint32_t)(r * a.m_ld_b + 4 * (lane & 1));
     }
     auto copy = [&](int s, int k) __attribute__((always_inline)) {  // ring step s into stage k
       if (s >= n) return;
@@ -110,28 +139,40 @@ __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
         if (part) off = ks + (xb ^ (64 * (i & 1))) < ke ? off : kOOB;
         lds_load16<0>(rx, st + (XL * cw + i) * 1024, off, ks);
       });
-      if (sp) {
-        lds_load16<kTiledNT>(rv, st + XB + (2 * cw) * 1024, vo[0], 1024 * ss);
-        lds_load16<kTiledNT>(rv, st + XB + (2 * cw + 1) * 1024, vo[1], 1024 * ss);
-        if (cw < 2) lds_load16<kTiledNT>(rm, st + XB + 8192 + cw * 1024, mo, 256 * ss);
-      } else {
+      if constexpr (TL) {
+        if (sp) {
+          lds_load16<kTiledNT>(rv, st + XB + (2 * cw) * 1024, vo[0], 1024 * ss);
+          lds_load16<kTiledNT>(rv, st + XB + (2 * cw + 1) * 1024, vo[1], 1024 * ss);
+          if (cw < 2) lds_load16<kTiledNT>(rm, st + XB + 8192 + cw * 1024, mo, 256 * ss);
+        } else {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          lds_load16<kTiledNT>(rd, st + XB + (2 * cw + u) * 2048, dof[u], 2048 * ss);
-          lds_load16<kTiledNT>(rd, st + XB + (2 * cw + u) * 2048 + 1024, dof[u], 2048 * ss + 1024);
+          for (int u = 0; u < 4; ++u)
+            lds_load16<kTiledNT>(rd, st + XB + (4 * cw + u) * 1024, dof[u], 2048 * ss + 1024 * (u & 1));
         }
+      } else if (sp) {  // rows are not padded: a partial step's weights past the region read as zeros too
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          lds_load16<kNT>(rv, st + XB + (2 * cw + u) * 1024, part && ks + 2 * vc >= ke ? kOOB : vo[u], 64 * ss);
+        lds_load4<kNT>(rm, st + XB + 8192 + cw * 256, part && ks + 64 * (lane & 1) >= ke ? kOOB : mo, 8 * ss);
+      } else {
+        static_for<4>([&](auto u_const) {
+          constexpr int u = decltype(u_const)::value;
+          uint32_t off = dof[u];
+          if (part) off = ks + (xb ^ (64 * (u & 1))) < ke ? off : kOOB;
+          lds_load16<kNT>(rd, st + XB + (4 * cw + u) * 1024, off, 128 * ss);
+        });
       }
     };
     // Wait until the copies of all but the last k steps in flight have landed.  A 2:4 step is
-    // XL + 2 loads (XL + 3 on waves 0 and 1), a dense one XL + 4; where both are in flight
-    // the smaller count waits longer than needed.
+    // XL + 3 loads (tiled: XL + 2 on waves 2 and 3), a dense one XL + 4; where both are in
+    // flight the smaller count waits longer than needed.
     auto wait_steps = [&](bool sp, int k) __attribute__((always_inline)) {
       static_for<NS>([&](auto i_const) {
         constexpr int i = NS - 1 - decltype(i_const)::value;
         if (k == i) {
           if (!sp)
             wait_vm<i * (XL + 4)>();
-          else if (cw < 2)
+          else if (!TL || cw < 2)
             wait_vm<i * (XL + 3)>();
           else
             wait_vm<i * (XL + 2)>();
@@ -173,9 +214,15 @@ __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
       auto read_a = [&](auto p_const, auto t_const, const uint8_t* st) __attribute__((always_inline)) {
         constexpr int p = decltype(p_const)::value, t = decltype(t_const)::value;
         const uint8_t* ws = st + XB;
-        if constexpr (SP) {
+        if constexpr (SP && TL) {
           alo[p][t] = *reinterpret_cast<const v4i*>(ws + (RPW * wr + t) * 1024 + 16 * lane);
           aix[p][t] = *reinterpret_cast<const int*>(ws + 8192 + (RPW * wr + t) * 256 + 16 * li + 4 * lq);
+        } else if constexpr (SP) {
+          alo[p][t] = *reinterpret_cast<const v4i*>(ws + (RPW * wr + t) * 1024 + 64 * li + 16 * (lq ^ (li >> 2)));
+          aix[p][t] = *reinterpret_cast<const int*>(ws + 8192 + (RPW * wr + t) * 128 + 8 * li + 4 * (lq >> 1));
+        } else if constexpr (!TL) {
+          alo[p][t] = *reinterpret_cast<const v4i*>(ws + (RPW * wr + t) * 2048 + 128 * li + xc0);
+          ahi[p][t] = *reinterpret_cast<const v4i*>(ws + (RPW * wr + t) * 2048 + 128 * li + xc1);
         } else {
           alo[p][t] = *reinterpret_cast<const v4i*>(ws + (RPW * wr + t) * 2048 + 16 * lane);
           ahi[p][t] = *reinterpret_cast<const v4i*>(ws + (RPW * wr + t) * 2048 + 1024 + 16 * lane);
@@ -203,10 +250,15 @@ __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
             read_b(Q(), std::integral_constant<int, 2 * t + 1>(), sn);
 #pragma unroll
             for (int c = 0; c < TC; ++c) {
-              if constexpr (SP)
-                acc[t][c] = mma_sparse(alo[P][t], bq[P][c], acc[t][c], aix[P][t], std::integral_constant<int, kFP8>());
-              else
-                acc[t][c] = mma_dense(cat8(alo[P][t], ahi[P][t]), bq[P][c], acc[t][c], std::integral_constant<int, kFP8>());
+              if constexpr (SP) {
+                acc[t][c] = mma_sparse(alo[P][t], bq[P][c], acc[t][c], TL ? aix[P][t] : (int)((uint32_t)aix[P][t] >> (16 * (lq & 1))), Dt());
+              } else if constexpr (TL) {
+                acc[t][c] = mma_dense(cat8(alo[P][t], ahi[P][t]), bq[P][c], acc[t][c], Dt());
+              } else {
+                acc[t][c] = mma_dense(cat8(alo[P][t], alo[P][t]), bq[P][c], acc[t][c], Dt());
+                acc[t][c] = mma_dense(cat8(ahi[P][t], ahi[P][t]), __builtin_shufflevector(bq[P][c], bq[P][c], 4, 5, 6, 7, 4, 5, 6, 7),
+                                      acc[t][c], Dt());
+              }
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -273,14 +325,16 @@ __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
 
 }  // namespace
 
-hipError_t launch_mid(const GemmArgs& a, hipStream_t s) {
+hipError_t launch_mid(int dtype, const GemmArgs& a, hipStream_t s) {
   static_assert(kMidLds <= 160 * 1024, "LDS of a CU");
-  if (!a.tiled) return hipErrorInvalidValue;  // the planner sends row-major weights to the 128 x 256 kernel
+  // fp8 row-major weights go to the 128 x 256 kernel, bf16 ones have no tiled layout
+  if ((dtype == kFP8) != (a.tiled != 0)) return hipErrorInvalidValue;
   for (int i = 0; i < a.nreg; ++i)
     if (a.reg[i].ksplit > 1 && !a.part) return hipErrorInvalidValue;
-  hipError_t e = set_big_lds(spense_gemm_mid_kernel, 1, 0, kMidLds);
+  auto k = dtype == kFP8 ? spense_gemm_mid_kernel<kFP8> : spense_gemm_mid_kernel<kBF16>;
+  hipError_t e = set_big_lds(k, 1, dtype == kFP8 ? 0 : 1, kMidLds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(spense_gemm_mid_kernel, dim3(a.groups), dim3(768), kMidLds, s, a);
+  hipLaunchKernelGGL(k, dim3(a.groups), dim3(768), kMidLds, s, a);
   return hipGetLastError();
 }
 

@@ -113,8 +113,8 @@ struct LaunchShape {
 
 // The 256 x 256 large-M kernel (LaunchShape::big == 2).
 hipError_t launch_big2(const GemmArgs& a, hipStream_t s);
-// The 128 x 128 kernel (LaunchShape::big == 3).
-hipError_t launch_mid(const GemmArgs& a, hipStream_t s);
+// The 128 x 128 kernel (LaunchShape::big == 3): tiled fp8 or row-major bf16 weights.
+hipError_t launch_mid(int dtype, const GemmArgs& a, hipStream_t s);
 
 hipError_t launch_gemm(int dtype, const LaunchShape& ls, const GemmArgs& a, hipStream_t s);
 

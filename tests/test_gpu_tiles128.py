@@ -1,5 +1,5 @@
-"""The 128 x 128 GEMM kernel (tiled fp8 between decode and the 256 x 256 grid) as the
-planner chooses it: bit for bit the row-split kernel's results on exact-integer data (their
+"""The 128 x 128 GEMM kernel (tiled fp8 between decode and the 256 x 256 grid, bf16 above 64
+tokens) as the planner chooses it: bit for bit the row-split kernel's results on exact-integer data (their
 sums are exact in any order), and repeatable on random data."""
 import sys
 
@@ -25,16 +25,21 @@ def S():
 CASES = [(1, 257, 6500, 2080, 1056), (0, 385, 5000, 2048, 3000), (1, 513, 4608, 2048, 2048), (0, 300, 6528, 2048, 0),
          (1, 640, 5120, 2112, 32), (0, 256, 11300, 2048, 8432), (1, 1537, 1100, 2304, 1728),
          (1, 100, 2410, 14368, 10016), (1, 250, 1100, 14336, 14336), (0, 70, 2304, 14336, 1200), (1, 128, 2435, 15000, 96)]
-CASES = [(a, M, N, K // 32 * 32, db) for a, M, N, K, db in CASES]
+CASES = [(a, M, N, K // 32 * 32, db, gen.FP8) for a, M, N, K, db in CASES]
+# bf16, row-major: several rounds, partial steps (boundary and K off multiples of 64), rows off
+# multiples of 16, all-2:4, all-dense, K slices
+CASES += [(1, 513, 5000, 4128, 2080, gen.BF16), (0, 513, 9001, 4096, 6001, gen.BF16), (1, 700, 4608, 4128, 4128, gen.BF16),
+          (0, 300, 8192, 4128, 0, gen.BF16), (1, 200, 2600, 16416, 12320, gen.BF16), (0, 65, 25600, 2080, 19200, gen.BF16)]
 
 
-@pytest.mark.parametrize("axis,M,N,K,db", CASES)
-def test_planned_tiles_exact(S, axis, M, N, K, db, capfd):
-    print(f"[128x128] axis={axis} M={M} N={N} K={K} db={db}", file=sys.stderr, flush=True)
-    W, mask, X, sw, sx = gen.make_exact_int(41, M, M, N, K, gen.OUTPUT if axis == 0 else gen.INPUT, db, gen.FP8)
-    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+@pytest.mark.parametrize("axis,M,N,K,db,dtype", CASES)
+def test_planned_tiles_exact(S, axis, M, N, K, db, dtype, capfd):
+    print(f"[128x128] axis={axis} M={M} N={N} K={K} db={db} {dtype}", file=sys.stderr, flush=True)
+    W, mask, X, sw, sx = gen.make_exact_int(41, M, M, N, K, gen.OUTPUT if axis == 0 else gen.INPUT, db, dtype)
+    dev = lambda a: None if a is None else torch.from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a).cuda()  # noqa: E731
     X, sw, sx = dev(X), dev(sw), dev(sx)
-    pw = S.tile(S.compress(dev(W), dev(mask), axis, db))
+    pw = S.compress(dev(W), dev(mask), axis, db)
+    pw = S.tile(pw) if dtype == gen.FP8 else pw
     ref = S.gemm(X, pw, sw, sx, out_f32=True, plan=S.plan_override(kernel=2, ksplit=1))
     prev = S.spense_set_log(1)
     capfd.readouterr()
@@ -54,7 +59,7 @@ def test_planned_tiles_exact(S, axis, M, N, K, db, capfd):
         assert torch.all(big[:, N:] == 7.0)
 
 
-@pytest.mark.parametrize("axis,M,N,K,db", [CASES[0], CASES[7]])
+@pytest.mark.parametrize("axis,M,N,K,db", [CASES[0][:5], CASES[7][:5]])
 def test_planned_tiles_repeatable(S, axis, M, N, K, db):
     """Random data: the same bits every time, and within the fp32 sums' reordering (K
     slices) of the row-split kernel: both are within 2^-12 of sum |x w| (the fp8
