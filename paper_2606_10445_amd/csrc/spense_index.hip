@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <type_traits>
 
 #include "spense.h"
@@ -59,34 +60,41 @@ __global__ __launch_bounds__(256) void row_scores_kernel(const uint8_t* __restri
 
 // Row scores, streaming form: a wave per row (rows 0..I-1 of Wgate, then of Wup, shared
 // out among the waves of the grid).  Lane l owns the 16-byte pieces l, l + 64, ... of
-// every row (T of them, T <= TMAX) and keeps sqrt(h_in) of their elements in registers,
-// so each wave computes those square roots once; all T loads of a row are issued before
-// the first is used.  Each lane sums its pieces in order, then the wave adds its lanes
-// with a fixed butterfly.
+// every row (T of them, T <= TMAX) and keeps sqrt(h_in) of their elements in registers;
+// the workgroup computes each square root once, in LDS (D <= 8192), so that a wave does
+// not spend as long on its 8 T roots as on several rows.  A row's loads are issued before
+// the previous row is summed.  Each lane sums its pieces in order, then the wave adds its
+// lanes with a fixed butterfly.  HBM-bound: 25600 x 5120 bf16, gate and up, 158 us with
+// the roots per wave and one row at a time, 122 now.
 template <int TYPE, int TMAX>
 __global__ __launch_bounds__(256) void row_scores_wave_kernel(const uint8_t* __restrict__ wg,
                                                               const uint8_t* __restrict__ wu, int64_t ld_b, int64_t D,
                                                               int T, const float* __restrict__ h_in,
                                                               float* __restrict__ out, int64_t I) {
   constexpr int EP = TYPE == SPENSE_BF16 ? 8 : 4;  // elements per 16-byte piece
+  __shared__ float root[TMAX * 64 * EP];
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
   const int64_t nwaves = (int64_t)gridDim.x * 4;
+  for (int j = threadIdx.x; j < TMAX * 64 * EP; j += 256) root[j] = j < D ? sqrtf(h_in[j]) : 0.0f;
+  __syncthreads();
   float sh[TMAX][EP];
 #pragma unroll
-  for (int t = 0; t < TMAX; ++t) {
-    const int64_t j = ((int64_t)t * 64 + lane) * EP;
+  for (int t = 0; t < TMAX; ++t)
 #pragma unroll
-    for (int e = 0; e < EP; ++e) sh[t][e] = (t < T && j < D) ? sqrtf(h_in[j + e]) : 0.0f;
-  }
-  for (int64_t r = wave; r < 2 * I; r += nwaves) {
+    for (int e = 0; e < EP; ++e) sh[t][e] = root[(t * 64 + lane) * EP + e];
+  auto load = [&](int4 (&v)[TMAX], int64_t r) __attribute__((always_inline)) {
     const uint8_t* row = (r < I ? wg + r * ld_b : wu + (r - I) * ld_b);
-    int4 v[TMAX];
 #pragma unroll
     for (int t = 0; t < TMAX; ++t) {
       const int64_t j = ((int64_t)t * 64 + lane) * EP;
       v[t] = (t < T && j < D) ? *reinterpret_cast<const int4*>(row + j * (16 / EP)) : make_int4(0, 0, 0, 0);
     }
+  };
+  int4 v[TMAX], nx[TMAX];
+  if (wave < 2 * I) load(v, wave);
+  for (int64_t r = wave; r < 2 * I; r += nwaves) {
+    if (r + nwaves < 2 * I) load(nx, r + nwaves);
     float acc = 0.0f;
 #pragma unroll
     for (int t = 0; t < TMAX; ++t) {
@@ -104,6 +112,8 @@ __global__ __launch_bounds__(256) void row_scores_wave_kernel(const uint8_t* __r
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if (lane == 0) out[r] = acc / (float)D;
+#pragma unroll
+    for (int t = 0; t < TMAX; ++t) v[t] = nx[t];
   }
 }
 
@@ -128,33 +138,30 @@ __global__ __launch_bounds__(256) void col_scores_kernel(const uint8_t* __restri
   }
 }
 
-// Column scores, streaming form: a workgroup of 16 waves covers 256 columns, lane l the
-// four columns 4l..4l+3 (one 8- or 16-byte load per row); wave w sums rows w, w + 16, ...
-// (UNR rows' loads in flight at a time), then the 16 partial sums of each column are
-// added in wave order.  Needs I % 4 == 0 and 4-element-aligned rows.
+// Column scores, streaming form: a workgroup of 16 waves covers 128 columns, lane l the
+// columns 2l, 2l + 1 (one 4- or 8-byte load per row); wave w sums rows w, w + 16, ... (UNR
+// rows' loads in flight at a time), then the 16 partial sums of each column are added in
+// wave order.  Needs I % 4 == 0 and 4-element-aligned rows.  256 columns a workgroup
+// left 100 workgroups at I = 25600 (69 us for 5120 rows of bf16; 200 workgroups 48).
 template <int TYPE>
 __global__ __launch_bounds__(1024) void col_scores_wide_kernel(const uint8_t* __restrict__ wd, int64_t ld_b,
                                                                int64_t D, int64_t I, const float* __restrict__ h_mid,
                                                                float* __restrict__ out) {
-  constexpr int UNR = 8;
-  typedef typename std::conditional<TYPE == SPENSE_BF16, uint2, uint4>::type V;
-  __shared__ float part[16][256];
+  constexpr int UNR = 16;
+  typedef typename std::conditional<TYPE == SPENSE_BF16, uint32_t, uint2>::type V;
+  __shared__ float part[16][128];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t c0 = (int64_t)blockIdx.x * 256 + lane * 4;
+  const int64_t c0 = (int64_t)blockIdx.x * 128 + lane * 2;
   const bool live = c0 < I;
   const uint8_t* base = wd + c0 * (TYPE == SPENSE_BF16 ? 2 : 4);
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  float acc[2] = {0.0f, 0.0f};
   auto add = [&](const V& v) __attribute__((always_inline)) {
     if constexpr (TYPE == SPENSE_BF16) {
-      acc[0] += fabsf(__uint_as_float(v.x << 16));
-      acc[1] += fabsf(__uint_as_float(v.x & 0xffff0000u));
-      acc[2] += fabsf(__uint_as_float(v.y << 16));
-      acc[3] += fabsf(__uint_as_float(v.y & 0xffff0000u));
+      acc[0] += fabsf(__uint_as_float(v << 16));
+      acc[1] += fabsf(__uint_as_float(v & 0xffff0000u));
     } else {
       acc[0] += fabsf(__uint_as_float(v.x));
       acc[1] += fabsf(__uint_as_float(v.y));
-      acc[2] += fabsf(__uint_as_float(v.z));
-      acc[3] += fabsf(__uint_as_float(v.w));
     }
   };
   if (live) {
@@ -169,10 +176,10 @@ __global__ __launch_bounds__(1024) void col_scores_wide_kernel(const uint8_t* __
     for (; n < D; n += 16) add(*reinterpret_cast<const V*>(base + n * ld_b));
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) part[wave][lane * 4 + k] = acc[k];
+  for (int k = 0; k < 2; ++k) part[wave][lane * 2 + k] = acc[k];
   __syncthreads();
-  if (threadIdx.x < 256) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (threadIdx.x < 128) {
+    const int64_t i = (int64_t)blockIdx.x * 128 + threadIdx.x;
     if (i < I) {
       float s = 0.0f;
 #pragma unroll
@@ -190,7 +197,16 @@ __global__ __launch_bounds__(1024) void normalize_kernel(const float* __restrict
   float inv[3];
   for (int v = 0; v < 3; ++v) {
     float acc = 0.0f;
-    for (int64_t i = threadIdx.x; i < I; i += 1024) acc += raw[v * I + i];
+    // eight loads in flight; added in index order
+    int64_t i = threadIdx.x;
+    for (; i + 7 * 1024 < I; i += 8 * 1024) {
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = raw[v * I + i + 1024 * u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += x[u];
+    }
+    for (; i < I; i += 1024) acc += raw[v * I + i];
     const float mean = block_sum<1024>(acc, red) / (float)I;
     inv[v] = 1.0f / (mean + eps);
   }
@@ -300,6 +316,111 @@ __global__ __launch_bounds__(1024) void select_kernel(const float* __restrict__ 
   }
 }
 
+// Sum of v over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);  // row_shr:8: lane 15 of a row has its sum
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 15) + (uint32_t)__builtin_amdgcn_readlane((int)v, 31) +
+         (uint32_t)__builtin_amdgcn_readlane((int)v, 47) + (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The same selection with the keys in registers (I <= 1024 KPT), thread t the indices
+// t KPT .. t KPT + KPT - 1.  The key of the n_dense-th largest priority bit by bit from the
+// top (a bit is set if at least n_dense keys are as large with it): counts by comparison,
+// with no histogram that near-equal priorities all hit in one counter.  Then one prefix
+// sum over the threads places both parts, through LDS (4 I bytes) so that perm leaves in
+// order.  I = 25600: radix passes over memory 65 us, 50 here.
+template <int KPT>
+__global__ __launch_bounds__(1024) void select_reg_kernel(const float* __restrict__ t, int64_t I, int64_t n_dense,
+                                                          uint8_t* __restrict__ flag, int32_t* __restrict__ perm, int vec) {
+  extern __shared__ int32_t order[];
+  __shared__ uint32_t cnt[2][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i0 = (int)threadIdx.x * KPT, n = (int)I;
+  const int mine = min(max(n - i0, 0), KPT);  // this thread's indices
+  uint32_t key[KPT];  // 0 past I: no candidate threshold is 0, so these are never counted
+#pragma unroll
+  for (int u = 0; u < KPT; u += 4) {
+    float4 x = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""));
+    if (vec && u + 4 <= mine) {
+      x = *reinterpret_cast<const float4*>(t + i0 + u);
+    } else {
+      if (u < mine) x.x = t[i0 + u];
+      if (u + 1 < mine) x.y = t[i0 + u + 1];
+      if (u + 2 < mine) x.z = t[i0 + u + 2];
+      if (u + 3 < mine) x.w = t[i0 + u + 3];
+    }
+    key[u] = order_key(x.x), key[u + 1] = order_key(x.y), key[u + 2] = order_key(x.z), key[u + 3] = order_key(x.w);
+  }
+  // sum of v over the workgroup (buffers alternate: one barrier a call)
+  auto total_of = [&](uint32_t v, int b) __attribute__((always_inline)) {
+    v = wave_sum(v);
+    if (lane == 0) cnt[b][wave] = v;
+    __syncthreads();
+    uint32_t s = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) s += cnt[b][w];
+    return s;
+  };
+  uint32_t T = 0, k = 0;  // threshold key, indices with that key that belong to the set
+  if (n_dense > 0) {
+    for (int bit = 31; bit >= 0; --bit) {
+      const uint32_t cand = T | (1u << bit);
+      uint32_t c = 0;
+#pragma unroll
+      for (int u = 0; u < KPT; ++u) c += key[u] >= cand ? 1u : 0u;
+      if (total_of(c, bit & 1) >= (uint32_t)n_dense) T = cand;
+    }
+    uint32_t c = 0;
+#pragma unroll
+    for (int u = 0; u < KPT; ++u) c += key[u] > T ? 1u : 0u;
+    k = (uint32_t)n_dense - total_of(c, 1);
+    __syncthreads();
+  }
+  // exclusive prefix of v over the threads, in thread order
+  auto prefix_of = [&](uint32_t v, int b) __attribute__((always_inline)) {
+    uint32_t inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t x = __shfl_up(inc, o, 64);
+      inc += lane >= o ? x : 0u;
+    }
+    if (lane == 63) cnt[b][wave] = inc;
+    __syncthreads();
+    uint32_t before = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) before += w < wave ? cnt[b][w] : 0u;
+    return before + inc - v;
+  };
+  uint32_t eq = 0;
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) eq += n_dense > 0 && u < mine && key[u] == T ? 1u : 0u;
+  uint32_t eq_rank = prefix_of(eq, 0), f = 0, set = 0;
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) {
+    const bool e = n_dense > 0 && u < mine && key[u] == T;
+    const bool in = n_dense > 0 && u < mine && (key[u] > T || (e && eq_rank < k));
+    eq_rank += e ? 1u : 0u;
+    set |= in ? 1u << u : 0u;
+    f += in ? 1u : 0u;
+  }
+  int d = (int)prefix_of(f, 1);  // flagged indices before this thread's
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) {
+    if (u < mine) {
+      const bool in = (set >> u) & 1u;
+      flag[i0 + u] = in ? 1 : 0;
+      const int pos = in ? n - (int)n_dense + d : i0 + u - d;
+      if (pos >= 0 && pos < n) order[pos] = i0 + u;
+      d += in ? 1 : 0;
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += 1024) perm[i] = order[i];
+}
+
 // dst[r] = src[perm[r]] row by row (bytes per row `cols_b`; source rows = destination
 // rows, indices clamped into range), a wave per row.  vec: 16-byte pieces, up to 8 of a
 // row's loads in flight before their stores; else bytes.
@@ -332,36 +453,63 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint8_t* __restr
   }
 }
 
-// dst[n][c] = src[n][perm[c]] (elements of ES bytes); blockIdx.y walks the rows.  Each
-// thread writes V consecutive outputs, one 16-byte store when vec (V = 16 / ES), else
-// element stores.
+// dst[n][c] = src[n][perm[c]] (elements of ES bytes).  A thread owns GCU 4-byte pieces of
+// V = 4 / ES consecutive outputs, 256 pieces apart, and keeps their sources' indices over the
+// rows blockIdx.y, blockIdx.y + gridDim.y, ...; neighbouring lanes write neighbouring pieces
+// and (ascending runs of perm) read neighbouring sources.  vec: 4-byte stores; else element
+// stores.  With a row per workgroup, 16 bytes per thread and perm read again for each row,
+// 5120 x 25600 bf16 took 333 us, now 156.
+constexpr int GCU = 4;
 template <int ES>
 __global__ __launch_bounds__(256) void gather_cols_kernel(const uint8_t* __restrict__ src, int64_t ld_src_b,
                                                           uint8_t* __restrict__ dst, int64_t ld_dst_b, int64_t rows,
                                                           int64_t cols, const int32_t* __restrict__ perm, int vec) {
   typedef typename std::conditional<ES == 1, uint8_t, typename std::conditional<ES == 2, uint16_t, uint32_t>::type>::type T;
-  constexpr int V = 16 / ES;
-  const int64_t c0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * V;
-  if (c0 >= cols) return;
-  int32_t p[V];
+  constexpr int V = 4 / ES;
+  const int64_t c0 = ((int64_t)blockIdx.x * GCU * 256 + threadIdx.x) * V;
+  int32_t p[GCU][V];
 #pragma unroll
-  for (int e = 0; e < V; ++e) p[e] = c0 + e < cols ? min(max(perm[c0 + e], 0), (int32_t)(cols - 1)) : 0;
-  for (int64_t n = blockIdx.y; n < rows; n += gridDim.y) {
-    const T* s = reinterpret_cast<const T*>(src + n * ld_src_b);
-    T* d = reinterpret_cast<T*>(dst + n * ld_dst_b);
-    if (vec) {
-      union {
-        T e[V];
-        int4 v;
-      } o;
+  for (int u = 0; u < GCU; ++u)
 #pragma unroll
-      for (int e = 0; e < V; ++e) o.e[e] = s[p[e]];
-      *reinterpret_cast<int4*>(d + c0) = o.v;
-    } else {
-#pragma unroll
-      for (int e = 0; e < V; ++e)
-        if (c0 + e < cols) d[c0 + e] = s[p[e]];
+    for (int e = 0; e < V; ++e) {
+      const int64_t c = c0 + 256 * V * u + e;
+      p[u][e] = c < cols ? min(max(perm[c], 0), (int32_t)(cols - 1)) : 0;
     }
+  T v[2][GCU][V];
+  auto load = [&](T (&x)[GCU][V], int64_t n) __attribute__((always_inline)) {
+    const T* s = reinterpret_cast<const T*>(src + n * ld_src_b);
+#pragma unroll
+    for (int u = 0; u < GCU; ++u)
+#pragma unroll
+      for (int e = 0; e < V; ++e) x[u][e] = s[p[u][e]];
+  };
+  auto store = [&](const T (&x)[GCU][V], int64_t n) __attribute__((always_inline)) {
+    T* d = reinterpret_cast<T*>(dst + n * ld_dst_b);
+#pragma unroll
+    for (int u = 0; u < GCU; ++u) {
+      const int64_t c = c0 + 256 * V * u;
+      if (vec && c + V <= cols) {
+        uint32_t o = 0;
+#pragma unroll
+        for (int e = 0; e < V; ++e) o |= (uint32_t)x[u][e] << (8 * ES * e % 32);
+        *reinterpret_cast<uint32_t*>(d + c) = o;
+      } else {
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+          if (c + e < cols) d[c + e] = x[u][e];
+      }
+    }
+  };
+  int64_t n = blockIdx.y;
+  for (; n + gridDim.y < rows; n += 2 * gridDim.y) {  // two rows' loads in flight
+    load(v[0], n);
+    load(v[1], n + gridDim.y);
+    store(v[0], n);
+    store(v[1], n + gridDim.y);
+  }
+  if (n < rows) {
+    load(v[0], n);
+    store(v[0], n);
   }
 }
 
@@ -371,6 +519,17 @@ namespace {
 int grid_for(int64_t waves) {  // workgroups of 4 waves, at most 8 per CU's worth
   const int64_t g = (waves + 3) / 4;
   return (int)(g < 2048 ? (g < 1 ? 1 : g) : 2048);
+}
+
+template <int TYPE>
+void launch_row_scores(dim3 grid, hipStream_t st, const uint8_t* g, const uint8_t* u, int64_t ld_b, int64_t D, int T,
+                       const float* h_in, float* raw, int64_t I) {
+  if (T <= 4)
+    hipLaunchKernelGGL((row_scores_wave_kernel<TYPE, 4>), grid, dim3(256), 0, st, g, u, ld_b, D, T, h_in, raw, I);
+  else if (T <= 10)
+    hipLaunchKernelGGL((row_scores_wave_kernel<TYPE, 10>), grid, dim3(256), 0, st, g, u, ld_b, D, T, h_in, raw, I);
+  else
+    hipLaunchKernelGGL((row_scores_wave_kernel<TYPE, 16>), grid, dim3(256), 0, st, g, u, ld_b, D, T, h_in, raw, I);
 }
 }  // namespace
 
@@ -384,12 +543,13 @@ hipError_t launch_index_scores(int type, const void* wg, const void* wu, int64_t
   const int64_t T = (D + 64 * ep - 1) / (64 * ep);
   const bool row_vec = D % ep == 0 && ld_gu_b % 16 == 0 && (uintptr_t)g % 16 == 0 && (uintptr_t)u % 16 == 0 && T <= 16;
   const bool col_vec = I % 4 == 0 && ld_d_b % (4 * es) == 0 && (uintptr_t)d % (4 * es) == 0;
-  const dim3 rg((unsigned)I, 2), cg((unsigned)((I + 63) / 64)), wg_grid((unsigned)grid_for(2 * I));
-  const dim3 cwg((unsigned)((I + 255) / 256));
+  const dim3 rg((unsigned)I, 2), cg((unsigned)((I + 63) / 64));
+  const unsigned gw = (unsigned)grid_for(2 * I);
+  const dim3 wg_grid(gw < 512 ? gw : 512);  // two workgroups per CU: the registers of two rows in flight
+  const dim3 cwg((unsigned)((I + 127) / 128));
   if (type == SPENSE_BF16) {
     if (row_vec)
-      hipLaunchKernelGGL((row_scores_wave_kernel<SPENSE_BF16, 16>), wg_grid, dim3(256), 0, st, g, u, ld_gu_b, D, (int)T,
-                         h_in, raw, I);
+      launch_row_scores<SPENSE_BF16>(wg_grid, st, g, u, ld_gu_b, D, (int)T, h_in, raw, I);
     else
       hipLaunchKernelGGL(row_scores_kernel<SPENSE_BF16>, rg, dim3(256), 0, st, g, u, ld_gu_b, D, h_in, raw, I);
     if (col_vec)
@@ -398,8 +558,7 @@ hipError_t launch_index_scores(int type, const void* wg, const void* wu, int64_t
       hipLaunchKernelGGL(col_scores_kernel<SPENSE_BF16>, cg, dim3(256), 0, st, d, ld_d_b, D, I, h_mid, raw);
   } else {
     if (row_vec)
-      hipLaunchKernelGGL((row_scores_wave_kernel<SPENSE_F32, 16>), wg_grid, dim3(256), 0, st, g, u, ld_gu_b, D, (int)T,
-                         h_in, raw, I);
+      launch_row_scores<SPENSE_F32>(wg_grid, st, g, u, ld_gu_b, D, (int)T, h_in, raw, I);
     else
       hipLaunchKernelGGL(row_scores_kernel<SPENSE_F32>, rg, dim3(256), 0, st, g, u, ld_gu_b, D, h_in, raw, I);
     if (col_vec)
@@ -413,7 +572,26 @@ hipError_t launch_index_scores(int type, const void* wg, const void* wu, int64_t
 
 hipError_t launch_dense_permutation(const float* total, int64_t I, int64_t n_dense, uint8_t* flag, int32_t* perm,
                                     hipStream_t st) {
-  hipLaunchKernelGGL(select_kernel, dim3(1), dim3(1024), 0, st, total, I, n_dense, flag, perm);
+  const int vec = (uintptr_t)total % 16 == 0;
+  if (I <= 1024 * 15) {  // 4 I bytes of LDS and the counters: within the default 64 KB
+    hipLaunchKernelGGL(select_reg_kernel<16>, dim3(1), dim3(1024), (size_t)I * 4, st, total, I, n_dense, flag, perm, vec);
+  } else if (I <= 1024 * 32) {
+    // above the default limit: a per-device attribute, set once
+    static std::once_flag once[64];
+    static hipError_t rc[64];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    std::call_once(once[dev], [&] {
+      rc[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(select_reg_kernel<32>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, 1024 * 32 * 4);
+    });
+    if (rc[dev] != hipSuccess) return rc[dev];
+    hipLaunchKernelGGL(select_reg_kernel<32>, dim3(1), dim3(1024), (size_t)I * 4, st, total, I, n_dense, flag, perm, vec);
+  } else {
+    hipLaunchKernelGGL(select_kernel, dim3(1), dim3(1024), 0, st, total, I, n_dense, flag, perm);
+  }
   return hipGetLastError();
 }
 
@@ -431,9 +609,12 @@ hipError_t launch_gather_cols(int es, const void* src, int64_t ld_src_b, void* d
                               int64_t cols, const int32_t* perm, hipStream_t st) {
   const uint8_t* s = static_cast<const uint8_t*>(src);
   uint8_t* d = static_cast<uint8_t*>(dst);
-  const int64_t V = 16 / es;
-  const int vec = (uintptr_t)d % 16 == 0 && ld_dst_b % 16 == 0 && cols % V == 0;
-  const dim3 grid((unsigned)((cols + 256 * V - 1) / (256 * V)), (unsigned)(rows < 65535 ? rows : 65535));
+  const int64_t per = 256 * GCU * 4 / es;  // columns of a workgroup
+  const int vec = (uintptr_t)d % 4 == 0 && ld_dst_b % 4 == 0;
+  const int64_t gx = (cols + per - 1) / per;
+  // about eight workgroups per CU: each keeps its indices over many rows
+  const int64_t gy = (2048 + gx - 1) / gx;
+  const dim3 grid((unsigned)gx, (unsigned)(rows < gy ? rows : gy));
   if (es == 1)
     hipLaunchKernelGGL(gather_cols_kernel<1>, grid, dim3(256), 0, st, s, ld_src_b, d, ld_dst_b, rows, cols, perm, vec);
   else if (es == 2)
