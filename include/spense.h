@@ -339,8 +339,9 @@ int spense_gemm_grouped(const void* X, int64_t M, int64_t ldx, int32_t count, co
  *   gives the codes and scales that spense_glu_quantize_fp8 gives for the G and U of
  *   spense_gemm_grouped, bit for bit).  A workgroup computes gate and up tiles of the
  *   same rows and pairs them on chip, so G and U are never written.  Like
- *   spense_gemm_grouped it runs the row-split kernel, which pays for up to 64 tokens;
- *   for more, two spense_gemm calls (fp32 out) and spense_glu_quantize_fp8 are faster.
+ *   spense_gemm_grouped it runs the row-split kernel, which pays for up to 64 tokens, or
+ *   the 256 x 256 kernel above that from 160 tiles of 128 rows x 256 tokens; between the
+ *   two, two spense_gemm calls (fp32 out) and spense_glu_quantize_fp8 are faster.
  * gate, up: fp8 e4m3fn, output-split, tiled layout, with equal N, K and dense_begin.
  * X: M x K fp8 codes (ldx bytes, 16-byte aligned, ldx a multiple of 16).  w_scale_gate /
  * w_scale_up: N fp32 each or NULL; x_scale: M fp32 or NULL.  H: M x N fp32, leading

@@ -639,18 +639,26 @@ def mlp(X: torch.Tensor, x_scale: torch.Tensor, gate: PackedWeight, up: PackedWe
         gate_scale=None, up_scale=None, down_scale=None, out=None, workspace: Workspace | None = None):
     """The GLU MLP of the paper's sec. 3.3.1 Eq. (4) on Spense weights: H = glu(gate(X),
     up(X)) (output-split) and (Hq, sh) its per-token fp8 quantisation (for tiled fp8
-    weights of one geometry and up to 64 tokens the GLU in the gate / up epilogue, then
-    the quantisation from the epilogue's row maxima; otherwise G and U in fp32 and the GLU
-    fused with the quantisation), Y = down(Hq) (input-split, bf16 out).  X: fp8 codes
+    weights of one geometry and up to 64 tokens, or enough for the 256 x 256 tiles, the GLU
+    in the gate / up epilogue, then the quantisation from the epilogue's row maxima;
+    otherwise G and U in fp32 and the GLU fused with the quantisation), Y = down(Hq) (input-split, bf16 out).  X: fp8 codes
     with x_scale."""
     # the paired launch runs the row-split kernel, which pays for one block of up to 64
-    # tokens; above that the grouped call (one 256 x 256 tile grid over both weights where
-    # it fills the GPU, else a plan per weight) gives G and U
+    # tokens, or the 256 x 256 kernel where its grid fills the GPU (160 tiles of 128 rows of
+    # both weights; the library's own rule); in between the grouped call (a plan per
+    # weight) gives G and U
     groupable = (gate.kind == up.kind == SPENSE_LAYOUT_TILED and gate.dtype == up.dtype == SPENSE_FP8_E4M3FN
                  and gate.split == up.split == SPENSE_SPLIT_OUTPUT)
-    paired = groupable and X.shape[0] <= 64
-    if paired and gate.N == up.N and gate.K == up.K and gate.dense_begin == up.dense_begin:
-        Hq, sh = gemm_glu_fp8(X, gate, up, gate_scale, up_scale, x_scale, workspace=workspace)
+    M = X.shape[0]
+    blocks = -(-gate.dense_begin // 128) - (-(gate.N - gate.dense_begin) // 128)
+    tiles = groupable and 64 < M <= 65536 and blocks * -(-M // 256) >= 160 and gate.N >= 512 and gate.K > 0
+    if ((groupable and M <= 64 or tiles) and gate.N == up.N and gate.K == up.K
+            and gate.dense_begin == up.dense_begin):
+        scratch = workspace
+        if tiles:  # H, of the size that G was: from the allocator for this call, not kept
+            scratch = Workspace(X.device)
+            scratch.buf = torch.empty(spense_gemm_glu_fp8_workspace_size(M, gate.N), dtype=torch.uint8, device=X.device)
+        Hq, sh = gemm_glu_fp8(X, gate, up, gate_scale, up_scale, x_scale, workspace=scratch)
     else:
         if groupable and gate.K == up.K:
             scales = None if gate_scale is None and up_scale is None else [gate_scale, up_scale]

@@ -837,7 +837,7 @@ __attribute__((constructor)) void read_log_env() {
 }
 
 const char* kernel_name(const spense::LaunchShape& ls) {
-  if (ls.big == 2) return "large-M 256x256";
+  if (ls.big == 2) return ls.glu ? "large-M 256x256, gate/up paired" : "large-M 256x256";
   // the 128 x 128 kernel in the two-half kernel's place keeps that rule's name, which callers
   // read the log for; tile=128x128 at the end of the line tells them apart
   if (ls.big == 3) return ls.halves ? "row-split, two 64-token halves" : "large-M 128x128";
@@ -992,7 +992,8 @@ int check_glu_pair(const void* X, int64_t M, int64_t ldx, const spense_packed_t*
 
 // The paired gate / up launch (arguments checked, M, N > 0): H (fp32, ldh) and, when hmax
 // is given, the per-workgroup maxima of |h| per token, hmax[m * groups + g]; *groups_out
-// receives the number of workgroups along N.
+// receives the number of maxima per token (workgroups along N, two each on the 256 x 256
+// kernel).
 int launch_glu_pair(const void* X, int64_t M, int64_t ldx, const spense_packed_t* gate, const spense_packed_t* up,
                     const float* w_scale_gate, const float* w_scale_up, const float* x_scale, float* H, int64_t ldh,
                     float* hmax, int32_t* groups_out, hipStream_t stream) {
@@ -1039,15 +1040,61 @@ int launch_glu_pair(const void* X, int64_t M, int64_t ldx, const spense_packed_t
     kind[i] = regs[i].kbound == 0 ? 0 : 1;
     tile[i] = regs[i].kbound == 0 ? tile_d : tile_s;
   }
-  int bw[2];
-  pick_waves(nreg, rows, kind, tile, 1, 4, ls.mblocks, x_cost, bw);
-  int32_t groups = 0;
-  for (int i = 0; i < nreg; ++i) {
-    regs[i].wused = bw[kind[i]];
-    regs[i].nrb = (int32_t)ceil_div(regs[i].rows, 16 * regs[i].wused);
-    regs[i].wg0 = groups;
-    groups += regs[i].nrb;
-    a.reg[i] = regs[i];
+  // Many tokens: the 256 x 256 kernel, 128 rows of both weights a tile, on the grouped
+  // launch's rule (which its callers would otherwise use for G and U); the maxima need two
+  // slots per row block, which a weight of very few rows has no room for.
+  const int64_t T256 = ceil_div(M, 256);
+  int64_t blocks = 0;
+  for (int i = 0; i < nreg; ++i) blocks += ceil_div(regs[i].rows, 128);
+  const bool big2 = M >= kBigMinM && blocks * T256 >= 160 && blocks * T256 < (1 << 22) &&
+                    2 * blocks <= ceil_div(N, 16) + 1;
+  int32_t groups = 0, slots = 0;
+  if (big2) {
+    ls.rows = 0;
+    ls.big = 2;
+    ls.ct = 4;
+    ls.mblocks = 1;
+    const int64_t GT = xcd_token_group(T256);
+    const int64_t rc = GT > 0 ? 8 / (T256 / GT) : 1;
+    Region both[2];  // as many 256-row blocks as there are pairs of 128
+    for (int i = 0; i < nreg; ++i) {
+      both[i] = regs[i];
+      both[i].rows = (int32_t)(256 * ceil_div(regs[i].rows, 128));
+    }
+    const int64_t rbl = ceil_div(regs[nreg - 1].rows, 128);
+    const int64_t half_rb = choose_half_rows(both, nreg, T256, M, rc);
+    for (int i = 0; i < nreg; ++i) {
+      regs[i].nrb = (int32_t)((ceil_div(regs[i].rows, 128) - (i == nreg - 1 ? half_rb : 0)) * T256);
+      regs[i].wg0 = groups;
+      groups += regs[i].nrb;
+      a.reg[i] = regs[i];
+    }
+    a.tblocks = (int32_t)T256;
+    a.btok = M > 256 && ceil_div(M, 192) == T256 ? 192 : 0;  // as for one weight
+    a.hg0 = groups;
+    a.hrb0 = (int32_t)(rbl - half_rb);
+    a.hper = (int32_t)ceil_div(M, 128);
+    groups = (int32_t)(groups + half_rb * a.hper);
+    if (GT > 0) {
+      const int64_t rbx = (blocks - half_rb) / rc * rc;
+      if (rbx > 0) {
+        a.xgt = (int32_t)GT;
+        a.xrc = (int32_t)rc;
+        a.xg1 = (int32_t)(rbx * T256);
+      }
+    }
+    a.hmax_ld = slots = (int32_t)(2 * blocks);
+  } else {
+    int bw[2];
+    pick_waves(nreg, rows, kind, tile, 1, 4, ls.mblocks, x_cost, bw);
+    for (int i = 0; i < nreg; ++i) {
+      regs[i].wused = bw[kind[i]];
+      regs[i].nrb = (int32_t)ceil_div(regs[i].rows, 16 * regs[i].wused);
+      regs[i].wg0 = groups;
+      groups += regs[i].nrb;
+      a.reg[i] = regs[i];
+    }
+    slots = groups;
   }
   a.nreg = nreg;
   a.groups = groups;
@@ -1068,9 +1115,9 @@ int launch_glu_pair(const void* X, int64_t M, int64_t ldx, const spense_packed_t
                                static_cast<const uint8_t*>(PW[i]->dense), (uint32_t)T.values_bytes,
                                (uint32_t)T.meta_bytes, (uint32_t)T.dense_bytes, H, ldh, SW[i], vec ? 1 : 0};
   // the row maxima take one slot per workgroup along N: at most ceil(rows / 16) per region
-  if (hmax && groups > ceil_div(N, 16) + 1) return fail(SPENSE_ERR_HIP, "internal: %d workgroups along N", groups);
+  if (hmax && slots > ceil_div(N, 16) + 1) return fail(SPENSE_ERR_HIP, "internal: %d workgroups along N", slots);
   a.hmax = hmax;
-  *groups_out = groups;
+  *groups_out = slots;
   if (g_log.load(std::memory_order_relaxed) >= 2)
     log_plan("paired gate/up", SPENSE_FP8_E4M3FN, M, N, SPENSE_SPLIT_OUTPUT, K, db, true, ls, a, 0);
   hipError_t e = spense::launch_gemm(SPENSE_FP8_E4M3FN, ls, a, stream);

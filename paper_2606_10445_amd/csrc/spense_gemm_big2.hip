@@ -42,11 +42,23 @@ constexpr int kB2SWgt = kB2RowTiles * 1024 + kB2RowTiles * 256;      // 2:4 valu
 constexpr int kB2DWgt = kB2RowTiles * 2048;                          // both dense halves of one step
 constexpr int kB2Lds = 2 * kB2XSlot + (4 * kB2SWgt > 3 * kB2DWgt ? 4 * kB2SWgt : 3 * kB2DWgt);
 
-// GR: a grouped launch (several weights sharing X and K): up to kMaxRegions regions, each
+// MODE 1: a grouped launch (several weights sharing X and K): up to kMaxRegions regions, each
 // reading its weight's buffers, output and scales from a.mat[R.mat].
-template <bool GR>
+// MODE 2: the gate / up pair (a.mat[0], a.mat[1], one geometry): a workgroup takes the same 128
+// rows of both weights, row tiles 8 wr + [0, 4) of the 16 gate's and 8 wr + [4, 8) up's, so
+// that each wave holds g and u of the same outputs and writes h = u silu(g) (fp32) and its row
+// maxima.  G and U written in fp32 and read again cost a 25600 x 5120 pair 420 MB more per
+// 2048 tokens than H does: GEMM and GLU quantisation 450 + 124 us, now 366 + 46 (the
+// quantisation reads and writes 5.7 TB/s); the whole MLP at M = 256 142 -> 126 us.
+enum { kB2Plain = 0, kB2Grouped = 1, kB2Glu = 2 };
+
+template <int MODE>
 __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
+  constexpr bool GR = MODE == kB2Grouped, GL = MODE == kB2Glu;
+  constexpr int kRows = GL ? kB2Rows / 2 : kB2Rows;  // weight rows of a tile (each of both weights)
   constexpr int RPW = 8, TC = 4;  // row tiles and token tiles of a wave
+  // the tile's first row of row tile r; the weight it belongs to is (r >> 2) & 1 in a pair
+  auto tile_row = [](int r) __attribute__((always_inline)) { return 16 * (GL ? (r >> 3) * 4 + (r & 3) : r); };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int li = lane & 15, lq = lane >> 4;
   const bool late = wave >= 4;  // dense steps: the half of the waves that runs one slot behind
@@ -81,17 +93,21 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
   }
   const Region& R = a.reg[ri];
   const int rowend = R.row0 + R.rows;
-  const int rblk = R.row0 + rb * kB2Rows;
+  const int rblk = R.row0 + rb * kRows;
   // tokens of this tile: 256, or 192 (full tiles of a 192-token block), or 128 (half tiles)
   const int ntok = half ? kB2Tokens / 2 : (a.btok > 0 ? a.btok : kB2Tokens);
   const int K = R.kend, kbound = R.kbound;
 
   extern __shared__ __attribute__((aligned(1024))) uint8_t big_lds[];
   const MatDesc& MD = a.mat[GR ? R.mat : 0];
+  // a pair: the weight whose row tiles this wave copies (values 2 wave, 2 wave + 1, metadata
+  // 4 wave .. 4 wave + 3, dense 4 w4 .. 4 w4 + 3)
+  const MatDesc& MV = GL ? a.mat[(wave >> 1) & 1] : MD;
+  const MatDesc& MM = GL ? a.mat[wave & 1] : MD;
   const __amdgpu_buffer_rsrc_t rx = rsrc(a.X, a.x_bytes),
-                               rv = GR ? rsrc(MD.values, MD.v_bytes) : rsrc(a.values, a.v_bytes),
-                               rm = GR ? rsrc(MD.meta, MD.m_bytes) : rsrc(a.meta, a.m_bytes),
-                               rd = GR ? rsrc(MD.dense, MD.d_bytes) : rsrc(a.dense, a.d_bytes);
+                               rv = GR || GL ? rsrc(MV.values, MV.v_bytes) : rsrc(a.values, a.v_bytes),
+                               rm = GR || GL ? rsrc(MM.meta, MM.m_bytes) : rsrc(a.meta, a.m_bytes),
+                               rd = GR || GL ? rsrc(MM.dense, MM.d_bytes) : rsrc(a.dense, a.d_bytes);
   v4f acc[RPW][TC];
 #pragma unroll
   for (int t = 0; t < RPW; ++t)
@@ -125,11 +141,11 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int r0 = rblk + 16 * (2 * wave + u);
+      const int r0 = rblk + tile_row(2 * wave + u);
       wo[u] = r0 < rowend ? (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 4096u + 16u * lane : kOOB;
     }
     if (wave < 4) {
-      const int r0 = rblk + 16 * (4 * wave + (lane >> 4));
+      const int r0 = rblk + tile_row(4 * wave + (lane >> 4));
       if (r0 < rowend) mo = (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 1024u + 16u * li;
     }
     // A copy past the last step reads (and writes) zeros, so that every step issues the same
@@ -239,7 +255,7 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (late) {
-        const int r0 = rblk + 16 * (4 * w4 + (i >> 1));
+        const int r0 = rblk + tile_row(4 * w4 + (i >> 1));
         lo[i] = r0 < rowend && r0 >= R.dense_row_off
                     ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
                     : kOOB;
@@ -328,12 +344,48 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
   // (out_tile_write); the waves of token quarters past the tile's tokens (2 and 3 of a 256
   // x 128 tile, 3 of a 256 x 192 one) then only help with the stores
   const bool idle = wc * (kB2Tokens / 4) >= ntok;
-  const bool via_lds = !a.out_f32 && ((uintptr_t)MD.Y % 16 == 0) && (MD.ldy % 8 == 0) && (rblk % 8 == 0);
+  const bool via_lds = !GL && !a.out_f32 && ((uintptr_t)MD.Y % 16 == 0) && (MD.ldy % 8 == 0) && (rblk % 8 == 0);
   if (idle) {
     run(std::false_type());
     if (!via_lds) return;
   } else {
     run(std::true_type());
+  }
+  if constexpr (GL) {  // no wave gets here without tokens
+    const float* const sg = a.mat[0].sw;
+    const float* const su = a.mat[1].sw;
+    const int nw = rblk + 64 * wr + 4 * lq, mw = m0 + 16 * TC * wc + li;
+    EpiScales<RPW / 2, TC> eg;
+    EpiScales<RPW / 2, 1> eu;
+    epi_scales(eg, sg, a.sx, a.M, nw, mw, rowend);
+    epi_scales(eu, su, nullptr, a.M, nw, mw, rowend);
+    // the row block's number over both regions: its two slots of the row maxima
+    const int slot = 2 * (R.wg0 / a.tblocks + rb) + wr;
+#pragma unroll
+    for (int c = 0; c < TC; ++c) {
+      const int m = mw + 16 * c;
+      float tmax = 0.0f;
+#pragma unroll
+      for (int t = 0; t < RPW / 2; ++t) {
+        const int n0 = nw + 16 * t;
+        float h[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float gg = acc[t][c][r], uu = acc[t + RPW / 2][c][r];
+          if (sg) gg = gg * eg.w[t][r];
+          if (su) uu = uu * eu.w[t][r];
+          h[r] = glu_silu(gg * eg.x[c], uu * eg.x[c]);
+          if (n0 + r < rowend) tmax = fmaxf(tmax, fabsf(h[r]));
+        }
+        if (m < a.M && n0 < rowend) put4(MD.Y, MD.ldy, MD.vec_store, a, h, m, n0, rowend);
+      }
+      if (a.hmax) {
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+        if (lq == 0 && m < a.M) a.hmax[(int64_t)m * a.hmax_ld + slot] = tmax;
+      }
+    }
+    return;
   }
   EpiScales<RPW, TC> es;
   if (!idle) epi_scales(es, MD.sw, a.sx, a.M, rblk + 16 * RPW * wr + 4 * lq, m0 + 16 * TC * wc + li, rowend);
@@ -359,9 +411,11 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
 hipError_t launch_big2(const GemmArgs& a, hipStream_t s) {
   static_assert(kB2Lds <= 160 * 1024, "LDS of a CU");
   if (!a.tiled) return hipErrorInvalidValue;  // the planner sends row-major weights to the 128 x 256 kernel
-  const bool gr = a.nmat > 1;
-  auto k = gr ? spense_gemm_big2_kernel<true> : spense_gemm_big2_kernel<false>;
-  hipError_t e = set_big_lds(k, 1, gr ? 3 : 2, kB2Lds);
+  const int mode = a.hmax_ld > 0 ? kB2Glu : (a.nmat > 1 ? kB2Grouped : kB2Plain);
+  if (mode == kB2Glu && a.nmat != 2) return hipErrorInvalidValue;
+  auto k = mode == kB2Glu ? spense_gemm_big2_kernel<kB2Glu>
+                          : (mode == kB2Grouped ? spense_gemm_big2_kernel<kB2Grouped> : spense_gemm_big2_kernel<kB2Plain>);
+  hipError_t e = set_big_lds(k, 1, 2 + mode, kB2Lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(a.groups), dim3(512), kB2Lds, s, a);
   return hipGetLastError();

@@ -277,8 +277,8 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, uint8_t* ds
 // attribute: set once per (device, kernel instance), under std::call_once, so that host
 // threads making their first large-M call together do not race.
 constexpr int kMaxDevices = 64;
-std::once_flag g_big_lds_once[kMaxDevices][2][4];  // [device][tiled][kernel instance]
-hipError_t g_big_lds_rc[kMaxDevices][2][4];
+std::once_flag g_big_lds_once[kMaxDevices][2][5];  // [device][tiled][kernel instance]
+hipError_t g_big_lds_rc[kMaxDevices][2][5];
 
 template <typename KernelT>
 hipError_t set_big_lds(KernelT k, int tiled, int which, int lds) {

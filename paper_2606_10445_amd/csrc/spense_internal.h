@@ -86,6 +86,7 @@ struct GemmArgs {
   // blocks of a row group on one XCD (row groups a multiple of 8)
   int32_t rorder, mblk;
   float* hmax;  // paired gate / up launch: per-workgroup maxima of |h| per token, hmax[m * groups + g] (or NULL)
+  int32_t hmax_ld;  // 256 x 256 kernel: > 0 = paired gate / up launch, hmax[m * hmax_ld + 2 row block + row half]
   MatDesc mat[kMaxMats];
   Region reg[kMaxRegions];
 };
@@ -107,7 +108,7 @@ struct LaunchShape {
   int big;      // large-M kernels (fp8): 1 = 128-row x 256-token workgroup tiles, 2 = 256 x 256,
                 // 3 = 128 x 128 (tiled weights, K slices)
   int halves;   // big == 3 where the two-half row-split kernel would otherwise run (the log's name for it)
-  int glu;      // row-split kernel, gate and up paired: waves 0-3 gate tiles, 4-7 the same up tiles
+  int glu;      // gate and up paired; row-split kernel: waves 0-3 gate tiles, 4-7 the same up tiles
   int xres;     // row-split kernel, one token tile: >0 = the activations of all xres chunks stay in LDS
 };
 

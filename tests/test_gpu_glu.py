@@ -224,3 +224,36 @@ def test_gemm_glu_validates_arguments(S):
         S.gemm_glu(tdev(X), pg, rowmajor)  # not the tiled layout
     with pytest.raises(ValueError):
         S.gemm_glu(tdev(X[:, :128]), pg, pg)  # K differs from X
+
+
+# The 256 x 256 kernel's pair (128 rows of both weights a tile, from 160 tiles): one token
+# block, 192-token blocks, ragged rows and tokens, regions that end inside a tile and off
+# multiples of 4, all 2:4, all dense, 256 x 128 tail tiles, partial last steps of K.
+@pytest.mark.parametrize("M,N,K,db", [(65, 20480, 160, 15360), (300, 10203, 672, 5002), (513, 7000, 512, 7000),
+                                      (700, 9000, 288, 0), (2100, 5000, 416, 3744)])
+def test_gemm_glu_tiles_exact(S, M, N, K, db, capfd):
+    say(f"[gemm-glu tiles] M={M} N={N} K={K} dense_begin={db}")
+    (Wg, mg, sg), (Wu, mu, su), X, sx = exact_pair(61 + M, M, N, K, db)
+    pg, pu = packed(S, Wg, mg, db), packed(S, Wu, mu, db)
+    Xd, sgd, sud, sxd = tdev(X), tdev(sg), tdev(su), tdev(sx)
+    G, U = S.gemm_grouped(Xd, [pg, pu], [sgd, sud], sxd, out_f32=True)
+    q0, s0 = S.glu_quantize_fp8(G, U)
+    prev = S.spense_set_log(2)
+    capfd.readouterr()
+    try:
+        for pad in (12, 3):  # 16-byte stores, element stores; the columns past N stay untouched
+            Hbuf = torch.full((M, (N + 3) // 4 * 4 + pad), 7.0, dtype=torch.float32, device="cuda")
+            H = S.gemm_glu(Xd, pg, pu, sgd, sud, sxd, out=Hbuf[:, :N])
+            q1, s1 = S.quantize_fp8(H.contiguous())
+            assert torch.equal(q1, q0) and torch.equal(s1, s0), pad
+            assert torch.all(Hbuf[:, N:] == 7.0)
+        for _ in range(3):
+            q2, s2 = S.gemm_glu_fp8(Xd, pg, pu, sgd, sud, sxd)
+            assert torch.equal(q2, q0) and torch.equal(s2, s0)
+        torch.cuda.synchronize()
+    finally:
+        S.spense_set_log(prev)
+    assert "large-M 256x256, gate/up paired" in capfd.readouterr().err
+    g, u = (y.cpu().numpy().astype(np.float64) for y in (G, U))
+    h_ref = oracle.glu_f64(g, u)
+    assert np.all(np.abs(H.cpu().numpy() - h_ref) <= glu_bound(g, u, h_ref))
