@@ -631,6 +631,13 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   // 5120 x 8192 at M = 256 (2 slices) / 517 / 2048 56 / 124 / 408 -> 45 / 62 / 202, 5120 x
   // 25600 at M = 256 (3 slices) 180 -> 108, 1024 x 5120 at M = 2048 (2 slices) 76 -> 35; the
   // row-split kernel stays at 1024 x 5120 up to M = 512 (13 at M = 128 against 19).
+  // The 256 x 256 kernel takes over where a model of it (per step 0.83 a round and 0.54 for a
+  // full chip) stays 10% below both: 8192 x 5120 at M = 2048 (256 tiles) 182 -> 119, 25600 x
+  // 5120 at M = 512 / 700 / 1024 / 2048 171 / 213 / 299 / 568 -> 108 / 165 / 194 / 387, 5120 x
+  // 8192 and x 25600 at M = 2048 186 / 620 -> 129 / 481, 12288 x 4096 at M = 700 / 1024 99 / 113
+  // -> 76 / 84; with fewer tiles one round of it is as long as two of 128 x 128 ones (8192 x
+  // 5120 at M = 512 / 1024 51 / 94 against 90 / 91, 12288 x 4096 at M = 512 68 against 74).
+  // Tiles of 256 rows x 128 tokens save only a tenth of a round (8192 x 5120 at M = 1024 89).
   if (ov.kernel == 0 && !ov.rt && !ov.waves && !ov.ct && ov.ksplit <= 1 && !ov.wused && !ov.wused_d && !ov.wused_s &&
       !ov.u8 && !ov.xres && ov.order < 0 && dtype == SPENSE_BF16 && M > 64) {
     const int64_t rb = split == SPENSE_SPLIT_OUTPUT ? ceil_div(dense_begin, 128) + ceil_div(N - dense_begin, 128)
@@ -645,6 +652,14 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
         best = t;
         mid_ks = (int)S;
       }
+    }
+    const int64_t tiles = ceil_div(M, 256) * (split == SPENSE_SPLIT_OUTPUT
+                                                  ? ceil_div(dense_begin, 256) + ceil_div(N - dense_begin, 256)
+                                                  : ceil_div(N, 256));
+    const double t256 = 8 + (double)steps * (0.54 * (double)tiles / kCUs + 0.83 * (double)ceil_div(tiles, kCUs));
+    if (t256 < 0.9 * best) {
+      mid_ks = 0;
+      big = 2;
     }
   }
   const bool mid = mid_ks > 0;
@@ -746,7 +761,7 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
     rbl = ceil_div(regs[nreg - 1].rows, 256);
     const int64_t GT = xcd_token_group(tblocks);
     const int64_t rc = GT > 0 ? 8 / (tblocks / GT) : 1;
-    half_rb = ov.halfrb >= 0 ? std::min<int64_t>(ov.halfrb, rbl) : choose_half_rows(regs, nreg, tblocks, M, rc);
+    half_rb = dtype != SPENSE_FP8_E4M3FN ? 0 : ov.halfrb >= 0 ? std::min<int64_t>(ov.halfrb, rbl) : choose_half_rows(regs, nreg, tblocks, M, rc);
     regs[nreg - 1].nrb = (int32_t)((rbl - half_rb) * tblocks);
   }
   spense::GemmArgs& a = pl->args;
@@ -766,7 +781,7 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   // gate / up at M = 257 / 300 / 384 / 540 / 576 65.8 / 65.7 / 66.4 / 86.1 / 87.0 -> 62.8 /
   // 63.3 / 65.1 / 81.9 / 82.8; Seed-OSS gate 66.8 / 66.8 / 67.4 / 95.5 / 96.0 -> 63.3 /
   // 63.6 / 65.9 / 88.0 / 89.3.
-  a.btok = big == 2 && M > 256 && ceil_div(M, 192) == tblocks ? 192 : 0;
+  a.btok = big == 2 && dtype == SPENSE_FP8_E4M3FN && M > 256 && ceil_div(M, 192) == tblocks ? 192 : 0;
   a.hg0 = groups;
   a.hrb0 = (int32_t)(rbl - half_rb);
   a.hper = (int32_t)ceil_div(M, 128);

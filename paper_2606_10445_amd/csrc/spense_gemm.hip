@@ -1434,13 +1434,13 @@ hipError_t launch_big_wv(const GemmArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_big(const LaunchShape& ls, const GemmArgs& a, hipStream_t s) {
-  if (ls.big == 2) return launch_big2(a, s);
   return ls.waves == 4 ? launch_big_wv<4>(a, s) : launch_big_wv<8>(a, s);
 }
 
 template <int DT>
 hipError_t launch_dt(const LaunchShape& ls, const GemmArgs& a, hipStream_t s) {
   if (ls.big == 3) return launch_mid(DT, a, s);
+  if (ls.big == 2) return launch_big2(DT, a, s);
   if (ls.big) return DT == kFP8 ? launch_big(ls, a, s) : hipErrorInvalidValue;
   if (a.tiled && !ls.rows) return hipErrorInvalidValue;  // the K-split kernel reads the row-major layout only
   if (ls.rows == 2) {  // two 64-token halves per workgroup: tiled fp8, 8 waves, one row tile

@@ -31,7 +31,9 @@ namespace {
 //     231 us, 2.3 PFLOP/s, in a step the random-data MMA rate above; M = 300 66 -> 54 us.
 // Measured, before (both kinds: reads one row tile ahead, copies in two bunches) -> after, us:
 // gate/up M = 300 / 512 / 2048 64 / 69 / 211 -> 51 / 59 / 206, down M = 2048 212 -> 189, o
-// 76 -> 69, q 75 -> 66.
+// 76 -> 69, q 75 -> 66.  bf16 (row-major weights, a step is 64 columns: the same bytes and
+// MMA clocks), 128 x 128 kernel -> this one: 8192 x 5120 M = 2048 182 -> 119, 25600 x 5120
+// M = 1024 / 2048 299 / 568 -> 194 / 387 (0.87 PFLOP/s).
 //
 // The activations have two stages (the B fragments of a step are in registers before its
 // MMAs, so its stage is free again half a step in), the weights four (2:4, 20 KB each) or
@@ -52,8 +54,12 @@ constexpr int kB2Lds = 2 * kB2XSlot + (4 * kB2SWgt > 3 * kB2DWgt ? 4 * kB2SWgt :
 // quantisation reads and writes 5.7 TB/s); the whole MLP at M = 256 142 -> 126 us.
 enum { kB2Plain = 0, kB2Grouped = 1, kB2Glu = 2 };
 
-template <int MODE>
+template <int DT, int MODE>
 __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
+  constexpr bool TL = DT == kFP8;  // tiled weights; bf16 reads the row-major layout
+  constexpr int ES = Traits<DT>::ES;
+  typedef std::integral_constant<int, DT> Dt;
+  static_assert(TL || MODE == kB2Plain, "grouped and paired launches are fp8");
   constexpr bool GR = MODE == kB2Grouped, GL = MODE == kB2Glu;
   constexpr int kRows = GL ? kB2Rows / 2 : kB2Rows;  // weight rows of a tile (each of both weights)
   constexpr int RPW = 8, TC = 4;  // row tiles and token tiles of a wave
@@ -96,7 +102,7 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
   const int rblk = R.row0 + rb * kRows;
   // tokens of this tile: 256, or 192 (full tiles of a 192-token block), or 128 (half tiles)
   const int ntok = half ? kB2Tokens / 2 : (a.btok > 0 ? a.btok : kB2Tokens);
-  const int K = R.kend, kbound = R.kbound;
+  const int K = R.kend * ES, kbound = R.kbound * ES;  // bytes of an activation row
 
   extern __shared__ __attribute__((aligned(1024))) uint8_t big_lds[];
   const MatDesc& MD = a.mat[GR ? R.mat : 0];
@@ -134,6 +140,11 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     // .. 4 wave + 3 (lane l: 16 bytes of tile 4 wave + l / 16, 256 s bytes in for step s).
     const int xb = 16 * ((lane & 7) ^ (lane >> 4));  // column of this lane's 16 bytes in a step; odd blocks xb ^ 64
     uint32_t xo[4], wo[2], mo = kOOB;
+    // row-major values: lane l takes the 16-byte piece (l % 4) ^ (row / 4 % 4) of row l / 4 of
+    // its tile, so that the four lane groups' reads of 16 rows meet in no bank; metadata: word
+    // l % 2 of row l / 2 of the wave's 32
+    const int vc = 16 * ((lane & 3) ^ ((lane >> 4) & 3));
+    const bool meta_wave = !TL || wave < 4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = 32 * wave + 8 * i + (lane >> 3), m = m0 + r;
@@ -141,10 +152,15 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int r0 = rblk + tile_row(2 * wave + u);
-      wo[u] = r0 < rowend ? (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 4096u + 16u * lane : kOOB;
+      const int r0 = rblk + tile_row(2 * wave + u) + (TL ? 0 : lane >> 2);
+      wo[u] = r0 >= rowend ? kOOB
+              : TL         ? (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 4096u + 16u * lane
+                           : (uint32_t)(r0 * a.v_ld_b + vc);
     }
-    if (wave < 4) {
+    if constexpr (!TL) {
+      const int r0 = rblk + 32 * wave + (lane >> 1);
+      if (r0 < rowend) mo = (uint32_t)(r0 * a.m_ld_b + 4 * (lane & 1));
+    } else if (wave < 4) {
       const int r0 = rblk + tile_row(4 * wave + (lane >> 4));
       if (r0 < rowend) mo = (uint32_t)(r0 / 16) * (uint32_t)nch_sp * 1024u + 16u * li;
     }
@@ -158,15 +174,21 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     };
     auto w_copy = [&](auto u_const, int s, int k) __attribute__((always_inline)) {
       constexpr int u = decltype(u_const)::value;
-      lds_load16<kTiledNT>(rv, sw + k * kB2SWgt + (2 * wave + u) * 1024, s < n_sp ? wo[u] : kOOB, 1024 * s);
+      if constexpr (TL)
+        lds_load16<kTiledNT>(rv, sw + k * kB2SWgt + (2 * wave + u) * 1024, s < n_sp ? wo[u] : kOOB, 1024 * s);
+      else  // rows are not padded: weights past the region read as zeros too
+        lds_load16<kNT>(rv, sw + k * kB2SWgt + (2 * wave + u) * 1024, 128 * s + 2 * vc < kbound ? wo[u] : kOOB, 64 * s);
     };
     auto m_copy = [&](int s, int k) __attribute__((always_inline)) {
-      if (wave < 4)
+      if constexpr (!TL)
+        lds_load4<kNT>(rm, sw + k * kB2SWgt + kB2RowTiles * 1024 + wave * 256,
+                       128 * s + 64 * (lane & 1) < kbound ? mo : kOOB, 8 * s);
+      else if (wave < 4)
         lds_load16<kTiledNT>(rm, sw + k * kB2SWgt + kB2RowTiles * 1024 + wave * 1024, s < n_sp ? mo : kOOB, 256 * s);
     };
     auto wait_w = [&](auto n_const) __attribute__((always_inline)) {  // all but the last n steps' weight copies
       constexpr int n = decltype(n_const)::value;
-      if (wave < 4)
+      if (meta_wave)
         wait_vm<3 * n>();
       else
         wait_vm<2 * n>();
@@ -180,8 +202,11 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     };
     auto read_a = [&](auto q_const, int t, int k) __attribute__((always_inline)) {
       constexpr int q = decltype(q_const)::value;
-      av[q] = *reinterpret_cast<const v4i*>(sw + k * kB2SWgt + (RPW * wr + t) * 1024 + 16 * lane);
-      aix[q] = *reinterpret_cast<const int*>(sw + k * kB2SWgt + kB2RowTiles * 1024 + (RPW * wr + t) * 256 + 16 * li + 4 * lq);
+      const uint8_t* const wt = sw + k * kB2SWgt + (RPW * wr + t) * 1024;
+      const uint8_t* const mt = sw + k * kB2SWgt + kB2RowTiles * 1024;
+      av[q] = *reinterpret_cast<const v4i*>(wt + (TL ? 16 * lane : 64 * li + 16 * (lq ^ (li >> 2))));
+      aix[q] = *reinterpret_cast<const int*>(TL ? mt + (RPW * wr + t) * 256 + 16 * li + 4 * lq
+                                                : mt + (RPW * wr + t) * 128 + 8 * li + 4 * (lq >> 1));
     };
     static_for<4>([&](auto i) { x_copy(i, 0, 0); });
     static_for<2>([&](auto u) { w_copy(u, 0, 0); });
@@ -190,7 +215,7 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     static_for<2>([&](auto u) { w_copy(u, 1, 1); });
     m_copy(1, 1);
     static_for<2>([&](auto u) { w_copy(u, 2, 2); });
-    if (wave < 4)
+    if (meta_wave)
       wait_vm<4 + 3 + 2>();
     else
       wait_vm<4 + 2 + 2>();
@@ -230,7 +255,7 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
           constexpr int q = t % AQ;
 #pragma unroll
           for (int c = 0; c < TC; ++c)
-            acc[t][c] = mma_sparse(av[q], bq[P][c], acc[t][c], aix[q], std::integral_constant<int, kFP8>());
+            acc[t][c] = mma_sparse(av[q], bq[P][c], acc[t][c], TL ? aix[q] : (int)((uint32_t)aix[q] >> (16 * (lq & 1))), Dt());
         }
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -255,10 +280,11 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (late) {
-        const int r0 = rblk + tile_row(4 * w4 + (i >> 1));
-        lo[i] = r0 < rowend && r0 >= R.dense_row_off
-                    ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
-                    : kOOB;
+        // row-major rows like the activations, eight per block
+        const int r0 = rblk + (TL ? tile_row(4 * w4 + (i >> 1)) : 64 * w4 + 8 * i + (lane >> 3));
+        lo[i] = !(r0 < rowend && r0 >= R.dense_row_off) ? kOOB
+                : TL ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
+                     : (uint32_t)((r0 - R.dense_row_off) * a.d_ld_b + (kbound - R.dense_col_off * ES) + (xb ^ (64 * (i & 1))));
       } else {
         const int r = 64 * w4 + 8 * i + (lane >> 3), m = m0 + r;
         lo[i] = m < a.M && r < ntok ? (uint32_t)((int64_t)m * a.ldx_b + kbound + (xb ^ (64 * (i & 1)))) : kOOB;
@@ -275,7 +301,13 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     auto w_copy = [&](int s, int k) __attribute__((always_inline)) {
       static_for<8>([&](auto i_const) {
         constexpr int i = decltype(i_const)::value;
-        lds_load16<kTiledNT>(rd, sw + k * kB2DWgt + (8 * w4 + i) * 1024, lo[i], 2048 * s + 1024 * (i & 1));
+        if constexpr (TL) {
+          lds_load16<kTiledNT>(rd, sw + k * kB2DWgt + (8 * w4 + i) * 1024, lo[i], 2048 * s + 1024 * (i & 1));
+        } else {
+          uint32_t off = lo[i];
+          if (kbound + 128 * s + 128 > K) off = kbound + 128 * s + (xb ^ (64 * (i & 1))) < K ? off : kOOB;
+          lds_load16<kNT>(rd, sw + k * kB2DWgt + (8 * w4 + i) * 1024, off, 128 * s);
+        }
       });
     };
     if (!late) {
@@ -296,7 +328,8 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     for (int s = 0; s < n_de; ++s) {
       v8i bq[TC], av[RPW];
       if constexpr (ACT) {
-        const uint8_t* wl = sw + k * kB2DWgt + (RPW * wr) * 2048 + 16 * lane;
+        const uint8_t* wl = sw + k * kB2DWgt + (RPW * wr) * 2048 + (TL ? 16 * lane : 128 * li);
+        const int wc0 = TL ? 0 : xc0, wc1 = TL ? 1024 : xc1;
 #pragma unroll
         for (int c = 0; c < TC; ++c) {
           const uint8_t* p = xr + (s & 1) * kB2XSlot + c * 2048;
@@ -304,7 +337,7 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
         }
 #pragma unroll
         for (int t = 0; t < RPW; ++t)
-          av[t] = cat8(*reinterpret_cast<const v4i*>(wl + t * 2048), *reinterpret_cast<const v4i*>(wl + t * 2048 + 1024));
+          av[t] = cat8(*reinterpret_cast<const v4i*>(wl + t * 2048 + wc0), *reinterpret_cast<const v4i*>(wl + t * 2048 + wc1));
       }
       __builtin_amdgcn_sched_barrier(0);
       // activations of step s + 1 (awaited after this step's MMAs), weights of step s + 2
@@ -323,8 +356,12 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
 #pragma unroll
         for (int t = 0; t < RPW; ++t)
 #pragma unroll
-          for (int c = 0; c < TC; ++c)
-            acc[t][c] = mma_dense(av[t], bq[c], acc[t][c], std::integral_constant<int, kFP8>());
+          for (int c = 0; c < TC; ++c) {
+            acc[t][c] = mma_dense(av[t], bq[c], acc[t][c], Dt());
+            if constexpr (!TL)
+              acc[t][c] = mma_dense(__builtin_shufflevector(av[t], av[t], 4, 5, 6, 7, 4, 5, 6, 7),
+                                    __builtin_shufflevector(bq[c], bq[c], 4, 5, 6, 7, 4, 5, 6, 7), acc[t][c], Dt());
+          }
         __builtin_amdgcn_s_setprio(0);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -408,14 +445,17 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
 
 }  // namespace
 
-hipError_t launch_big2(const GemmArgs& a, hipStream_t s) {
+hipError_t launch_big2(int dtype, const GemmArgs& a, hipStream_t s) {
   static_assert(kB2Lds <= 160 * 1024, "LDS of a CU");
-  if (!a.tiled) return hipErrorInvalidValue;  // the planner sends row-major weights to the 128 x 256 kernel
+  // the planner sends row-major fp8 weights to the 128 x 256 kernel; bf16 has no tiled layout
+  if ((dtype == kFP8) != (a.tiled != 0)) return hipErrorInvalidValue;
   const int mode = a.hmax_ld > 0 ? kB2Glu : (a.nmat > 1 ? kB2Grouped : kB2Plain);
-  if (mode == kB2Glu && a.nmat != 2) return hipErrorInvalidValue;
-  auto k = mode == kB2Glu ? spense_gemm_big2_kernel<kB2Glu>
-                          : (mode == kB2Grouped ? spense_gemm_big2_kernel<kB2Grouped> : spense_gemm_big2_kernel<kB2Plain>);
-  hipError_t e = set_big_lds(k, 1, 2 + mode, kB2Lds);
+  if ((mode == kB2Glu && a.nmat != 2) || (mode != kB2Plain && dtype != kFP8)) return hipErrorInvalidValue;
+  auto k = dtype != kFP8        ? spense_gemm_big2_kernel<kBF16, kB2Plain>
+           : mode == kB2Glu     ? spense_gemm_big2_kernel<kFP8, kB2Glu>
+           : mode == kB2Grouped ? spense_gemm_big2_kernel<kFP8, kB2Grouped>
+                                : spense_gemm_big2_kernel<kFP8, kB2Plain>;
+  hipError_t e = set_big_lds(k, a.tiled ? 1 : 0, 2 + mode, kB2Lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(a.groups), dim3(512), kB2Lds, s, a);
   return hipGetLastError();

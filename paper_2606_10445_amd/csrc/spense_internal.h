@@ -112,8 +112,8 @@ struct LaunchShape {
   int xres;     // row-split kernel, one token tile: >0 = the activations of all xres chunks stay in LDS
 };
 
-// The 256 x 256 large-M kernel (LaunchShape::big == 2).
-hipError_t launch_big2(const GemmArgs& a, hipStream_t s);
+// The 256 x 256 large-M kernel (LaunchShape::big == 2): tiled fp8 or row-major bf16 weights.
+hipError_t launch_big2(int dtype, const GemmArgs& a, hipStream_t s);
 // The 128 x 128 kernel (LaunchShape::big == 3): tiled fp8 or row-major bf16 weights.
 hipError_t launch_mid(int dtype, const GemmArgs& a, hipStream_t s);
 

@@ -30,9 +30,13 @@ CASES = [(a, M, N, K // 32 * 32, db, gen.FP8) for a, M, N, K, db in CASES]
 # multiples of 16, all-2:4, all-dense, K slices
 CASES += [(1, 513, 5000, 4128, 2080, gen.BF16), (0, 513, 9001, 4096, 6001, gen.BF16), (1, 700, 4608, 4128, 4128, gen.BF16),
           (0, 300, 8192, 4128, 0, gen.BF16), (1, 200, 2600, 16416, 12320, gen.BF16), (0, 65, 25600, 2080, 19200, gen.BF16)]
+# bf16 on the 256 x 256 kernel: ragged rows and tokens, a boundary and K inside a step, all-2:4,
+# all-dense, a row boundary off multiples of 16
+CASES256 = [(0, 1030, 9000, 2080, 6001, gen.BF16), (1, 1300, 7003, 2112, 1056, gen.BF16),
+            (1, 1100, 8200, 2080, 2080, gen.BF16), (0, 2049, 5000, 2048, 0, gen.BF16)]
 
 
-@pytest.mark.parametrize("axis,M,N,K,db,dtype", CASES)
+@pytest.mark.parametrize("axis,M,N,K,db,dtype", CASES + CASES256)
 def test_planned_tiles_exact(S, axis, M, N, K, db, dtype, capfd):
     print(f"[128x128] axis={axis} M={M} N={N} K={K} db={db} {dtype}", file=sys.stderr, flush=True)
     W, mask, X, sw, sx = gen.make_exact_int(41, M, M, N, K, gen.OUTPUT if axis == 0 else gen.INPUT, db, dtype)
@@ -49,7 +53,10 @@ def test_planned_tiles_exact(S, axis, M, N, K, db, dtype, capfd):
     finally:
         S.spense_set_log(prev)
     log = capfd.readouterr().err.strip().splitlines()[-1]
-    assert "waves=12" in log and "block_tokens=128" in log, log
+    if (axis, M, N, K, db, dtype) in CASES256:
+        assert "large-M 256x256" in log, log
+    else:
+        assert "waves=12" in log and "block_tokens=128" in log, log
     assert torch.equal(y, ref)
     for pad in (8, 3):  # whole-row stores, scalar stores; the padding is untouched
         big = torch.full((M, N + pad), 7.0, dtype=torch.bfloat16, device="cuda")
