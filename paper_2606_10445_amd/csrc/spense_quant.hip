@@ -8,12 +8,14 @@
 // even mantissa, and saturates to +-448.
 //
 // One workgroup per token row.  Rows of up to 32768 fp32 / 65536 bf16 elements with
-// 16-byte aligned rows are held in registers (1024 threads, one read); other rows take
+// 16-byte aligned rows are held in registers (1024 or 256 threads, one read); other rows take
 // two passes (the maximum, then the codes, re-reading the row from L2), the GLU value
 // computed by the same instructions in both, so the maximum is always the maximum of
 // exactly the values that are encoded (it is exact in any order).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "spense.h"
 #include "spense_internal.h"
@@ -95,19 +97,19 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_rows_kernel(const uint
   for (int64_t k = threadIdx.x; k < K; k += kQuantThreads) qr[k] = (uint8_t)encode_e4m3fn(value(k) / s);
 }
 
-// Rows held in registers (rows of up to NJ * E * kRowThreads elements, 16-byte aligned):
-// thread t owns the 16-byte pieces t + kRowThreads * j (E = 4 fp32 or 8 bf16 elements
+// Rows held in registers (rows of up to NJ * E * NT elements, 16-byte aligned): thread t of
+// NT owns the 16-byte pieces t + NT * j (E = 4 fp32 or 8 bf16 elements
 // each), loads them all at once, keeps the activation values, reduces the maximum over
 // the workgroup and encodes from registers, one 4- or 8-byte store of codes per piece.
 constexpr int kRowThreads = 1024;
 
-template <int TYPE, bool GLU, int NJ>
-__global__ __launch_bounds__(kRowThreads) void quantize_rows_reg_kernel(const uint8_t* __restrict__ src0, int64_t ld0_b,
+template <int TYPE, bool GLU, int NJ, int NT>
+__global__ __launch_bounds__(NT) void quantize_rows_reg_kernel(const uint8_t* __restrict__ src0, int64_t ld0_b,
                                                                         const uint8_t* __restrict__ src1, int64_t ld1_b,
                                                                         int64_t K, uint8_t* __restrict__ q, int64_t ldq,
                                                                         float* __restrict__ scales) {
   constexpr int E = TYPE == SPENSE_BF16 ? 8 : 4;
-  __shared__ float red[kRowThreads / 64];
+  __shared__ float red[NT / 64];
   const int64_t m = blockIdx.x;
   const uint8_t* r0 = src0 + m * ld0_b;
   const uint8_t* r1 = GLU ? src1 + m * ld1_b : nullptr;
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(kRowThreads) void quantize_rows_reg_kernel(const ui
   v4i ra[NJ], rb[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    const int64_t k0 = (int64_t)E * (threadIdx.x + kRowThreads * j);
+    const int64_t k0 = (int64_t)E * (threadIdx.x + NT * j);
     const int64_t ks = k0 + E <= K ? k0 : 0;
     ra[j] = *reinterpret_cast<const v4i*>(r0 + ks * ES);
     if constexpr (GLU) rb[j] = *reinterpret_cast<const v4i*>(r1 + ks * ES);
@@ -126,7 +128,7 @@ __global__ __launch_bounds__(kRowThreads) void quantize_rows_reg_kernel(const ui
   float amax = 0.0f;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    const int64_t k0 = (int64_t)E * (threadIdx.x + kRowThreads * j);
+    const int64_t k0 = (int64_t)E * (threadIdx.x + NT * j);
     if (k0 + E <= K) {  // a whole piece
       const v4i a = ra[j];
       v4i b = {0, 0, 0, 0};
@@ -158,13 +160,13 @@ __global__ __launch_bounds__(kRowThreads) void quantize_rows_reg_kernel(const ui
 #pragma unroll
     for (int e = 0; e < E; ++e) amax = fmaxf(amax, fabsf(v[j][e]));
   }
-  amax = block_max<kRowThreads>(amax, red);
+  amax = block_max<NT>(amax, red);
   const float s = amax > 0.0f ? amax / 448.0f : 1.0f;
   if (threadIdx.x == 0) scales[m] = s;
   uint8_t* qr = q + m * ldq;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    const int64_t k0 = (int64_t)E * (threadIdx.x + kRowThreads * j);
+    const int64_t k0 = (int64_t)E * (threadIdx.x + NT * j);
     float t[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) t[e] = v[j][e] / s;
@@ -251,18 +253,40 @@ hipError_t launch_quant_type(const uint8_t* a, int64_t ld0_b, const uint8_t* b, 
   const int64_t nj = (pieces + kRowThreads - 1) / kRowThreads;
   const dim3 grid((unsigned)M);
   if (aligned && nj <= 8) {
+    auto launch = [&](auto nj_const, auto nt_const) {
+      constexpr int NJ = decltype(nj_const)::value, NT = decltype(nt_const)::value;
+      hipLaunchKernelGGL((quantize_rows_reg_kernel<TYPE, GLU, NJ, NT>), grid, dim3(NT), 0, st, a, ld0_b, b, ld1_b, K, q,
+                         ldq, scales);
+    };
+    // 256 threads a row instead of 1024 where that leaves fewer idle threads or, above a row
+    // per CU, more rows in flight (2048 rows of 1024 threads run in four rounds of two a CU).
+    // us, 1024 -> 256 threads, bf16: M = 2048 K = 2048 / 4096 / 5120 / 8192 / 10240 13.2 / 13.5
+    // / 13.6 / 14.2 / 20.5 -> 6.4 / 6.5 / 9.2 / 12.5 / 14.9, M = 517 6.0 / 5.9 / 6.0 / 5.8 / 8.5
+    // -> 4.0 / 3.8 / 4.7 / 5.5 / 6.3; M = 16 K = 2048 / 4096 / 10240 3.5 / 3.5 / 4.5 -> 3.2 / 3.0
+    // / 4.0 but K = 5120 / 8192 (three, four pieces a thread) 3.5 / 3.3 against 3.6 / 3.7; longer
+    // rows (K = 16384: 21.6 against 20.8 at M = 2048, 4.2 against 4.9 at 16) stay with 1024.
+    const int64_t n256 = (pieces + 255) / 256;
+    if (!GLU && n256 <= 5 && (M > 256 || n256 <= 2 || n256 == 5)) {
+      std::integral_constant<int, 256> nt;
+      if (n256 <= 2)
+        launch(std::integral_constant<int, 2>(), nt);
+      else if (n256 <= 3)
+        launch(std::integral_constant<int, 3>(), nt);
+      else if (n256 <= 4)
+        launch(std::integral_constant<int, 4>(), nt);
+      else
+        launch(std::integral_constant<int, 5>(), nt);
+      return hipGetLastError();
+    }
+    std::integral_constant<int, kRowThreads> nt;
     if (nj <= 1)
-      hipLaunchKernelGGL((quantize_rows_reg_kernel<TYPE, GLU, 1>), grid, dim3(kRowThreads), 0, st, a, ld0_b, b, ld1_b, K,
-                         q, ldq, scales);
+      launch(std::integral_constant<int, 1>(), nt);
     else if (nj <= 2)
-      hipLaunchKernelGGL((quantize_rows_reg_kernel<TYPE, GLU, 2>), grid, dim3(kRowThreads), 0, st, a, ld0_b, b, ld1_b, K,
-                         q, ldq, scales);
+      launch(std::integral_constant<int, 2>(), nt);
     else if (nj <= 4)
-      hipLaunchKernelGGL((quantize_rows_reg_kernel<TYPE, GLU, 4>), grid, dim3(kRowThreads), 0, st, a, ld0_b, b, ld1_b, K,
-                         q, ldq, scales);
+      launch(std::integral_constant<int, 4>(), nt);
     else
-      hipLaunchKernelGGL((quantize_rows_reg_kernel<TYPE, GLU, 8>), grid, dim3(kRowThreads), 0, st, a, ld0_b, b, ld1_b, K,
-                         q, ldq, scales);
+      launch(std::integral_constant<int, 8>(), nt);
   } else {
     hipLaunchKernelGGL((quantize_rows_kernel<TYPE, GLU>), grid, dim3(kQuantThreads), 0, st, a, ld0_b, b, ld1_b, K, q,
                        ldq, scales);

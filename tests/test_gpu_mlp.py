@@ -125,6 +125,28 @@ def check_glu_codes(q, s, G, U):
     assert same.mean() >= 0.999
 
 
+# the rows' thread counts change at two, three, four and five pieces of 256 x 16 bytes and
+# above 256 rows; ragged ends on both sides of each
+@pytest.mark.parametrize("M", [3, 256, 257])
+@pytest.mark.parametrize("src,pieces", [("f32", p) for p in (256, 512, 513, 768, 1024, 1025, 1280, 1281)]
+                         + [("bf16", p) for p in (512, 513, 768, 1024, 1025, 1280, 1281)])
+def test_quantize_fp8_thread_rules(S, M, src, pieces):
+    say(f"[quantize rules] {src} M={M} pieces={pieces}")
+    e = 8 if src == "bf16" else 4
+    K = pieces * e - (3 if pieces % 256 == 1 else 0)
+    big = torch.zeros((M, (K + 7) // 8 * 8), dtype=torch.float32)
+    big[:, :K] = torch.from_numpy(rows(K, M, K))
+    if src == "bf16":
+        big = big.to(torch.bfloat16)
+    qbuf = torch.full((M, big.shape[1]), 0xAB, dtype=torch.uint8, device="cuda")
+    q, s = S.quantize_fp8(big.cuda()[:, :K], q=qbuf[:, :K])
+    torch.cuda.synchronize()
+    rq, rs = oracle.quantize_rows(np.ascontiguousarray(big[:, :K].float().numpy()))
+    assert same_codes(q.cpu().numpy(), rq)
+    assert np.array_equal(s.cpu().numpy().view(np.uint32), rs.view(np.uint32))
+    assert torch.all(qbuf[:, K:] == 0xAB)
+
+
 @pytest.mark.parametrize("M,I", [(1, 64), (5, 1000), (64, 25600), (33, 257)])
 @pytest.mark.parametrize("src", ["f32", "bf16"])
 def test_glu_quantize_fp8_valid_rounding(S, M, I, src):
