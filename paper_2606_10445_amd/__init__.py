@@ -319,29 +319,38 @@ def _row_major(t: torch.Tensor, name: str):
 
 class Workspace:
     """A device buffer for spense_gemm's scratch, grown on demand and reused across calls
-    (calls that overlap on one workspace race)."""
+    (calls that overlap on one workspace race).  A buffer that a captured call used is kept
+    when a larger one replaces it: the graph holds its address."""
 
     def __init__(self, device):
         self.device = torch.device(device)
         self.buf = None
+        self._captured = []  # buffers that captured calls used
 
     def get(self, nbytes: int):
         if nbytes == 0:
             return None, 0
         if self.buf is None or self.buf.numel() < nbytes:
             self.buf = torch.zeros(max(nbytes, 1 << 20), dtype=torch.uint8, device=self.device)
+        if torch.cuda.is_current_stream_capturing() and not any(b is self.buf for b in self._captured):
+            self._captured.append(self.buf)
         return self.buf.data_ptr(), self.buf.numel()
 
 
-_workspaces: dict = {}
+class _CallScratch:
+    """The scratch of one call that was given no workspace: from torch's allocator, so that
+    calls on other streams or threads hold other memory and a captured call's belongs to its
+    graph.  The allocator hands it out again only in this stream's order."""
 
+    def __init__(self, device):
+        self.device = device
+        self.buf = None
 
-def workspace_for(device) -> Workspace:
-    d = torch.device(device)
-    key = (d.type, d.index if d.index is not None else torch.cuda.current_device())
-    if key not in _workspaces:
-        _workspaces[key] = Workspace(torch.device("cuda", key[1]))
-    return _workspaces[key]
+    def get(self, nbytes: int):
+        if nbytes == 0:
+            return None, 0
+        self.buf = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        return self.buf.data_ptr(), nbytes
 
 
 class PackedWeight:
@@ -466,7 +475,7 @@ def gemm(X: torch.Tensor, pw: PackedWeight, w_scale=None, x_scale=None, out=None
     _check_scale(w_scale, pw.N, X.device, "w_scale")
     _check_scale(x_scale, M, X.device, "x_scale")
     out = _out(out, M, pw.N, out_f32, X.device)
-    ws = workspace or workspace_for(X.device)
+    ws = workspace or _CallScratch(X.device)
     flags = SPENSE_OUT_F32 if out_f32 else SPENSE_OUT_BF16
     if plan is None:
         wp, wn = ws.get(spense_gemm_workspace_size(M, pw.desc))
@@ -571,7 +580,7 @@ def gemm_glu_fp8(X: torch.Tensor, gate: PackedWeight, up: PackedWeight, gate_sca
     _check_scale(gate_scale, N, X.device, "gate_scale")
     _check_scale(up_scale, N, X.device, "up_scale")
     _check_scale(x_scale, M, X.device, "x_scale")
-    ws = workspace or workspace_for(X.device)
+    ws = workspace or _CallScratch(X.device)
     wp, wn = ws.get(spense_gemm_glu_fp8_workspace_size(M, N) if M > 0 and N > 0 else 0)
     _check(spense_gemm_glu_fp8(_ptr(X), M, X.stride(0), ctypes.byref(gate.desc), ctypes.byref(up.desc),
                                _ptr(gate_scale), _ptr(up_scale), _ptr(x_scale), _ptr(q), q.stride(0), _ptr(scales),
@@ -592,7 +601,7 @@ def dense_gemm(X: torch.Tensor, W: torch.Tensor, w_scale=None, x_scale=None, out
     _check_scale(w_scale, N, X.device, "w_scale")
     _check_scale(x_scale, M, X.device, "x_scale")
     out = _out(out, M, N, out_f32, X.device)
-    ws = workspace or workspace_for(X.device)
+    ws = workspace or _CallScratch(X.device)
     wp, wn = ws.get(spense_dense_gemm_workspace_size(M, N, K, dtype))
     _check(spense_dense_gemm(_ptr(X), M, X.stride(0), _ptr(W), W.stride(0), N, K, dtype, _ptr(w_scale),
                              _ptr(x_scale), _ptr(out), out.stride(0), SPENSE_OUT_F32 if out_f32 else SPENSE_OUT_BF16,
@@ -654,11 +663,9 @@ def mlp(X: torch.Tensor, x_scale: torch.Tensor, gate: PackedWeight, up: PackedWe
     tiles = groupable and 64 < M <= 65536 and blocks * -(-M // 256) >= 160 and gate.N >= 512 and gate.K > 0
     if ((groupable and M <= 64 or tiles) and gate.N == up.N and gate.K == up.K
             and gate.dense_begin == up.dense_begin):
-        scratch = workspace
-        if tiles:  # H, of the size that G was: from the allocator for this call, not kept
-            scratch = Workspace(X.device)
-            scratch.buf = torch.empty(spense_gemm_glu_fp8_workspace_size(M, gate.N), dtype=torch.uint8, device=X.device)
-        Hq, sh = gemm_glu_fp8(X, gate, up, gate_scale, up_scale, x_scale, workspace=scratch)
+        Hq, sh = gemm_glu_fp8(X, gate, up, gate_scale, up_scale, x_scale,
+                              # above 64 tokens H is as large as G was: not kept in the workspace
+                              workspace=None if tiles else workspace)
     else:
         if groupable and gate.K == up.K:
             scales = None if gate_scale is None and up_scale is None else [gate_scale, up_scale]
@@ -756,7 +763,7 @@ def obs_factor(H: torch.Tensor, percdamp: float = 0.01, workspace: Workspace | N
     K = H.shape[0]
     U = torch.empty((K, K), dtype=torch.float32, device=H.device)
     dead = torch.empty(K, dtype=torch.uint8, device=H.device)
-    ws = workspace or workspace_for(H.device)
+    ws = workspace or _CallScratch(H.device)
     wp, wn = ws.get(spense_obs_factor_workspace_size(K))
     _check(spense_obs_factor(_ptr(H), H.stride(0), K, percdamp, _ptr(U), U.stride(0), _ptr(dead), wp, wn,
                              _stream(H.device)))
@@ -774,7 +781,7 @@ def obs_prune_24(W: torch.Tensor, U: torch.Tensor, dense_begin: int, dead: torch
         raise ValueError("W (N x K) and U (K x K) must be fp32")
     N, K = W.shape
     keep = torch.empty((N, K), dtype=torch.uint8, device=W.device)
-    ws = workspace or workspace_for(W.device)
+    ws = workspace or _CallScratch(W.device)
     wp, wn = ws.get(spense_obs_prune_workspace_size(N))
     _check(spense_obs_prune_24(_ptr(W), W.stride(0), N, K, _ptr(U), U.stride(0), _ptr(dead), dense_begin, _ptr(keep),
                                keep.stride(0), wp, wn, _stream(W.device)))
