@@ -200,14 +200,19 @@ int spense_decompress(const spense_packed_t* packed, void* W_out, int64_t ldw, h
 int spense_tile(const spense_packed_t* src, const spense_packed_t* dst, hipStream_t stream);
 
 /*
- * Device workspace (bytes) that spense_gemm needs for this M and weight; 0 means none.
- * It is non-zero when the plan cuts K into slices run by separate workgroups (weights
- * with fewer than 1024 16-row tiles at up to 64 tokens, when every slice keeps enough of
- * K: e.g. k / v and down from one token on, o from 17 tokens; few-row or long-K weights
- * at two or three 64-token blocks; long-K weights of fewer than 768 tiles at 65-128 and
- * 193-320 tokens, as 128-token blocks in 2 to 6 slices): S x M x N fp32 partial sums,
- * added in slice order by a second kernel of the same call.  The workspace is only
- * scratch between the two kernels of one call; calls that overlap on one workspace race.
+ * Device workspace (bytes) that spense_gemm uses for this M and weight; 0 means none.
+ * It is non-zero when the plan cuts K into slices run by separate workgroups: S x M x N
+ * fp32 partial sums (S <= 8), added in slice order by a second kernel of the same call.
+ * Up to 320 tokens the row-split kernels do that on weights with few rows or a long K
+ * (fewer than 1024 16-row tiles at up to 64 tokens, e.g. k / v and down from one token on,
+ * o from 17; k / v and down at 65-128, down at 129-192): the call needs that workspace.
+ * Above 64 tokens the 128 x 128 kernel does it where its tiles alone would leave compute
+ * units idle (tiled fp8 weights with K above 13824 at 65-128 and 193-320 tokens; bf16
+ * weights at any M; at most 16 MiB): with less workspace than this, or none, the call runs
+ * the plan without these slices, slower, its sums in another order, and with whatever
+ * workspace that plan needs.
+ * The workspace is only scratch between the two kernels of one call; calls that overlap
+ * on one workspace race.
  */
 size_t spense_gemm_workspace_size(int64_t M, const spense_packed_t* packed);
 
@@ -242,10 +247,12 @@ int spense_gemm(const void* X, int64_t M, int64_t ldx, const spense_packed_t* pa
  * without the workspace, the same plan and kernels, results bit for bit equal to
  * spense_gemm's.  The fp32 partial sums of K-sliced plans go to a scratch array of
  * SPENSE_NOALLOC_SCRATCH_BYTES that the library keeps on each device it runs on until the
- * process ends (a K-sliced plan needs slices x M x N x 4 bytes: 15.7 MB for a 5120-row
- * down projection at 65-128 tokens, 6 slices, or at 193-256, 3).  Every call on a device shares that array, which keeps the last call's
- * partial sums (each call writes every partial it reads): calls that overlap on one
- * device, from any stream or thread, race and must be serialised by the caller.
+ * process ends (a K-sliced plan needs slices x M x N x 4 bytes: 15.7 MB for a
+ * 5120-row down projection at 65-128 tokens, 6 slices, or at 193-256, 3).  Every call on
+ * a device shares that array, which keeps the last call's partial sums (each call writes
+ * every partial it reads): calls that overlap on one device, from any stream or thread,
+ * race and must be serialised by the caller, whatever their shape (which ones are sliced
+ * is the planner's choice).
  * SPENSE_ERR_WS if the plan would need more scratch than the array holds.  No hipMalloc,
  * hipFree or other allocation on any path.  Errors otherwise as spense_gemm.
  */

@@ -175,10 +175,11 @@ struct Plan {
 struct Override {
   int kernel = 0, rt = 0, waves = 0, ct = 0, ksplit = 0, wused = 0, wused_d = 0, wused_s = 0, order = -1, xcd = -1,
       u8 = 0, halfrb = -1, xres = 0;
+  bool no_mid_slices = false;  // the library's own: the 128 x 128 kernel without K slices (gemm_common)
   bool operator==(const Override& o) const {
     return kernel == o.kernel && rt == o.rt && waves == o.waves && ct == o.ct && ksplit == o.ksplit &&
            wused == o.wused && wused_d == o.wused_d && wused_s == o.wused_s && order == o.order && xcd == o.xcd &&
-           u8 == o.u8 && halfrb == o.halfrb && xres == o.xres;
+           u8 == o.u8 && halfrb == o.halfrb && xres == o.xres && no_mid_slices == o.no_mid_slices;
   }
 };
 
@@ -608,7 +609,7 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
     const int64_t tb = ceil_div(M, 128), wgs = rb * tb, steps = ceil_div(K, 128);
     if (tb >= 2 && K >= 2048 && wgs <= kCUs && wgs >= (tb == 2 ? 176 : (M > 1536 ? 112 : 144))) {
       mid_ks = 1;
-    } else if (ov.ksplit < 1 && wgs >= 16 && wgs < 144 && ceil_div(K, 512) >= 28 && M <= 320 && (M <= 128 || M > 192)) {
+    } else if (ov.ksplit < 1 && !ov.no_mid_slices && wgs >= 16 && wgs < 144 && ceil_div(K, 512) >= 28 && M <= 320 && (M <= 128 || M > 192)) {
       double best = 0;
       for (int64_t S = 2; S <= 8 && S * wgs <= kCUs; ++S) {
         const double bytes = 4.0 * (double)S * (double)M * (double)N;
@@ -644,7 +645,7 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
                                                     : ceil_div(N, 128);
     const int64_t wgs = rb * ceil_div(M, 128), steps = ceil_div(K, 64);
     double best = 0.9 * (M <= 256 ? 0.42e-3 : 0.34e-3) * (double)ceil_div(M, 64) * (double)ceil_div(N, 16) * (double)steps;
-    for (int64_t S = 1; S <= (ov.ksplit < 1 ? 8 : 1) && 4 * S <= std::max<int64_t>(steps, 4); ++S) {
+    for (int64_t S = 1; S <= (ov.ksplit < 1 && !ov.no_mid_slices ? 8 : 1) && 4 * S <= std::max<int64_t>(steps, 4); ++S) {
       const double bytes = S > 1 ? 4.0 * (double)S * (double)M * (double)N : 0;
       if (bytes > (double)SPENSE_NOALLOC_SCRATCH_BYTES) break;
       const double t = 8 + 0.55 * (double)ceil_div(wgs * S, kCUs) * (double)ceil_div(steps, S) + (S > 1 ? 3 + 0.65e-6 * bytes : 0);
@@ -916,6 +917,13 @@ int gemm_common(const void* X, int64_t M, int64_t ldx, int32_t dtype, int32_t sp
   if ((reinterpret_cast<uintptr_t>(Y) % out_es)) return fail(SPENSE_ERR_ALIGN, "Y misaligned");
   if ((int64_t)M * ldy > (int64_t)1 << 40) return fail(SPENSE_ERR_ARG, "Y too large");
   Plan pl = cached_plan(dtype, M, N, split, K, dense_begin, tiled, ov);
+  // The K slices of the 128 x 128 kernel are a matter of speed: a caller without their workspace
+  // gets the plan that does without them (bf16 5120 x 8192 at M = 256 57 us against 45).
+  if (pl.ls.big == 3 && pl.ws_bytes > 0 && (!ws || ws_bytes < pl.ws_bytes || !aligned16(ws))) {
+    Override one = ov;
+    one.no_mid_slices = true;
+    pl = cached_plan(dtype, M, N, split, K, dense_begin, tiled, one);
+  }
   if (pl.ws_bytes > 0) {
     if (!ws || ws_bytes < pl.ws_bytes)
       return fail(SPENSE_ERR_WS, "workspace of %zu bytes needed, %zu given", pl.ws_bytes, ws ? ws_bytes : (size_t)0);

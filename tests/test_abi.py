@@ -176,6 +176,21 @@ def test_tiled_descriptor_validation(S):
     assert S.spense_decompress(dst, 4096, 128, None) == S.SPENSE_ERR_ARG
 
 
+@pytest.mark.parametrize("dtype,N,K,split,M", [(2, 5120, 8192, 1, 256), (2, 1024, 5120, 0, 2048), (1, 4096, 14336, 1, 200)])
+def test_optional_k_slices_do_without_a_workspace(S, dtype, N, K, split, M):
+    """The slices of the 128 x 128 kernel are used where there is a workspace for them: with
+    less, or none, or one that is not aligned, the call is not refused for it.  (ldx makes X
+    span 2 GiB, so that the call ends before a launch.)"""
+    L = S.spense_layout(N, K, dtype, split, (K if split else N) * 3 // 4)
+    pk = S.spense_packed_t(dtype, split, N, K, (K if split else N) * 3 // 4, 4096, L.values_ld, 8192, L.meta_ld, 16384,
+                           L.dense_ld, S.SPENSE_LAYOUT_TILED if dtype == 1 else S.SPENSE_LAYOUT_ROWMAJOR)
+    need = S.spense_gemm_workspace_size(M, pk)
+    assert 0 < need <= S.SPENSE_NOALLOC_SCRATCH_BYTES and need % (M * N * 4) == 0
+    for ws, n in ((None, 0), (4096, need - 4), (4096 + 8, need), (4096, need)):
+        rc = S.spense_gemm(4096, M, 1 << 25, pk, None, None, 4096, N, 0, ws, n, None)
+        assert rc in (S.SPENSE_ERR_DEVICE, S.SPENSE_ERR_HIP, S.SPENSE_ERR_ARG), (ws, n)
+
+
 def test_k_slices_need_a_workspace(S):
     """Weights with few rows (down: 5120 x 25600) are sliced along K at decode M; the
     partial sums need slices x M x N floats of workspace, checked before any device call."""

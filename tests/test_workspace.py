@@ -2,8 +2,11 @@
 import threading
 import types
 
+import numpy as np
 import pytest
 import torch
+
+import gen
 
 
 @pytest.fixture(scope="module")
@@ -113,3 +116,24 @@ def test_a_graph_keeps_its_scratch(S, own):
         torch.cuda.synchronize()
         assert torch.equal(out, want)
         assert all(bool((t == 7).all()) for t in others)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 256, 5120, 8192), ("fp8", 200, 4096, 14336)])
+def test_c_call_without_a_workspace(S, dtype, M, N, K):
+    """A call that is sliced only where it has the workspace: without one, the same values
+    (whole numbers: any order of the sums) and every other result in place."""
+    print(f"[no workspace] {dtype} M={M} {N}x{K}", flush=True)
+    W, mask, X, sw, sx = gen.make_exact_int(51, 0, M, N, K, gen.INPUT, K * 3 // 4, gen.BF16 if dtype == "bf16" else gen.FP8)
+    dev = lambda a: None if a is None else torch.from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a).cuda()  # noqa: E731
+    pw = S.compress(dev(W), dev(mask), 1, K * 3 // 4)
+    pw = pw if dtype == "bf16" else S.tile(pw)
+    X, sw, sx = dev(X), dev(sw), dev(sx)
+    want = S.gemm(X, pw, sw, sx, out_f32=True)
+    y = torch.full((M, N), 7.0, device="cuda")
+    ptr = lambda t: None if t is None else t.data_ptr()  # noqa: E731
+    rc = S.spense_gemm(X.data_ptr(), M, K, pw.desc, ptr(sw), ptr(sx), y.data_ptr(), N, S.SPENSE_OUT_F32, None, 0,
+                       torch.cuda.current_stream().cuda_stream)
+    assert rc == S.SPENSE_OK
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
