@@ -947,9 +947,11 @@ int gemm_common(const void* X, int64_t M, int64_t ldx, int32_t dtype, int32_t sp
   a.M = (int32_t)M;
   a.N = (int32_t)N;
   a.out_f32 = (out_flags & SPENSE_OUT_F32) ? 1 : 0;
-  bool vec = (ldy % 4 == 0) && (reinterpret_cast<uintptr_t>(Y) % (4 * out_es) == 0);
-  for (int i = 0; i < a.nreg; ++i) vec = vec && (a.reg[i].row0 % 4 == 0);
-  a.vec_store = vec ? 1 : 0;
+  // output and partial-sum quads start at a region's first row (any dense_begin) + 4 i
+  bool vec_rows = true;
+  for (int i = 0; i < a.nreg; ++i) vec_rows = vec_rows && (a.reg[i].row0 % 4 == 0);
+  a.vec_store = vec_rows && (ldy % 4 == 0) && (reinterpret_cast<uintptr_t>(Y) % (4 * out_es) == 0) ? 1 : 0;
+  a.part_vec = vec_rows && N % 4 == 0 && aligned16(ws) ? 1 : 0;
   // extents of the range-checked loads; every one must stay below 2^31
   int64_t sparse_rows = split == SPENSE_SPLIT_OUTPUT ? dense_begin : N;
   int64_t sparse_cols = split == SPENSE_SPLIT_OUTPUT ? K : dense_begin;

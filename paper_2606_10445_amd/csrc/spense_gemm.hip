@@ -833,7 +833,7 @@ __global__ __launch_bounds__(64 * WR) void spense_gemm_rows_kernel(GemmArgs a) {
         store4e(MD.Y, MD.ldy, MD.sw != nullptr, MD.vec_store, a, es, t, cc, acc[t][cc], m, n0, rowend);
       } else {  // unscaled fp32 partial of this K slice, one 16-byte store where it can
         float* pp = a.part + ((int64_t)slice * a.M + m) * a.N + n0;
-        if (n0 + 3 < rowend && a.N % 4 == 0 && (uintptr_t)a.part % 16 == 0) {
+        if (n0 + 3 < rowend && a.part_vec) {
           *reinterpret_cast<v4f*>(pp) = acc[t][cc];
         } else {
 #pragma unroll
@@ -956,7 +956,7 @@ __global__ __launch_bounds__(64 * WR) void spense_gemm_rows2_kernel(GemmArgs a) 
       if (m >= a.M || n0 >= rowend) continue;
       const v4f v = c < CT ? acc0[0][c] : acc1[0][c - CT];
       float* pp = a.part + ((int64_t)slice * a.M + m) * a.N + n0;
-      if (n0 + 3 < rowend && a.N % 4 == 0 && (uintptr_t)a.part % 16 == 0) {
+      if (n0 + 3 < rowend && a.part_vec) {
         *reinterpret_cast<v4f*>(pp) = v;
       } else {
 #pragma unroll

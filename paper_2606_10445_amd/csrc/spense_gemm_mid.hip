@@ -285,7 +285,6 @@ __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
 
   if (S > 1) {  // unscaled fp32 partials of this K slice, one 16-byte store where it can
     if (idle) return;
-    const bool vec = a.N % 4 == 0 && (uintptr_t)a.part % 16 == 0;
 #pragma unroll
     for (int t = 0; t < RPW; ++t)
 #pragma unroll
@@ -293,7 +292,7 @@ __global__ __launch_bounds__(768) void spense_gemm_mid_kernel(GemmArgs a) {
         const int m = m0 + 16 * (TC * wc + c) + li, n0 = rblk + 16 * (RPW * wr + t) + 4 * lq;
         if (m >= a.M || n0 >= rowend) continue;
         float* pp = a.part + ((int64_t)slice * a.M + m) * a.N + n0;
-        if (vec && n0 + 3 < rowend) {
+        if (a.part_vec && n0 + 3 < rowend) {
           *reinterpret_cast<v4f*>(pp) = acc[t][c];
         } else {
 #pragma unroll

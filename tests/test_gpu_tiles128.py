@@ -26,6 +26,8 @@ CASES = [(1, 257, 6500, 2080, 1056), (0, 385, 5000, 2048, 3000), (1, 513, 4608, 
          (1, 640, 5120, 2112, 32), (0, 256, 11300, 2048, 8432), (1, 1537, 1100, 2304, 1728),
          (1, 100, 2410, 14368, 10016), (1, 250, 1100, 14336, 14336), (0, 70, 2304, 14336, 1200), (1, 128, 2435, 15000, 96)]
 CASES = [(a, M, N, K // 32 * 32, db, gen.FP8) for a, M, N, K, db in CASES]
+# K slices and a dense region that starts off multiples of 4 (its partial sums are not in whole quads)
+CASES += [(0, 70, 2304, 14336, 1202, gen.FP8)]
 # bf16, row-major: several rounds, partial steps (boundary and K off multiples of 64), rows off
 # multiples of 16, all-2:4, all-dense, K slices
 CASES += [(1, 513, 5000, 4128, 2080, gen.BF16), (0, 513, 9001, 4096, 6001, gen.BF16), (1, 700, 4608, 4128, 4128, gen.BF16),
@@ -81,3 +83,15 @@ def test_planned_tiles_repeatable(S, axis, M, N, K, db):
     for _ in range(5):
         assert torch.equal(S.gemm(X, pw, out_f32=True), first)
     assert (first - ref).norm() <= 2.0 ** -12 * ref.norm()
+
+
+@pytest.mark.parametrize("M", [16, 64, 100])
+def test_row_split_slices_off_quads(S, M):
+    """The row-split kernels' partial sums where the dense region starts off multiples of 4."""
+    N, K, db = 1024, 5120, 766
+    print(f"[slices off quads] M={M}", file=sys.stderr, flush=True)
+    W, mask, X, sw, sx = gen.make_exact_int(43, M, M, N, K, gen.OUTPUT, db, gen.FP8)
+    W, mask, X, sw, sx = (torch.from_numpy(a).cuda() for a in (W, mask, X, sw, sx))
+    pw = S.tile(S.compress(W, mask, 0, db))
+    assert S.spense_gemm_workspace_size(M, pw.desc) > 0
+    assert torch.equal(S.gemm(X, pw, sw, sx), S.gemm(X, pw, sw, sx, plan=S.plan_override(kernel=2, ksplit=1)))
