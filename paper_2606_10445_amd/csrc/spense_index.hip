@@ -570,13 +570,13 @@ hipError_t launch_index_scores(int type, const void* wg, const void* wu, int64_t
   return hipGetLastError();
 }
 
-hipError_t launch_dense_permutation(const float* total, int64_t I, int64_t n_dense, uint8_t* flag, int32_t* perm,
-                                    hipStream_t st) {
-  const int vec = (uintptr_t)total % 16 == 0;
-  if (I <= 1024 * 15) {  // 4 I bytes of LDS and the counters: within the default 64 KB
-    hipLaunchKernelGGL(select_reg_kernel<16>, dim3(1), dim3(1024), (size_t)I * 4, st, total, I, n_dense, flag, perm, vec);
-  } else if (I <= 1024 * 32) {
-    // above the default limit: a per-device attribute, set once
+namespace {
+// select_reg_kernel of up to IMAX indices: 4 I bytes of LDS, above the default limit (64 KB, with
+// the counters) by a per-device attribute that is set once.
+template <int KPT, int IMAX>
+hipError_t launch_select_reg(const float* total, int64_t I, int64_t n_dense, uint8_t* flag, int32_t* perm, hipStream_t st) {
+  static_assert(IMAX <= 1024 * KPT, "keys of a workgroup");
+  if (IMAX > 1024 * 15) {
     static std::once_flag once[64];
     static hipError_t rc[64];
     int dev = 0;
@@ -584,15 +584,32 @@ hipError_t launch_dense_permutation(const float* total, int64_t I, int64_t n_den
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     std::call_once(once[dev], [&] {
-      rc[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(select_reg_kernel<32>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 1024 * 32 * 4);
+      rc[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(select_reg_kernel<KPT>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, IMAX * 4);
     });
     if (rc[dev] != hipSuccess) return rc[dev];
-    hipLaunchKernelGGL(select_reg_kernel<32>, dim3(1), dim3(1024), (size_t)I * 4, st, total, I, n_dense, flag, perm, vec);
-  } else {
-    hipLaunchKernelGGL(select_kernel, dim3(1), dim3(1024), 0, st, total, I, n_dense, flag, perm);
   }
+  hipLaunchKernelGGL(select_reg_kernel<KPT>, dim3(1), dim3(1024), (size_t)I * 4, st, total, I, n_dense, flag, perm,
+                     (uintptr_t)total % 16 == 0 ? 1 : 0);
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_dense_permutation(const float* total, int64_t I, int64_t n_dense, uint8_t* flag, int32_t* perm,
+                                    hipStream_t st) {
+  // In registers where that is faster for any distribution of the priorities; its 32 counts have a
+  // barrier each, so the radix passes win on few indices and, like the counts of KPT keys a thread
+  // where many are padding, cost more as I grows.  us, radix passes (priorities uniform in [0, 1) /
+  // normal around 3 with deviation 0.3) and registers: I = 1024 6.5 / 7.0 and 23.5, 4096 12.3 /
+  // 13.9 and 23.8, 8192 20.9 / 24.2 and 24.7, 10240 25.0 / 29.2 and 25.8, 12288 29.1 / 34.1 and
+  // 26.6, 16384 37.0 / 43.7 and 32.2 (KPT 24; 41.4 with 32), 25600 55.1 / 65.4 and 48.9.
+  if (I <= 10240 || I > 1024 * 32) {
+    hipLaunchKernelGGL(select_kernel, dim3(1), dim3(1024), 0, st, total, I, n_dense, flag, perm);
+    return hipGetLastError();
+  }
+  if (I <= 1024 * 15) return launch_select_reg<16, 1024 * 15>(total, I, n_dense, flag, perm, st);
+  if (I <= 1024 * 24) return launch_select_reg<24, 1024 * 24>(total, I, n_dense, flag, perm, st);
+  return launch_select_reg<32, 1024 * 32>(total, I, n_dense, flag, perm, st);
 }
 
 hipError_t launch_gather_rows(const void* src, int64_t ld_src_b, void* dst, int64_t ld_dst_b, int64_t rows,

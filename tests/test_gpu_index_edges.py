@@ -13,7 +13,7 @@ def S():
     return S
 
 
-@pytest.mark.parametrize("I", [1, 15, 1023, 1025, 15360, 15361, 16384, 25601, 32768, 32769])
+@pytest.mark.parametrize("I", [1, 15, 1023, 1025, 10240, 10241, 15360, 15361, 16384, 24576, 24577, 25601, 32768, 32769])
 def test_permutation_edges(S, I):
     """TopK with ties, NaN, infinities and signed zeros; ties keep the lower index, NaN last."""
     print(f"[perm] I={I}", flush=True)
