@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -453,63 +454,81 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint8_t* __restr
   }
 }
 
-// dst[n][c] = src[n][perm[c]] (elements of ES bytes).  A thread owns GCU 4-byte pieces of
-// V = 4 / ES consecutive outputs, 256 pieces apart, and keeps their sources' indices over the
-// rows blockIdx.y, blockIdx.y + gridDim.y, ...; neighbouring lanes write neighbouring pieces
-// and (ascending runs of perm) read neighbouring sources.  vec: 4-byte stores; else element
-// stores.  With a row per workgroup, 16 bytes per thread and perm read again for each row,
-// 5120 x 25600 bf16 took 333 us, now 156.
+// dst[n][c] = src[n][perm[c]] (elements of ES bytes).  tpr threads of a workgroup (a power of
+// two; all 256 on wide rows) share a row; each owns GCU 4-byte pieces of V = 4 / ES consecutive
+// outputs, tpr pieces apart, and keeps their sources' indices over the rows n, n + step, ...;
+// neighbouring lanes write neighbouring pieces and (ascending runs of perm) read neighbouring
+// sources.  xcd: all workgroups of a row on one XCD (workgroups are dealt to the 8 XCDs
+// round-robin), so that a scattered perm's lines are read into one L2 and not into eight.
+// vec: 4-byte stores; else element stores.
+// us, 5120 x 25600, perm of two ascending runs / random: a row per workgroup and perm read again
+// for each 323 / 571 (bf16), 288 / 733 (fp32), 306 / 449 (bytes); indices kept, two rows in
+// flight, a row's workgroups on all XCDs 150 / 663, 238 / 1450, 96 / 221; now 149 / 478, 203 / 673,
+// 84 / 203.  Two rows in flight (ROWS) of fp32 push the rows out of L2 again: 227 / 779.
 constexpr int GCU = 4;
-template <int ES>
+constexpr int64_t kGatherGroups = 2048;  // eight workgroups per CU
+template <int ES, bool WIDE>
 __global__ __launch_bounds__(256) void gather_cols_kernel(const uint8_t* __restrict__ src, int64_t ld_src_b,
                                                           uint8_t* __restrict__ dst, int64_t ld_dst_b, int64_t rows,
-                                                          int64_t cols, const int32_t* __restrict__ perm, int vec) {
+                                                          int64_t cols, const int32_t* __restrict__ perm, int vec, int xcd,
+                                                          int tpr_narrow) {
   typedef typename std::conditional<ES == 1, uint8_t, typename std::conditional<ES == 2, uint16_t, uint32_t>::type>::type T;
-  constexpr int V = 4 / ES;
-  const int64_t c0 = ((int64_t)blockIdx.x * GCU * 256 + threadIdx.x) * V;
+  constexpr int V = 4 / ES, ROWS = ES == 4 ? 1 : 2;
+  const int tpr = WIDE ? 256 : tpr_narrow;
+  int64_t n = blockIdx.y, cx = blockIdx.x;
+  if (xcd) {
+    const uint32_t g = blockIdx.y * gridDim.x + blockIdx.x, l = g / 8;
+    n = l / gridDim.x * 8 + g % 8;
+    cx = l % gridDim.x;
+  }
+  int64_t step = gridDim.y;
+  if (!WIDE) {
+    n = n * (256 / tpr) + threadIdx.x / tpr;
+    step *= 256 / tpr;
+  }
+  const int64_t c0 = (cx * GCU * tpr + threadIdx.x % tpr) * V;
   int32_t p[GCU][V];
 #pragma unroll
   for (int u = 0; u < GCU; ++u)
 #pragma unroll
     for (int e = 0; e < V; ++e) {
-      const int64_t c = c0 + 256 * V * u + e;
-      p[u][e] = c < cols ? min(max(perm[c], 0), (int32_t)(cols - 1)) : 0;
+      // every index at once (those past the row again the last one's)
+      p[u][e] = min(max(perm[min(c0 + (int64_t)tpr * V * u + e, cols - 1)], 0), (int32_t)(cols - 1));
     }
-  T v[2][GCU][V];
-  auto load = [&](T (&x)[GCU][V], int64_t n) __attribute__((always_inline)) {
-    const T* s = reinterpret_cast<const T*>(src + n * ld_src_b);
+  T v[ROWS][GCU][V];
+  auto load = [&](int r) __attribute__((always_inline)) {
+    const T* const sr = reinterpret_cast<const T*>(src + (n + r * step) * ld_src_b);
 #pragma unroll
     for (int u = 0; u < GCU; ++u)
 #pragma unroll
-      for (int e = 0; e < V; ++e) x[u][e] = s[p[u][e]];
+      for (int e = 0; e < V; ++e) v[r][u][e] = sr[p[u][e]];
   };
-  auto store = [&](const T (&x)[GCU][V], int64_t n) __attribute__((always_inline)) {
-    T* d = reinterpret_cast<T*>(dst + n * ld_dst_b);
+  auto store = [&](int r) __attribute__((always_inline)) {
+    T* const dr = reinterpret_cast<T*>(dst + (n + r * step) * ld_dst_b);
 #pragma unroll
     for (int u = 0; u < GCU; ++u) {
-      const int64_t c = c0 + 256 * V * u;
+      const int64_t c = c0 + (int64_t)tpr * V * u;
       if (vec && c + V <= cols) {
         uint32_t o = 0;
 #pragma unroll
-        for (int e = 0; e < V; ++e) o |= (uint32_t)x[u][e] << (8 * ES * e % 32);
-        *reinterpret_cast<uint32_t*>(d + c) = o;
+        for (int e = 0; e < V; ++e) o |= (uint32_t)v[r][u][e] << (8 * ES * e % 32);
+        *reinterpret_cast<uint32_t*>(dr + c) = o;
       } else {
 #pragma unroll
         for (int e = 0; e < V; ++e)
-          if (c + e < cols) d[c + e] = x[u][e];
+          if (c + e < cols) dr[c + e] = v[r][u][e];
       }
     }
   };
-  int64_t n = blockIdx.y;
-  for (; n + gridDim.y < rows; n += 2 * gridDim.y) {  // two rows' loads in flight
-    load(v[0], n);
-    load(v[1], n + gridDim.y);
-    store(v[0], n);
-    store(v[1], n + gridDim.y);
-  }
-  if (n < rows) {
-    load(v[0], n);
-    store(v[0], n);
+  for (; n < rows; n += ROWS * step) {
+    load(0);
+    if (ROWS == 2 && n + step < rows) {
+      load(1);
+      store(0);
+      store(1);
+    } else {
+      store(0);
+    }
   }
 }
 
@@ -626,18 +645,26 @@ hipError_t launch_gather_cols(int es, const void* src, int64_t ld_src_b, void* d
                               int64_t cols, const int32_t* perm, hipStream_t st) {
   const uint8_t* s = static_cast<const uint8_t*>(src);
   uint8_t* d = static_cast<uint8_t*>(dst);
-  const int64_t per = 256 * GCU * 4 / es;  // columns of a workgroup
+  const int64_t pieces = (cols * es + 3) / 4;
+  int tpr = 1;
+  while (tpr < 256 && (int64_t)tpr * GCU < pieces) tpr *= 2;
   const int vec = (uintptr_t)d % 4 == 0 && ld_dst_b % 4 == 0;
-  const int64_t gx = (cols + per - 1) / per;
-  // about eight workgroups per CU: each keeps its indices over many rows
-  const int64_t gy = (2048 + gx - 1) / gx;
-  const dim3 grid((unsigned)gx, (unsigned)(rows < gy ? rows : gy));
+  const int64_t gx = (pieces + tpr * GCU - 1) / (tpr * GCU), groups = (rows + 256 / tpr - 1) / (256 / tpr);
+  // each workgroup keeps its indices over many rows
+  int64_t gy = std::min(groups, std::max<int64_t>(1, kGatherGroups / gx));
+  const int xcd = gx > 1 && gy >= 8;
+  if (xcd) gy = gy / 8 * 8;
+  const dim3 grid((unsigned)gx, (unsigned)gy);
+  auto launch = [&](auto k) {
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, st, s, ld_src_b, d, ld_dst_b, rows, cols, perm, vec, xcd, tpr);
+  };
+  const bool wide = tpr == 256;
   if (es == 1)
-    hipLaunchKernelGGL(gather_cols_kernel<1>, grid, dim3(256), 0, st, s, ld_src_b, d, ld_dst_b, rows, cols, perm, vec);
+    wide ? launch(gather_cols_kernel<1, true>) : launch(gather_cols_kernel<1, false>);
   else if (es == 2)
-    hipLaunchKernelGGL(gather_cols_kernel<2>, grid, dim3(256), 0, st, s, ld_src_b, d, ld_dst_b, rows, cols, perm, vec);
+    wide ? launch(gather_cols_kernel<2, true>) : launch(gather_cols_kernel<2, false>);
   else
-    hipLaunchKernelGGL(gather_cols_kernel<4>, grid, dim3(256), 0, st, s, ld_src_b, d, ld_dst_b, rows, cols, perm, vec);
+    wide ? launch(gather_cols_kernel<4, true>) : launch(gather_cols_kernel<4, false>);
   return hipGetLastError();
 }
 

@@ -35,7 +35,7 @@ def test_permutation_edges(S, I):
 
 
 @pytest.mark.parametrize("dtype", [torch.uint8, torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("rows,cols", [(1, 1), (3, 4097), (517, 1024), (130, 4099)])
+@pytest.mark.parametrize("rows,cols", [(1, 1), (3, 4097), (517, 1024), (130, 4099), (2049, 7), (2100, 67), (5000, 260)])
 def test_gather_cols_edges(S, dtype, rows, cols):
     """Odd widths, rows that are not 4-byte aligned, a strided destination whose padding stays."""
     g = torch.Generator(device="cuda").manual_seed(cols)
