@@ -258,15 +258,17 @@ hipError_t launch_quant_type(const uint8_t* a, int64_t ld0_b, const uint8_t* b, 
       hipLaunchKernelGGL((quantize_rows_reg_kernel<TYPE, GLU, NJ, NT>), grid, dim3(NT), 0, st, a, ld0_b, b, ld1_b, K, q,
                          ldq, scales);
     };
-    // 256 threads a row instead of 1024 where that leaves fewer idle threads or, above a row
-    // per CU, more rows in flight (2048 rows of 1024 threads run in four rounds of two a CU).
+    // 256 threads a row instead of 1024 where that leaves fewer idle threads or, above a row per
+    // CU, more rows in flight (2048 rows of 1024 threads run in four rounds of two a CU).
     // us, 1024 -> 256 threads, bf16: M = 2048 K = 2048 / 4096 / 5120 / 8192 / 10240 13.2 / 13.5
-    // / 13.6 / 14.2 / 20.5 -> 6.4 / 6.5 / 9.2 / 12.5 / 14.9, M = 517 6.0 / 5.9 / 6.0 / 5.8 / 8.5
-    // -> 4.0 / 3.8 / 4.7 / 5.5 / 6.3; M = 16 K = 2048 / 4096 / 10240 3.5 / 3.5 / 4.5 -> 3.2 / 3.0
-    // / 4.0 but K = 5120 / 8192 (three, four pieces a thread) 3.5 / 3.3 against 3.6 / 3.7; longer
-    // rows (K = 16384: 21.6 against 20.8 at M = 2048, 4.2 against 4.9 at 16) stay with 1024.
+    // / 13.6 / 14.2 / 20.5 -> 6.4 / 6.5 / 9.2 / 12.5 / 14.9; M = 16 K = 2048 / 4096 / 10240 3.5 /
+    // 3.5 / 4.5 -> 3.2 / 3.0 / 4.0.  At three pieces a thread, no fewer idle threads, from a row
+    // per CU (K = 6144, M = 256 / 257: 4.3 / 4.7 against 4.4 / 4.2), at four, none idle with
+    // 1024, from two, the first round of those (K = 8192, M = 300 / 512 / 600: 4.8 / 5.2 / 6.4
+    // against 5.1 / 5.4 / 6.1).  Longer rows (K = 16384: 21.6 against 20.8 at M = 2048, 4.2
+    // against 4.9 at 16) stay with 1024.
     const int64_t n256 = (pieces + 255) / 256;
-    if (!GLU && n256 <= 5 && (M > 256 || n256 <= 2 || n256 == 5)) {
+    if (!GLU && n256 <= 5 && M > (n256 == 3 ? 256 : n256 == 4 ? 512 : 0)) {
       std::integral_constant<int, 256> nt;
       if (n256 <= 2)
         launch(std::integral_constant<int, 2>(), nt);

@@ -126,8 +126,8 @@ def check_glu_codes(q, s, G, U):
 
 
 # the rows' thread counts change at two, three, four and five pieces of 256 x 16 bytes and
-# above 256 rows; ragged ends on both sides of each
-@pytest.mark.parametrize("M", [3, 256, 257])
+# above 256 and 512 rows; ragged ends on both sides of each
+@pytest.mark.parametrize("M", [3, 256, 257, 513])
 @pytest.mark.parametrize("src,pieces", [("f32", p) for p in (256, 512, 513, 768, 1024, 1025, 1280, 1281)]
                          + [("bf16", p) for p in (512, 513, 768, 1024, 1025, 1280, 1281)])
 def test_quantize_fp8_thread_rules(S, M, src, pieces):
