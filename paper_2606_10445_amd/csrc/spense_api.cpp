@@ -253,15 +253,15 @@ int64_t xcd_token_group(int64_t T) {
 }
 
 // 256 x 256 kernel: the row blocks at the end of the last region that run as 256 x 128
-// tiles after every full tile.  With whole tiles the last round of the grid leaves CUs
-// idle: gate / up at M = 2048 is 800 tiles of 65 (2:4) and 84 us (dense) on 256 CUs, so
-// some CUs run four tiles while the average load is 218 us (per-workgroup timestamps on
-// MI355X).  Smaller tiles dispatched last fill that round.  Measured (us, half tiles'
-// row blocks 0 -> the best): gate / up M = 2048 277 -> 248 (12-24), down and o at M =
-// 2048 240 -> 220 and 92 -> 87 (4), Seed-OSS gate 278 -> 257 (12); q at M = 2048 (one
-// round of 256 tiles) only loses.  The rule: with more than one round, half tiles worth
-// about an eighth of the work (a dense step costing 1.28 2:4 steps, a half tile 0.6 of a
-// full one), rounded up to whole XCD row classes.
+// tiles after every full tile.  Where the full tiles end in a nearly empty round of the 256
+// CUs, smaller tiles dispatched last fill it.  Measured (us, no half tiles / these / half
+// tiles also where the last round is a quarter full or more): 21632 x 4864 M = 562 (258
+// full tiles) 78 / 76, 11264 x 9728 M = 1283 (264) 147 / 140, gate / up M = 640 (300) 88 /
+// 86 and M = 2048 (800) 193 / 191, 9984 x 640 M = 2001 (312) 38.6 / 35.3; 22528 x 5120 M =
+// 768 (330) 94 / - / 96, 22912 x 3072 M = 1246 (450) 75 / - / 98, 20480 x 4096 M = 1536
+// (480) 89 / - / 110: there the half tiles start a round of their own.  As many as are worth
+// about an eighth of the work (a dense step costing 1.28 2:4 steps, a half tile 0.6 of a full
+// one), rounded up to whole XCD row classes; one row block where less than one is over.
 int64_t choose_half_rows(const spense::Region* regs, int nreg, int64_t T, int64_t M, int64_t rc) {
   double W = 0;
   int64_t rbtot = 0;
@@ -275,7 +275,9 @@ int64_t choose_half_rows(const spense::Region* regs, int nreg, int64_t T, int64_
     wl = w;
     rbl = rb;
   }
-  if (rbtot * T <= kCUs || wl <= 0) return 0;
+  const int64_t over = rbtot * T % kCUs;  // full tiles of the last round
+  if (rbtot * T <= kCUs || wl <= 0 || over == 0 || over >= kCUs / 4) return 0;
+  if (over < T) return 1;
   const double per_rb = (double)ceil_div(M, 128) * 0.6 * wl;
   int64_t rh = (int64_t)std::ceil(W / 8.0 / per_rb);
   if (rc > 1) rh = ceil_div(rh, rc) * rc;

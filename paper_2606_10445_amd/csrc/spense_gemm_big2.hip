@@ -9,7 +9,13 @@ namespace {
 // workgroup and per wave: a workgroup computes 256 weight rows x 256 tokens, its 8 waves a
 // grid of 2 row halves x 4 token quarters, each wave 128 rows (8 row tiles) x 64 tokens (4
 // token tiles, 128 accumulators).  Each B fragment read from LDS feeds 8 MMAs, each A
-// fragment 4.  Tiled weight layout only.
+// fragment 4.  fp8 weights in the tiled layout, bf16 weights row-major.
+//
+// Tiles of fewer tokens (128-token tail tiles, 192-token blocks, the block that M ends in): the
+// four waves of a row half share them, 32, 48 or 64 each (NT = 2, 3, 4 token tiles).  With 64 each
+// and waves without tokens, a 128-token tile took 0.9 of a whole one's time (one wave a SIMD hides
+// no latency, and in dense steps its slot stays as long) and a 192-token one all of it: gate / up M
+// = 540 / 640 88 / 90 us, now 83 / 85.
 //
 // What bounds a step (all measured on MI355X): the CU's load path moves about 57 bytes per
 // clock from L2 and a load instruction costs at least ~18 clocks however few bytes it moves,
@@ -29,11 +35,11 @@ namespace {
 //     waves 0-3, and while one half issues the 32 MMAs of a step back to back, the other reads
 //     its fragments and issues its copies.  gate/up with every row dense, M = 2048: 259 ->
 //     231 us, 2.3 PFLOP/s, in a step the random-data MMA rate above; M = 300 66 -> 54 us.
-// Measured, before (both kinds: reads one row tile ahead, copies in two bunches) -> after, us:
-// gate/up M = 300 / 512 / 2048 64 / 69 / 211 -> 51 / 59 / 206, down M = 2048 212 -> 189, o
-// 76 -> 69, q 75 -> 66.  bf16 (row-major weights, a step is 64 columns: the same bytes and
-// MMA clocks), 128 x 128 kernel -> this one: 8192 x 5120 M = 2048 182 -> 119, 25600 x 5120
-// M = 1024 / 2048 299 / 568 -> 194 / 387 (0.87 PFLOP/s).
+// Measured, before (both kinds: reads one row tile ahead, copies in two bunches) -> now, us, on
+// one box: gate/up M = 300 / 540 / 640 / 1024 / 2048 64 / 81 / 86 / 109 / 201 -> 49 / 83 / 85 / 103 /
+// 188; M = 2048 down 207 -> 179, o 74 -> 65, q 70 -> 61.  bf16 (row-major weights, a step is 64 columns: the same bytes and
+// MMA clocks), 128 x 128 kernel -> this one: 8192 x 5120 M = 2048 182 -> 108, 25600 x 5120
+// M = 1024 / 2048 299 / 568 -> 185 / 380 (0.88 PFLOP/s).
 //
 // The activations have two stages (the B fragments of a step are in registers before its
 // MMAs, so its stage is free again half a step in), the weights four (2:4, 20 KB each) or
@@ -52,6 +58,13 @@ constexpr int kB2Lds = 2 * kB2XSlot + (4 * kB2SWgt > 3 * kB2DWgt ? 4 * kB2SWgt :
 // maxima.  G and U written in fp32 and read again cost a 25600 x 5120 pair 420 MB more per
 // 2048 tokens than H does: GEMM and GLU quantisation 450 + 124 us, now 366 + 46 (the
 // quantisation reads and writes 5.7 TB/s); the whole MLP at M = 256 142 -> 126 us.
+// Keeps a kernel argument in its scalar registers: the compiler else loads it again where it is
+// used, in the prologue's and the epilogue's branches one memory round trip after the other.
+template <typename T>
+__device__ __forceinline__ void keep_scalar(T& v) {
+  asm volatile("" : "+s"(v));
+}
+
 enum { kB2Plain = 0, kB2Grouped = 1, kB2Glu = 2 };
 
 template <int DT, int MODE>
@@ -62,17 +75,16 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
   static_assert(TL || MODE == kB2Plain, "grouped and paired launches are fp8");
   constexpr bool GR = MODE == kB2Grouped, GL = MODE == kB2Glu;
   constexpr int kRows = GL ? kB2Rows / 2 : kB2Rows;  // weight rows of a tile (each of both weights)
-  constexpr int RPW = 8, TC = 4;  // row tiles and token tiles of a wave
+  constexpr int RPW = 8;  // row tiles of a wave
   // the tile's first row of row tile r; the weight it belongs to is (r >> 2) & 1 in a pair
   auto tile_row = [](int r) __attribute__((always_inline)) { return 16 * (GL ? (r >> 3) * 4 + (r & 3) : r); };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int li = lane & 15, lq = lane >> 4;
   const bool late = wave >= 4;  // dense steps: the half of the waves that runs one slot behind
-  const int w4 = wave & 3, wr = wave >> 2, wc = w4 ^ (2 * wr);
+  const int w4 = wave & 3, wr = wave >> 2, wc = w4;
   // Workgroups [0, hg0): 256 x 256 tiles, in the XCD-aware order when it is on.  From
   // hg0 on (dispatched last, so that they fill the tail of the grid): the row blocks
-  // hrb0 .. of the last region as 256 x 128 tiles, hper per row block; their waves of
-  // token quarters 2 and 3 only copy and take part in the barriers.
+  // hrb0 .. of the last region as 256 x 128 tiles, hper per row block.
   int g = blockIdx.x, ri, rb, m0;
   bool half = false;
   if (g < a.hg0) {
@@ -100,9 +112,14 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
   const Region& R = a.reg[ri];
   const int rowend = R.row0 + R.rows;
   const int rblk = R.row0 + rb * kRows;
-  // tokens of this tile: 256, or 192 (full tiles of a 192-token block), or 128 (half tiles)
-  const int ntok = half ? kB2Tokens / 2 : (a.btok > 0 ? a.btok : kB2Tokens);
+  // tokens of this tile: 256, or 192 (full tiles of a 192-token block), or 128 (half tiles), and
+  // those that M ends before; its four waves a row half take 16 NT of them each
+  const int ntok = min(half ? kB2Tokens / 2 : (a.btok > 0 ? a.btok : kB2Tokens), a.M - m0);
   const int K = R.kend * ES, kbound = R.kbound * ES;  // bytes of an activation row
+  uint32_t ldx = (uint32_t)a.ldx_b;  // X spans less than 2 GiB
+  keep_scalar(ldx);
+  int dense_row_off = R.dense_row_off;
+  keep_scalar(dense_row_off);
 
   extern __shared__ __attribute__((aligned(1024))) uint8_t big_lds[];
   const MatDesc& MD = a.mat[GR ? R.mat : 0];
@@ -114,25 +131,25 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
                                rv = GR || GL ? rsrc(MV.values, MV.v_bytes) : rsrc(a.values, a.v_bytes),
                                rm = GR || GL ? rsrc(MM.meta, MM.m_bytes) : rsrc(a.meta, a.m_bytes),
                                rd = GR || GL ? rsrc(MM.dense, MM.d_bytes) : rsrc(a.dense, a.d_bytes);
-  v4f acc[RPW][TC];
-#pragma unroll
-  for (int t = 0; t < RPW; ++t)
-#pragma unroll
-    for (int c = 0; c < TC; ++c) acc[t][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-
   const int n_sp = (kbound + 127) / 128, n_de = (K - kbound + 127) / 128;
   const int nch_sp = (n_sp + 3) / 4, nch_de = (n_de + 3) / 4;
 
   uint8_t* const sx = big_lds;                 // two activation stages
   uint8_t* const sw = big_lds + 2 * kB2XSlot;  // weight stages: values then metadata (four), or both dense halves (three)
 
-  const uint8_t* const xr = sx + (16 * TC * wc + li) * 128;  // (r >> 1) & 7 of the wave's rows r is (li >> 1) & 7
+  auto tile = [&](auto nt_const) __attribute__((always_inline)) {
+  constexpr int NT = decltype(nt_const)::value;  // token tiles of a wave
+  v4f acc[RPW][NT];
+#pragma unroll
+  for (int t = 0; t < RPW; ++t)
+#pragma unroll
+    for (int c = 0; c < NT; ++c) acc[t][c] = (v4f){0.f, 0.f, 0.f, 0.f};
+
+  const uint8_t* const xr = sx + (16 * NT * wc + li) * 128;  // (r >> 1) & 7 of the wave's rows r is (li >> 1) & 7
   const int xc0 = (lq ^ ((li >> 1) & 7)) << 4, xc1 = ((4 + lq) ^ ((li >> 1) & 7)) << 4;
 
-  // The 2:4 steps.  ACT = false (both run functions): a wave without tokens (token quarters
-  // past a 128- or 192-token tile) only copies and keeps the barriers.
-  auto run_sparse = [&](auto act_const) __attribute__((always_inline)) {
-    constexpr bool ACT = decltype(act_const)::value;
+  // The 2:4 steps.
+  auto run_sparse = [&]() __attribute__((always_inline)) {
     constexpr int NW = 4, AQ = 4, AD = 2, TB = 2;  // weight stages, A register sets, row tiles read ahead, barrier
     // This wave's copies (loop-invariant per-lane offsets, kOOB for rows past M or row tiles
     // past the region): activation blocks 4 wave .. 4 wave + 3 (8 tokens each), the values of
@@ -148,7 +165,7 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = 32 * wave + 8 * i + (lane >> 3), m = m0 + r;
-      xo[i] = m < a.M && r < ntok ? (uint32_t)((int64_t)m * a.ldx_b + (xb ^ (64 * (i & 1)))) : kOOB;
+      xo[i] = m < a.M && r < ntok ? (uint32_t)m * ldx + (xb ^ (64 * (i & 1))) : kOOB;
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -193,7 +210,7 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
       else
         wait_vm<2 * n>();
     };
-    v8i bq[2][TC];
+    v8i bq[2][NT];
     v4i av[AQ];
     int aix[AQ];
     auto read_b = [&](v8i& b, int st, int c) __attribute__((always_inline)) {
@@ -220,10 +237,8 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     else
       wait_vm<4 + 2 + 2>();
     barrier_lgkm0();
-    if constexpr (ACT) {
-      static_for<TC>([&](auto c) { read_b(bq[0][decltype(c)::value], 0, decltype(c)::value); });
-      static_for<AD>([&](auto t) { read_a(t, decltype(t)::value, 0); });
-    }
+    static_for<NT>([&](auto c) { read_b(bq[0][decltype(c)::value], 0, decltype(c)::value); });
+    static_for<AD>([&](auto t) { read_a(t, decltype(t)::value, 0); });
     int k = 0;  // weight stage of step s
     // Step s with the B fragments of set P (its activation stage too).  Before row tile TB, a
     // barrier: the next step's blocks have landed for every wave, and the stages of this
@@ -241,22 +256,18 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
           asm volatile("s_barrier" ::: "memory");
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (ACT) {
-          typedef std::integral_constant<int, (t + AD) % AQ> Q;
-          if constexpr (t + AD < RPW)
-            read_a(Q(), t + AD, k);
-          else
-            read_a(Q(), t + AD - RPW, kn);
-          if constexpr (t >= 3 && t < 3 + TC) read_b(bq[1 - P][t - 3], 1 - P, t - 3);
-        }
+        typedef std::integral_constant<int, (t + AD) % AQ> Q;
+        if constexpr (t + AD < RPW)
+          read_a(Q(), t + AD, k);
+        else
+          read_a(Q(), t + AD - RPW, kn);
+        if constexpr (t >= 3 && t < 3 + NT) read_b(bq[1 - P][t - 3], 1 - P, t - 3);
         if constexpr (t >= TB && t < TB + 4) x_copy(std::integral_constant<int, t - TB>(), s + 2, P);
         if constexpr (t >= 6) w_copy(std::integral_constant<int, t - 6>(), s + 3, kp);
-        if constexpr (ACT) {
-          constexpr int q = t % AQ;
+        constexpr int q = t % AQ;
 #pragma unroll
-          for (int c = 0; c < TC; ++c)
-            acc[t][c] = mma_sparse(av[q], bq[P][c], acc[t][c], TL ? aix[q] : (int)((uint32_t)aix[q] >> (16 * (lq & 1))), Dt());
-        }
+        for (int c = 0; c < NT; ++c)
+          acc[t][c] = mma_sparse(av[q], bq[P][c], acc[t][c], TL ? aix[q] : (int)((uint32_t)aix[q] >> (16 * (lq & 1))), Dt());
         __builtin_amdgcn_sched_barrier(0);
       });
       k = kn;
@@ -273,8 +284,7 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
 
   // The dense steps.  Waves 0-3 copy the activations (eight blocks each, of tokens [64 w4,
   // 64 w4 + 64)), waves 4-7 the weights (both halves of row tiles 4 w4 .. 4 w4 + 3).
-  auto run_dense = [&](auto act_const) __attribute__((always_inline)) {
-    constexpr bool ACT = decltype(act_const)::value;
+  auto run_dense = [&]() __attribute__((always_inline)) {
     const int xb = 16 * ((lane & 7) ^ (lane >> 4));
     uint32_t lo[8];
 #pragma unroll
@@ -282,12 +292,12 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
       if (late) {
         // row-major rows like the activations, eight per block
         const int r0 = rblk + (TL ? tile_row(4 * w4 + (i >> 1)) : 64 * w4 + 8 * i + (lane >> 3));
-        lo[i] = !(r0 < rowend && r0 >= R.dense_row_off) ? kOOB
-                : TL ? (uint32_t)((r0 - R.dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
-                     : (uint32_t)((r0 - R.dense_row_off) * a.d_ld_b + (kbound - R.dense_col_off * ES) + (xb ^ (64 * (i & 1))));
+        lo[i] = !(r0 < rowend && r0 >= dense_row_off) ? kOOB
+                : TL ? (uint32_t)((r0 - dense_row_off) / 16) * (uint32_t)nch_de * 8192u + 16u * lane
+                     : (uint32_t)((r0 - dense_row_off) * a.d_ld_b + (kbound - R.dense_col_off * ES) + (xb ^ (64 * (i & 1))));
       } else {
         const int r = 64 * w4 + 8 * i + (lane >> 3), m = m0 + r;
-        lo[i] = m < a.M && r < ntok ? (uint32_t)((int64_t)m * a.ldx_b + kbound + (xb ^ (64 * (i & 1)))) : kOOB;
+        lo[i] = m < a.M && r < ntok ? (uint32_t)m * ldx + kbound + (xb ^ (64 * (i & 1))) : kOOB;
       }
     }
     auto x_copy = [&](int s) __attribute__((always_inline)) {
@@ -326,19 +336,17 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     if (late) barrier_lgkm0();
     int k = 0;  // weight stage of step s (activation stage s % 2)
     for (int s = 0; s < n_de; ++s) {
-      v8i bq[TC], av[RPW];
-      if constexpr (ACT) {
-        const uint8_t* wl = sw + k * kB2DWgt + (RPW * wr) * 2048 + (TL ? 16 * lane : 128 * li);
-        const int wc0 = TL ? 0 : xc0, wc1 = TL ? 1024 : xc1;
+      v8i bq[NT], av[RPW];
+      const uint8_t* wl = sw + k * kB2DWgt + (RPW * wr) * 2048 + (TL ? 16 * lane : 128 * li);
+      const int wc0 = TL ? 0 : xc0, wc1 = TL ? 1024 : xc1;
 #pragma unroll
-        for (int c = 0; c < TC; ++c) {
-          const uint8_t* p = xr + (s & 1) * kB2XSlot + c * 2048;
-          bq[c] = cat8(*reinterpret_cast<const v4i*>(p + xc0), *reinterpret_cast<const v4i*>(p + xc1));
-        }
-#pragma unroll
-        for (int t = 0; t < RPW; ++t)
-          av[t] = cat8(*reinterpret_cast<const v4i*>(wl + t * 2048 + wc0), *reinterpret_cast<const v4i*>(wl + t * 2048 + wc1));
+      for (int c = 0; c < NT; ++c) {
+        const uint8_t* p = xr + (s & 1) * kB2XSlot + c * 2048;
+        bq[c] = cat8(*reinterpret_cast<const v4i*>(p + xc0), *reinterpret_cast<const v4i*>(p + xc1));
       }
+#pragma unroll
+      for (int t = 0; t < RPW; ++t)
+        av[t] = cat8(*reinterpret_cast<const v4i*>(wl + t * 2048 + wc0), *reinterpret_cast<const v4i*>(wl + t * 2048 + wc1));
       __builtin_amdgcn_sched_barrier(0);
       // activations of step s + 1 (awaited after this step's MMAs), weights of step s + 2
       if (!late) {
@@ -351,19 +359,17 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
       }
       barrier_lgkm0();
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (ACT) {
-        __builtin_amdgcn_s_setprio(1);
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int t = 0; t < RPW; ++t)
+      for (int t = 0; t < RPW; ++t)
 #pragma unroll
-          for (int c = 0; c < TC; ++c) {
-            acc[t][c] = mma_dense(av[t], bq[c], acc[t][c], Dt());
-            if constexpr (!TL)
-              acc[t][c] = mma_dense(__builtin_shufflevector(av[t], av[t], 4, 5, 6, 7, 4, 5, 6, 7),
-                                    __builtin_shufflevector(bq[c], bq[c], 4, 5, 6, 7, 4, 5, 6, 7), acc[t][c], Dt());
-          }
-        __builtin_amdgcn_s_setprio(0);
-      }
+        for (int c = 0; c < NT; ++c) {
+          acc[t][c] = mma_dense(av[t], bq[c], acc[t][c], Dt());
+          if constexpr (!TL)
+            acc[t][c] = mma_dense(__builtin_shufflevector(av[t], av[t], 4, 5, 6, 7, 4, 5, 6, 7),
+                                  __builtin_shufflevector(bq[c], bq[c], 4, 5, 6, 7, 4, 5, 6, 7), acc[t][c], Dt());
+        }
+      __builtin_amdgcn_s_setprio(0);
       __builtin_amdgcn_sched_barrier(0);
       if (!late) wait_vm<0>();
       barrier_lgkm0();
@@ -373,33 +379,24 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     xdl_fence();
   };
 
-  auto run = [&](auto act_const) __attribute__((always_inline)) {
-    if (n_sp > 0) run_sparse(act_const);
-    if (n_de > 0) run_dense(act_const);
-  };
+  if (n_sp > 0) run_sparse();
+  if (n_de > 0) run_dense();
   // bf16 output with 16-byte aligned rows leaves through LDS as whole token rows
-  // (out_tile_write); the waves of token quarters past the tile's tokens (2 and 3 of a 256
-  // x 128 tile, 3 of a 256 x 192 one) then only help with the stores
-  const bool idle = wc * (kB2Tokens / 4) >= ntok;
+  // (out_tile_write)
   const bool via_lds = !GL && !a.out_f32 && ((uintptr_t)MD.Y % 16 == 0) && (MD.ldy % 8 == 0) && (rblk % 8 == 0);
-  if (idle) {
-    run(std::false_type());
-    if (!via_lds) return;
-  } else {
-    run(std::true_type());
-  }
-  if constexpr (GL) {  // no wave gets here without tokens
+  const int mw = m0 + 16 * NT * wc + li;
+  if constexpr (GL) {
     const float* const sg = a.mat[0].sw;
     const float* const su = a.mat[1].sw;
-    const int nw = rblk + 64 * wr + 4 * lq, mw = m0 + 16 * TC * wc + li;
-    EpiScales<RPW / 2, TC> eg;
+    const int nw = rblk + 64 * wr + 4 * lq;
+    EpiScales<RPW / 2, NT> eg;
     EpiScales<RPW / 2, 1> eu;
     epi_scales(eg, sg, a.sx, a.M, nw, mw, rowend);
     epi_scales(eu, su, nullptr, a.M, nw, mw, rowend);
     // the row block's number over both regions: its two slots of the row maxima
     const int slot = 2 * (R.wg0 / a.tblocks + rb) + wr;
 #pragma unroll
-    for (int c = 0; c < TC; ++c) {
+    for (int c = 0; c < NT; ++c) {
       const int m = mw + 16 * c;
       float tmax = 0.0f;
 #pragma unroll
@@ -424,23 +421,36 @@ __global__ __launch_bounds__(512) void spense_gemm_big2_kernel(GemmArgs a) {
     }
     return;
   }
-  EpiScales<RPW, TC> es;
-  if (!idle) epi_scales(es, MD.sw, a.sx, a.M, rblk + 16 * RPW * wr + 4 * lq, m0 + 16 * TC * wc + li, rowend);
+  EpiScales<RPW, NT> es;
+  epi_scales(es, MD.sw, a.sx, a.M, rblk + 16 * RPW * wr + 4 * lq, mw, rowend);
   if (!via_lds) {
+    void* Y = MD.Y;
+    int64_t ldy = MD.ldy;
+    int vec_store = MD.vec_store;
+    keep_scalar(Y);
+    keep_scalar(ldy);
+    keep_scalar(vec_store);
 #pragma unroll
     for (int t = 0; t < RPW; ++t)
 #pragma unroll
-      for (int c = 0; c < TC; ++c) {
-        const int m = m0 + 16 * (TC * wc + c) + li;
+      for (int c = 0; c < NT; ++c) {
+        const int m = mw + 16 * c;
         const int n0 = rblk + 16 * (RPW * wr + t) + 4 * lq;
-        if (m < a.M && n0 < rowend) store4e(MD.Y, MD.ldy, MD.sw != nullptr, MD.vec_store, a, es, t, c, acc[t][c], m, n0, rowend);
+        if (m < a.M && n0 < rowend) store4e(Y, ldy, MD.sw != nullptr, vec_store, a, es, t, c, acc[t][c], m, n0, rowend);
       }
     return;
   }
   barrier_vm_lgkm0<0>();  // every wave's last operand reads and copies are done
-  if (!idle) out_tile_write<RPW, TC, kB2Rows / 8>(big_lds, acc, es, MD.sw != nullptr, wr, wc, li, lq);
+  out_tile_write<RPW, NT, kB2Rows / 8>(big_lds, acc, es, MD.sw != nullptr, wr, wc, li, lq);
   barrier_vm_lgkm0<0>();
   out_tile_store<kB2Rows / 8, 512>(big_lds, ntok, m0, a.M, rblk, rowend, MD.Y, MD.ldy);
+  };
+  if (ntok > 192)
+    tile(std::integral_constant<int, 4>());
+  else if (ntok > 128)
+    tile(std::integral_constant<int, 3>());
+  else
+    tile(std::integral_constant<int, 2>());
 }
 
 }  // namespace

@@ -575,6 +575,10 @@ def test_rows_random_shapes_exact(S, i, axis, N, K, db, M, ks):
 # db), ragged N, the last block partly filled; bf16 through LDS (leading dimension N + 8)
 # and quad by quad (N + 3), and fp32.
 TILE192_CASES = [(0, 257, 700, 512, 300), (1, 300, 520, 768, 256), (0, 384, 1100, 384, 1000), (1, 560, 640, 640, 320)]
+# a tile's waves share the tokens that it has, 32, 48 or 64 each: either side of 128 and 192 tokens
+# in a first and in a last block, 2:4 and dense steps of every count up to the pipelines' depth
+TILE192_CASES += [(0, 128, 300, 160, 100), (1, 129, 270, 288, 256), (0, 192, 300, 32, 140), (1, 193, 270, 672, 160),
+                  (0, 640, 300, 544, 300), (1, 641, 270, 1312, 640), (0, 704, 300, 416, 0), (1, 705, 270, 416, 128)]
 
 
 @pytest.mark.parametrize("axis,M,N,K,db", TILE192_CASES)
@@ -660,7 +664,7 @@ BIG2_HALF_CASES = [(0, 700, 784, 640, 528, 1), (0, 700, 784, 640, 528, 3), (1, 3
 
 @pytest.mark.parametrize("axis,M,N,K,db,rh", BIG2_HALF_CASES)
 def test_large_m_half_tiles_exact(S, axis, M, N, K, db, rh):
-    """256 x 128 tail tiles (the waves of the missing token quarters only copy): bit-exact
+    """256 x 128 tail tiles: bit-exact
     against the oracle on exact-integer data, and equal to the plan without them."""
     W, mask, X, sw, sx = gen.make_exact_int(17, M + N + rh, M, N, K, gaxis(axis), db, gen.FP8)
     pw, (v, m, d) = compress_both(S, W, mask, FP8, axis, db)

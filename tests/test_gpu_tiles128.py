@@ -35,7 +35,7 @@ CASES += [(1, 513, 5000, 4128, 2080, gen.BF16), (0, 513, 9001, 4096, 6001, gen.B
 # bf16 on the 256 x 256 kernel: ragged rows and tokens, a boundary and K inside a step, all-2:4,
 # all-dense, a row boundary off multiples of 16
 CASES256 = [(0, 1030, 9000, 2080, 6001, gen.BF16), (1, 1300, 7003, 2112, 1056, gen.BF16),
-            (1, 1100, 8200, 2080, 2080, gen.BF16), (0, 2049, 5000, 2048, 0, gen.BF16)]
+            (1, 1100, 8200, 2080, 2080, gen.BF16), (0, 2049, 5000, 2048, 0, gen.BF16), (0, 1200, 9000, 2080, 6001, gen.BF16)]
 
 
 @pytest.mark.parametrize("axis,M,N,K,db,dtype", CASES + CASES256)
