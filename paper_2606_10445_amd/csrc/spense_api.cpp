@@ -587,31 +587,49 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   if (ov.kernel == 3) big = 1;  // fp8 (checked by read_override)
   if (ov.kernel == 4) big = tiled ? 2 : 1;  // the 256 x 256 kernel reads the tiled layout
   // 128 x 128 tiles (spense_gemm_mid_kernel, tiled fp8), one round of workgroups: about 8 us
-  // + 0.43 us per 128 columns (measured from K = 2048 to 25600 and 1024 to 12288 rows).
-  // Without K slices it wins where the weight and M give 144 to 256 tiles (176 at two token
-  // blocks, 112 above 1536 tokens), measured (us, before -> this kernel): 8192 x 5120 at M =
-  // 288 / 352 / 448 / 512 (192, 192, 256, 256 tiles) 31 / 31 / 37 / 40 -> 28 / 28 / 27 / 29,
-  // at M = 160 / 224 (128) 22 / 26 against 27 / 27; 5120 x 8192 at M = 352 (120) 29 against
-  // 34, 448 / 640 / 768 (160-240) 37 / 46 / 45 -> 34 / 35 / 38; 12288 x 4096 at M = 200 (192)
-  // 26 -> 22; 10240 x 5120 at M = 224 (160, two blocks) 27 against 28, 288 (240) 33 -> 29;
-  // 3072 x 3072 at M = 400 (96) 14 against 17, 800 (168) 24 -> 17; 1024 x 5120 at M = 1536 /
-  // 2048 (96, 128) 22 against 29 and 35 -> 29; a second round always loses (8192 x 5120 at
-  // M = 640, 320 tiles: 38 against 48).  With fewer tiles and a long K (28 chunks of 512) it
-  // runs in K slices, the number that a model of the slices' steps and the partial sums'
-  // round trip (3 us + 0.65 us per MB) makes cheapest: 5120 x 25600 at M = 80 / 128 / 224 /
-  // 288 36 / 39 / 57 / 75 -> 30 / 35 / 49 / 64; 4096 x 14336 at M = 100 / 200 26 / 32 -> 24 /
-  // 28.  Not at 129-192 tokens (5120 x 25600 at M = 160: 51 against 52) nor on shorter K (5120
-  // x 8192 at M = 128 / 256: 20 / 24 against 23 / 27).  The partial
-  // sums never need more than spense_gemm_noalloc's scratch.
+  // + 0.43 us per 128 2:4 columns, 0.6 per 128 dense ones (measured from K = 2048 to 25600 and
+  // 1024 to 12288 rows).  Without K slices it wins where the weight and M give 144 to 256
+  // tiles, measured (us, before -> this kernel): 8192 x 5120 at M = 288 / 352 / 448 / 512 (192,
+  // 192, 256, 256 tiles) 31 / 31 / 37 / 40 -> 28 / 28 / 27 / 29; 5120 x 8192 at M = 352 (120) 29
+  // against 34, 448 / 640 / 768 (160-240) 37 / 46 / 45 -> 34 / 35 / 38; 3072 x 3072 at M = 400
+  // (96) 14 against 17, 800 (168) 24 -> 17; a second round always loses (8192 x 5120 at M = 640,
+  // 320 tiles: 38 against 48).  The line moves (all of this on about 400 geometries of both
+  // splits, 0-100% dense):
+  //  - two token blocks: 176 tiles (8192 x 5120 at M = 160 / 224, 128 tiles, 22 / 26 against 27 /
+  //    27; 12288 x 4096 at M = 200, 192 tiles, 26 -> 22), and up to 192 tokens, where the second
+  //    block is mostly empty, 208 from K = 6400 (12864 x 8704 at M = 135, 204 tiles, 42 against
+  //    48, 12800 x 10560 at 172, 200, 59 against 63; 15232 x 9216 at 129, 238, 54 -> 45);
+  //  - three token blocks up to 320 tokens: 152 (6060 x 7744 at M = 258, 144 tiles, 28 against 36,
+  //    6080 x 8704 at 293, 144, 30 against 34; 6656 x 3328 at 257, 156, 25 -> 17) and on K from
+  //    12288 not above 199 (8869 x 14880 at M = 262, 210, 76 against 87);
+  //  - four token blocks, K from 9600: 184 (4800 x 17984 at M = 385, 152 tiles, 75 against 87, 5504
+  //    x 25504 half dense at 407, 176, 108 against 132; 5760 x 19968 at 390, 184, 97 -> 90);
+  //  - above 1536 tokens 128 (1024 x 5120 at M = 2048, 128 tiles, 35 -> 29; 832 x 10240 at 2040,
+  //    112, 38 against 45, 1024 x 25184 at 1728, 112, 88 against 115).
+  // With fewer tiles and a long K (28 chunks of 512) it runs in K slices, the number that a model
+  // of the slices' steps and the partial sums' round trip (3 us + 0.65 us per MB) makes cheapest:
+  // 5120 x 25600 at M = 80 / 128 / 224 / 288 36 / 39 / 57 / 75 -> 30 / 35 / 49 / 64; 4096 x 14336
+  // at M = 100 / 200 26 / 32 -> 24 / 28.  Not at 129-192 tokens (5120 x 25600 at M = 160: 51
+  // against 52), nor from 97 to 128 where N is no multiple of 4 and the partial sums leave one
+  // by one (5534 x 15264 at M = 127 34 against 38), nor on shorter K (5120 x 8192 at M = 128 /
+  // 256: 20 / 24 against 23 / 27).  The partial sums never need more than spense_gemm_noalloc's
+  // scratch.
   int mid_ks = 0;  // K slices of the 128 x 128 kernel, 0: not used
   if (ov.kernel == 0 && !ov.rt && !ov.waves && !ov.ct && ov.ksplit <= 1 && !ov.wused && !ov.wused_d && !ov.wused_s &&
       !ov.u8 && !ov.xres && tiled && dtype == SPENSE_FP8_E4M3FN && M > 64) {
     const int64_t rb = split == SPENSE_SPLIT_OUTPUT ? ceil_div(dense_begin, 128) + ceil_div(N - dense_begin, 128)
                                                     : ceil_div(N, 128);
     const int64_t tb = ceil_div(M, 128), wgs = rb * tb, steps = ceil_div(K, 128);
-    if (tb >= 2 && K >= 2048 && wgs <= kCUs && wgs >= (tb == 2 ? 176 : (M > 1536 ? 112 : 144))) {
+    const int64_t least = tb == 2 ? (M <= 192 && K >= 6400 ? 208 : 176)
+                          : tb == 3 && M <= 320 ? 152
+                          : tb == 4 && K >= 9600 ? 184
+                          : M > 1536 ? 128
+                                     : 144;
+    const int64_t most = tb == 3 && M <= 320 && K >= 12288 ? 199 : kCUs;
+    if (tb >= 2 && K >= 2048 && wgs >= least && wgs <= most) {
       mid_ks = 1;
-    } else if (ov.ksplit < 1 && !ov.no_mid_slices && wgs >= 16 && wgs < 144 && ceil_div(K, 512) >= 28 && M <= 320 && (M <= 128 || M > 192)) {
+    } else if (ov.ksplit < 1 && !ov.no_mid_slices && wgs >= 16 && wgs < 144 && ceil_div(K, 512) >= 28 && M <= 320 &&
+               (M <= 96 || M > 192 || (M <= 128 && N % 4 == 0))) {
       double best = 0;
       for (int64_t S = 2; S <= 8 && S * wgs <= kCUs; ++S) {
         const double bytes = 4.0 * (double)S * (double)M * (double)N;

@@ -23,8 +23,8 @@ def S():
 # columns, partial last steps of both kinds, all-2:4 and all-dense; then K slices (fewer
 # tiles, K from 28 chunks of 512), which may end on either side of the boundary.
 CASES = [(1, 257, 6500, 2080, 1056), (0, 385, 5000, 2048, 3000), (1, 513, 4608, 2048, 2048), (0, 300, 6528, 2048, 0),
-         (1, 640, 5120, 2112, 32), (0, 256, 11300, 2048, 8432), (1, 1537, 1100, 2304, 1728),
-         (1, 100, 2410, 14368, 10016), (1, 250, 1100, 14336, 14336), (0, 70, 2304, 14336, 1200), (1, 128, 2435, 15000, 96)]
+         (1, 640, 5120, 2112, 32), (0, 256, 11300, 2048, 8432), (1, 1537, 1250, 2304, 1728),
+         (1, 100, 2412, 14368, 10016), (1, 250, 1100, 14336, 14336), (0, 70, 2304, 14336, 1200), (1, 90, 2435, 15000, 96)]
 CASES = [(a, M, N, K // 32 * 32, db, gen.FP8) for a, M, N, K, db in CASES]
 # K slices and a dense region that starts off multiples of 4 (its partial sums are not in whole quads)
 CASES += [(0, 70, 2304, 14336, 1202, gen.FP8)]
