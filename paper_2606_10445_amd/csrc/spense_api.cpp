@@ -685,8 +685,6 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   }
   const bool mid = mid_ks > 0;
   if (mid) {
-    // the two-half kernel's place (128 tokens a block there too), or the large-M kernels'
-    pl->ls.halves = rows2 || mid_ks > 1;
     rows2 = false;
     big = 3;
   }
@@ -874,9 +872,7 @@ __attribute__((constructor)) void read_log_env() {
 
 const char* kernel_name(const spense::LaunchShape& ls) {
   if (ls.big == 2) return ls.glu ? "large-M 256x256, gate/up paired" : "large-M 256x256";
-  // the 128 x 128 kernel in the two-half kernel's place keeps that rule's name, which callers
-  // read the log for; tile=128x128 at the end of the line tells them apart
-  if (ls.big == 3) return ls.halves ? "row-split, two 64-token halves" : "large-M 128x128";
+  if (ls.big == 3) return "large-M 128x128";
   if (ls.big == 1) return "large-M 128x256";
   if (ls.glu) return "row-split, gate/up paired";
   if (ls.rows == 2) return "row-split, two 64-token halves";
@@ -888,13 +884,13 @@ void log_plan(const char* what, int32_t dtype, int64_t M, int64_t N, int32_t spl
   fprintf(stderr,
           "spense: %s dtype=%s M=%lld N=%lld K=%lld split=%s dense_begin=%lld layout=%s -> %s act_tiles=%d "
           "row_tiles=%d waves=%d token_blocks=%d block_tokens=%d workgroups=%d regions=%d k_slices=%d "
-          "resident_x=%d half_tile_groups=%d workspace=%zu%s\n",
+          "resident_x=%d half_tile_groups=%d workspace=%zu\n",
           what, dtype == SPENSE_FP8_E4M3FN ? "fp8" : "bf16", (long long)M, (long long)N, (long long)K,
           split == SPENSE_SPLIT_OUTPUT ? "output" : "input", (long long)dense_begin, tiled ? "tiled" : "row-major",
           kernel_name(ls), ls.ct, ls.rt, ls.waves, ls.big ? a.tblocks : ls.mblocks,
           ls.big == 2 ? (a.btok > 0 ? a.btok : 256) : (ls.big == 3 ? 128 : ls.big ? 256 : (ls.rows == 2 ? 128 : 16 * ls.ct)), a.groups,
           a.nreg, a.nreg > 0 ? a.reg[0].ksplit : 1,
-          ls.xres, ls.big == 2 ? a.groups - a.hg0 : 0, ws_bytes, ls.big == 3 ? " tile=128x128" : "");
+          ls.xres, ls.big == 2 ? a.groups - a.hg0 : 0, ws_bytes);
 }
 
 const Plan& cached_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, int64_t dense_begin, bool tiled,

@@ -106,9 +106,8 @@ struct LaunchShape {
   int mblocks;  // grid.y
   int u8;       // eight instruction steps per batch of loads (single activation tile only)
   int rows;     // row-split workgroups with activations staged in LDS
-  int big;      // large-M kernels (fp8): 1 = 128-row x 256-token workgroup tiles, 2 = 256 x 256,
-                // 3 = 128 x 128 (tiled weights, K slices)
-  int halves;   // big == 3 where the two-half row-split kernel would otherwise run (the log's name for it)
+  int big;      // large-M kernels: 1 = 128-row x 256-token workgroup tiles (fp8), 2 = 256 x 256, 3 = 128 x
+                // 128 (optional K slices); 2 and 3 tiled fp8 or row-major bf16
   int glu;      // gate and up paired; row-split kernel: waves 0-3 gate tiles, 4-7 the same up tiles
   int xres;     // row-split kernel, one token tile: >0 = the activations of all xres chunks stay in LDS
 };

@@ -400,17 +400,18 @@ def test_k_slice_rule_on_the_layer_shapes(S):
     assert ws(5120, 25600, 1, 192) > 0 and ws(1024, 5120, 0, 192) == 0  # three: only the long K
     assert ws(1024, 5120, 0, 200) == 0  # four or more token blocks
     assert ws(5120, 25600, 1, 200) == 3 * 200 * 5120 * 4  # down from 193 tokens: 3 slices of 128 tokens
-    assert ws(5120, 25600, 1, 300) == 2 * 300 * 5120 * 4  # 257-320: two halves in 2 slices
+    assert ws(5120, 25600, 1, 300) == 2 * 300 * 5120 * 4  # 257-320: 2 slices
     assert ws(5120, 25600, 1, 350) == 0 and ws(5120, 25600, 1, 500) == 0
 
 
 def test_two_half_rule_on_the_layer_shapes(S, capfd):
-    """Where the planner runs two 64-token halves per row-split workgroup (tiled fp8, seen
-    through the dispatch log): one 128-token block on weights of at least 768 row tiles
-    (gate / up, 1600; 12288 rows), not on q (512) or at 64 tokens; two blocks where the
-    row-split kernel would take three or four (q from 193 tokens, 640 tiles from 129), not
-    where the large-M kernel runs (gate / up) or above 256 tokens; the row-major layout
-    never."""
+    """Where the planner runs two 64-token halves per row-split workgroup and where the 128 x
+    128 kernel (tiled fp8, seen through the dispatch log).  Two halves: one 128-token block
+    on weights of at least 768 row tiles (gate / up, 1600; 12288 rows), not on q (512) or at
+    64 tokens; two blocks where the row-split kernel would take three or four (q from 193
+    tokens, 640 tiles from 129), not where a large-M kernel runs (gate / up); the row-major
+    layout never.  128 x 128: one round of 144 to 256 tiles (two token blocks: from 176), or K
+    slices of a long K."""
     def kernel(N, K, split, M, layout=S.SPENSE_LAYOUT_TILED):
         db = N * 3 // 4 if split == 0 else K * 3 // 4
         L = S.spense_layout(N, K, 1, split, db)
@@ -419,7 +420,7 @@ def test_two_half_rule_on_the_layer_shapes(S, capfd):
         err = capfd.readouterr().err.strip().splitlines()
         assert err, (N, K, split, M)  # planned once in this test; a cached plan would log nothing
         return err[-1].split(" -> ")[1].split(" act_tiles")[0]
-    two = "row-split, two 64-token halves"
+    two, mid = "row-split, two 64-token halves", "large-M 128x128"
     prev = S.spense_set_log(1)
     try:
         # token counts other tests do not plan on these geometries (plans are cached per thread)
@@ -430,20 +431,23 @@ def test_two_half_rule_on_the_layer_shapes(S, capfd):
             assert kernel(8192, 5120, 0, M) == "row-split" and kernel(10240, 5120, 0, M) == "row-split"
         assert kernel(25600, 5120, 0, 63) == "row-split"
         assert kernel(8192, 5120, 0, 191) == "row-split" and kernel(8192, 5120, 0, 193) == two
-        assert kernel(10240, 5120, 0, 131) == two and kernel(16384, 8192, 1, 131) == two
+        assert kernel(10240, 5120, 0, 131) == two and kernel(16384, 8192, 1, 131) == mid
+        assert kernel(12864, 8704, 0, 131) == two  # 204 tiles, mostly empty second blocks
         assert kernel(25600, 5120, 0, 131).startswith("large-M") and kernel(25600, 5120, 0, 300).startswith("large-M")
-        # 257-768 tokens on 256-767 row tiles: q up to 384, o and down from 385 (and down
-        # at 257-320, in 2 slices), not the 128 x 256 kernel's q above 384
-        assert kernel(8192, 5120, 0, 257) == two and kernel(8192, 5120, 0, 383) == two
-        assert kernel(8192, 5120, 0, 449).startswith("large-M")
-        assert kernel(5120, 8192, 1, 450) == two and kernel(5120, 25600, 1, 639) == two
-        assert kernel(5120, 25600, 1, 301) == two and kernel(5120, 25600, 1, 350) == "row-split"
-        assert kernel(5120, 8192, 1, 301) == "row-split" and kernel(5120, 25600, 1, 700) == two
-        assert kernel(5120, 25600, 1, 769) != two and kernel(5120, 8192, 1, 900) != two
+        # 257-768 tokens on 256-767 row tiles: 128 x 128 tiles for q, o and down (down at
+        # 257-320 in 2 slices); two halves where those are too few (K below 2048, or 132
+        # tiles, which no two slices fit beside)
+        assert kernel(8192, 5120, 0, 257) == mid and kernel(8192, 5120, 0, 383) == mid
+        assert kernel(8192, 5120, 0, 449) == mid
+        assert kernel(5120, 8192, 1, 450) == mid and kernel(5120, 25600, 1, 639) == mid
+        assert kernel(4096, 1920, 1, 450) == two and kernel(5632, 25600, 1, 301) == two
+        assert kernel(5120, 25600, 1, 301) == mid and kernel(5120, 25600, 1, 350) == "row-split"
+        assert kernel(5120, 8192, 1, 301) == "row-split" and kernel(5120, 25600, 1, 700) == mid
+        assert kernel(5120, 25600, 1, 769) == "large-M 128x256" and kernel(5120, 8192, 1, 900) == "large-M 128x256"
         assert kernel(1024, 5120, 0, 450) != two  # k / v: 64 row tiles
         assert kernel(25600, 5120, 0, 99, layout=0) != two
         # short weights with a long K: with K slices (down 50 chunks, Seed-OSS o 20)
-        assert kernel(5120, 25600, 1, 67) == two and kernel(5120, 25600, 1, 250) == two
+        assert kernel(5120, 25600, 1, 67) == mid and kernel(5120, 25600, 1, 250) == mid
         assert kernel(5120, 25600, 1, 170) == "row-split"
         assert kernel(5120, 10240, 1, 67) == two and kernel(5120, 10240, 1, 120) == "row-split"
         assert kernel(5120, 8192, 1, 67) == "row-split"  # o, 16 chunks

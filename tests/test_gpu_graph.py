@@ -3,8 +3,8 @@ and replayed several times, with eager work and synchronisations between the rep
 give the eager results bit for bit.  Covers a K-sliced GEMM (partials in the workspace,
 then the reduction launch), the grouped launch, the paired gate / up launch with the
 row-maxima quantisation, and the whole MLP block, on the Qwen3-like shapes at M = 16,
-64 and 100 (at 100 down runs as two 64-token halves in K slices and the grouped gate /
-up as one two-half launch per weight; random data; the comparison is against the same
+64 and 100 (at 100 down runs on 128 x 128 tiles in K slices and the grouped gate / up as
+one two-half launch per weight; random data; the comparison is against the same
 calls run eagerly)."""
 import sys
 
