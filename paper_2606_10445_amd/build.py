@@ -31,10 +31,10 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-# The compiler the kernels' explicit matrix-core wait states (xdl_fence in spense_gemm.hip)
-# were checked with: the padding it inserts across basic blocks fell short there, and the
-# repeatability test over every kernel shape guards it.  A different compiler must pass
-# that test before anything else.
+# The compiler the kernels' explicit matrix-core wait states (xdl_fence in
+# spense_gemm_device.h) were checked with: the padding it inserts across basic blocks fell
+# short there, and the repeatability tests guard it (every kernel shape up to 64 tokens, the
+# large-M tiles, the paired launch).  A different compiler must pass them before anything else.
 CHECKED_TOOLCHAIN = ("HIP version: 7.2.26015-fc0010cf6a",
                      "AMD clang version 22.0.0git (https://github.com/RadeonOpenCompute/llvm-project roc-7.2.0 26014 "
                      "7b800a19466229b8479a78de19143dc33c3ab9b5)")
@@ -79,7 +79,7 @@ def build(verbose: bool = False) -> str:
     print(f"toolchain: {tc[0]}; {tc[1]}", flush=True)
     if tc != CHECKED_TOOLCHAIN:
         print("WARNING: not the compiler the matrix-core wait states were checked with; run "
-              "tests/test_gpu_parity.py::test_every_kernel_shape_is_repeatable_and_within_bound first", flush=True)
+              "tests/test_gpu_parity.py, test_gpu_tiles128.py and test_gpu_glu.py (-k repeatable) first", flush=True)
     return LIB
 
 

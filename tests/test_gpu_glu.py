@@ -257,3 +257,30 @@ def test_gemm_glu_tiles_exact(S, M, N, K, db, capfd):
     g, u = (y.cpu().numpy().astype(np.float64) for y in (G, U))
     h_ref = oracle.glu_f64(g, u)
     assert np.all(np.abs(H.cpu().numpy() - h_ref) <= glu_bound(g, u, h_ref))
+
+
+@pytest.mark.parametrize("M,N,K,db", [(300, 10203, 672, 5002), (450, 10240, 1056, 7680), (700, 9000, 288, 0)])
+def test_gemm_glu_tiles_random_repeatable(S, M, N, K, db):
+    """Random data: the pair's codes and scales are those of the grouped launch's G and U, bit for
+    bit and every time, and G and U are within the bound of their sums (2^-12 of sum |x w| for the
+    fp8 instructions' ~13 fraction bits, 2 gamma_K)."""
+    say(f"[gemm-glu tiles random] M={M} N={N} K={K} dense_begin={db}")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    draw = lambda *s: (torch.randn(s, generator=g, device="cuda") * 8).to(torch.float8_e4m3fn)  # noqa: E731
+    X, Ws = draw(M, K), [draw(N, K), draw(N, K)]
+    mask = torch.from_numpy(gen.random_mask_24(np.random.default_rng(3), N, K, gen.OUTPUT, db)).cuda()
+    pws = [S.tile(S.compress(W.view(torch.uint8), mask, 0, db)) for W in Ws]
+    sw = [torch.rand(N, generator=g, device="cuda") * 1e-3 for _ in range(2)]
+    sx = torch.rand(M, generator=g, device="cuda") + 0.5
+    Xq = X.view(torch.uint8)
+    GU = S.gemm_grouped(Xq, pws, sw, sx, out_f32=True)
+    q0, s0 = S.glu_quantize_fp8(*GU)
+    for _ in range(4):
+        q, s = S.gemm_glu_fp8(Xq, *pws, *sw, sx)
+        assert torch.equal(q, q0) and torch.equal(s, s0)
+    gamma = K * U32 / (1 - K * U32)
+    for y, W, w in zip(GU, Ws, sw):
+        Wd, scale = W.double() * mask, w.double()[None, :] * sx.double()[:, None]
+        want = (X.double() @ Wd.T) * scale
+        bound = (2.0 ** -12 + 2 * gamma) * (X.double().abs() @ Wd.abs().T) * scale + 4 * U32 * want.abs()
+        assert bool(((y.double() - want).abs() <= bound).all())
