@@ -348,7 +348,8 @@ int spense_gemm_grouped(const void* X, int64_t M, int64_t ldx, int32_t count, co
  *   same rows and pairs them on chip, so G and U are never written.  Like
  *   spense_gemm_grouped it runs the row-split kernel, which pays for up to 64 tokens, or
  *   the 256 x 256 kernel above that from 160 tiles of 128 rows x 256 tokens; between the
- *   two, two spense_gemm calls (fp32 out) and spense_glu_quantize_fp8 are faster.
+ *   two, two spense_gemm calls (fp32 out) and spense_glu_quantize_fp8 are faster
+ *   (spense_gemm_glu_pays).
  * gate, up: fp8 e4m3fn, output-split, tiled layout, with equal N, K and dense_begin.
  * X: M x K fp8 codes (ldx bytes, 16-byte aligned, ldx a multiple of 16).  w_scale_gate /
  * w_scale_up: N fp32 each or NULL; x_scale: M fp32 or NULL.  H: M x N fp32, leading
@@ -359,6 +360,11 @@ int spense_gemm_grouped(const void* X, int64_t M, int64_t ldx, int32_t count, co
 int spense_gemm_glu(const void* X, int64_t M, int64_t ldx, const spense_packed_t* gate, const spense_packed_t* up,
                     const float* w_scale_gate, const float* w_scale_up, const float* x_scale, float* H, int64_t ldh,
                     hipStream_t stream);
+
+/* 1 where spense_gemm_glu and spense_gemm_glu_fp8 are the faster way for M tokens and these
+ * weights' N and dense_begin, 0 where two GEMMs and spense_glu_quantize_fp8 are (and for sizes
+ * outside their ranges).  Host only. */
+int spense_gemm_glu_pays(int64_t M, int64_t N, int64_t dense_begin);
 
 /* Device workspace (bytes) that spense_gemm_glu_fp8 needs for M tokens and N gate / up
  * rows (0 for sizes below 1 or above 2^31-1). */

@@ -45,7 +45,7 @@ EXPORTS = ["spense_abi_version", "spense_set_log", "spense_last_error", "spense_
            "spense_quantize_fp8", "spense_glu_quantize_fp8", "spense_index_scores", "spense_dense_permutation",
            "spense_gather_rows", "spense_gather_cols", "spense_obs_factor_workspace_size", "spense_obs_factor",
            "spense_obs_prune_workspace_size", "spense_obs_prune_24", "spense_gemm_grouped", "spense_gemm_glu",
-           "spense_gemm_glu_fp8_workspace_size", "spense_gemm_glu_fp8", "spense_gemm_planned_workspace_size",
+           "spense_gemm_glu_pays", "spense_gemm_glu_fp8_workspace_size", "spense_gemm_glu_fp8", "spense_gemm_planned_workspace_size",
            "spense_gemm_planned", "spense_gemm_noalloc"]
 
 
@@ -129,6 +129,7 @@ def _load():
         "spense_obs_prune_24": (ctypes.c_int, [p, i64, i64, i64, p, i64, p, i64, p, i64, p, sz, p]),
         "spense_gemm_grouped": (ctypes.c_int, [p, i64, i64, i32, p, p, p, p, p, u32, p]),
         "spense_gemm_glu": (ctypes.c_int, [p, i64, i64, p, p, p, p, p, p, i64, p]),
+        "spense_gemm_glu_pays": (ctypes.c_int, [i64, i64, i64]),
         "spense_gemm_glu_fp8_workspace_size": (ctypes.c_size_t, [i64, i64]),
         "spense_gemm_glu_fp8": (ctypes.c_int, [p, i64, i64, p, p, p, p, p, p, i64, p, p, ctypes.c_size_t, p]),
         "spense_gemm_planned_workspace_size": (sz, [i64, P(spense_packed_t), P(spense_plan_override_t)]),
@@ -263,6 +264,10 @@ def spense_gemm_grouped(X, M, ldx, count, packed_array, w_scales_array, x_scale,
 
 def spense_gemm_glu(X, M, ldx, gate, up, w_scale_gate, w_scale_up, x_scale, H, ldh, stream) -> int:
     return _lib.spense_gemm_glu(X, M, ldx, gate, up, w_scale_gate, w_scale_up, x_scale, H, ldh, stream)
+
+
+def spense_gemm_glu_pays(M: int, N: int, dense_begin: int) -> int:
+    return _lib.spense_gemm_glu_pays(M, N, dense_begin)
 
 
 def spense_gemm_glu_fp8_workspace_size(M: int, N: int) -> int:
@@ -648,24 +653,18 @@ def mlp(X: torch.Tensor, x_scale: torch.Tensor, gate: PackedWeight, up: PackedWe
         gate_scale=None, up_scale=None, down_scale=None, out=None, workspace: Workspace | None = None):
     """The GLU MLP of the paper's sec. 3.3.1 Eq. (4) on Spense weights: H = glu(gate(X),
     up(X)) (output-split) and (Hq, sh) its per-token fp8 quantisation (for tiled fp8
-    weights of one geometry and up to 64 tokens, or enough for the 256 x 256 tiles, the GLU
-    in the gate / up epilogue, then the quantisation from the epilogue's row maxima;
-    otherwise G and U in fp32 and the GLU fused with the quantisation), Y = down(Hq) (input-split, bf16 out).  X: fp8 codes
-    with x_scale."""
-    # the paired launch runs the row-split kernel, which pays for one block of up to 64
-    # tokens, or the 256 x 256 kernel where its grid fills the GPU (160 tiles of 128 rows of
-    # both weights; the library's own rule); in between the grouped call (a plan per
-    # weight) gives G and U
+    weights of one geometry, where spense_gemm_glu_pays says so, the GLU in the gate / up
+    epilogue, then the quantisation from the epilogue's row maxima; otherwise G and U in
+    fp32 and the GLU fused with the quantisation), Y = down(Hq) (input-split, bf16 out).
+    X: fp8 codes with x_scale."""
+    # where the paired launch does not pay the grouped call (a plan per weight) gives G and U
     groupable = (gate.kind == up.kind == SPENSE_LAYOUT_TILED and gate.dtype == up.dtype == SPENSE_FP8_E4M3FN
                  and gate.split == up.split == SPENSE_SPLIT_OUTPUT)
     M = X.shape[0]
-    blocks = -(-gate.dense_begin // 128) - (-(gate.N - gate.dense_begin) // 128)
-    tiles = groupable and 64 < M <= 65536 and blocks * -(-M // 256) >= 160 and gate.N >= 512 and gate.K > 0
-    if ((groupable and M <= 64 or tiles) and gate.N == up.N and gate.K == up.K
-            and gate.dense_begin == up.dense_begin):
-        Hq, sh = gemm_glu_fp8(X, gate, up, gate_scale, up_scale, x_scale,
-                              # above 64 tokens H is as large as G was: not kept in the workspace
-                              workspace=None if tiles else workspace)
+    if (groupable and gate.N == up.N and gate.K == up.K and gate.dense_begin == up.dense_begin
+            and (M <= 64 or gate.K > 0 and spense_gemm_glu_pays(M, gate.N, gate.dense_begin))):
+        # above 64 tokens H is as large as G was: not kept in the workspace
+        Hq, sh = gemm_glu_fp8(X, gate, up, gate_scale, up_scale, x_scale, workspace=workspace if M <= 64 else None)
     else:
         if groupable and gate.K == up.K:
             scales = None if gate_scale is None and up_scale is None else [gate_scale, up_scale]

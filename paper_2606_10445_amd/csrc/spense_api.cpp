@@ -1031,6 +1031,16 @@ int check_glu_pair(const void* X, int64_t M, int64_t ldx, const spense_packed_t*
   return SPENSE_OK;
 }
 
+// The paired gate / up launch for many tokens: the 256 x 256 kernel, 128 rows of both weights a
+// tile, where those fill the GPU (grouped G and U on the grouped launch's rule are slower there:
+// the layer of a 25600 x 5120 MLP at M = 2048 1004 -> 855 us, the MLP at M = 256 155 -> 126); the
+// maxima need two slots per row block, which a weight of very few rows has no room for.
+int64_t glu_row_blocks(int64_t N, int64_t db) { return ceil_div(db, 128) + ceil_div(N - db, 128); }
+bool glu_on_tiles(int64_t M, int64_t N, int64_t db) {
+  const int64_t blocks = glu_row_blocks(N, db), tiles = blocks * ceil_div(M, 256);
+  return M >= kBigMinM && tiles >= 160 && tiles < (1 << 22) && 2 * blocks <= ceil_div(N, 16) + 1;
+}
+
 // The paired gate / up launch (arguments checked, M, N > 0): H (fp32, ldh) and, when hmax
 // is given, the per-workgroup maxima of |h| per token, hmax[m * groups + g]; *groups_out
 // receives the number of maxima per token (workgroups along N, two each on the 256 x 256
@@ -1081,14 +1091,8 @@ int launch_glu_pair(const void* X, int64_t M, int64_t ldx, const spense_packed_t
     kind[i] = regs[i].kbound == 0 ? 0 : 1;
     tile[i] = regs[i].kbound == 0 ? tile_d : tile_s;
   }
-  // Many tokens: the 256 x 256 kernel, 128 rows of both weights a tile, on the grouped
-  // launch's rule (which its callers would otherwise use for G and U); the maxima need two
-  // slots per row block, which a weight of very few rows has no room for.
-  const int64_t T256 = ceil_div(M, 256);
-  int64_t blocks = 0;
-  for (int i = 0; i < nreg; ++i) blocks += ceil_div(regs[i].rows, 128);
-  const bool big2 = M >= kBigMinM && blocks * T256 >= 160 && blocks * T256 < (1 << 22) &&
-                    2 * blocks <= ceil_div(N, 16) + 1;
+  const int64_t T256 = ceil_div(M, 256), blocks = glu_row_blocks(N, db);
+  const bool big2 = glu_on_tiles(M, N, db);
   int32_t groups = 0, slots = 0;
   if (big2) {
     ls.rows = 0;
@@ -1695,6 +1699,12 @@ int spense_gemm_glu(const void* X, int64_t M, int64_t ldx, const spense_packed_t
   int32_t groups = 0;
   rc = launch_glu_pair(X, M, ldx, gate, up, w_scale_gate, w_scale_up, x_scale, H, ldh, nullptr, &groups, stream);
   return rc ? rc : ok();
+}
+
+int spense_gemm_glu_pays(int64_t M, int64_t N, int64_t dense_begin) {
+  if (M < 1 || N < 1 || N > INT32_MAX || dense_begin < 0 || dense_begin > N) return 0;
+  // up to 65536 tokens H's quantisation grid (M x ceil(N / 2048)) fits for any N
+  return M < kBigMinM || (M <= 65536 && glu_on_tiles(M, N, dense_begin)) ? 1 : 0;
 }
 
 size_t spense_gemm_glu_fp8_workspace_size(int64_t M, int64_t N) {

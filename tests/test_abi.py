@@ -351,6 +351,18 @@ def test_gemm_glu_validates_arguments_on_the_host(S):
     assert f(X, 0, 256, ref(g), ref(g), None, None, None, H, 64, None) == S.SPENSE_OK  # M = 0
 
 
+def test_gemm_glu_pays_on_the_host(S):
+    """Up to 64 tokens, then from 160 tiles of 128 rows (of each region) x 256 tokens."""
+    f = S.spense_gemm_glu_pays
+    assert f(1, 64, 48) == f(64, 25600, 19200) == 1
+    assert f(65, 25600, 19200) == f(256, 25600, 19200) == 1  # 200 tiles
+    assert f(256, 20480, 15360) == 1 and f(256, 20352, 15360) == 0  # 160, 159
+    assert f(256, 20352, 15361) == 1  # 121 + 39 + 1 row blocks
+    assert f(65, 8192, 6144) == 0 and f(513, 8192, 6144) == 1 and f(512, 8192, 6144) == 0
+    assert f(65536, 25600, 0) == 1 and f(65537, 25600, 0) == 0
+    assert f(0, 64, 0) == f(8, 0, 0) == f(8, 64, 65) == f(8, 64, -1) == 0
+
+
 def test_gemm_glu_fp8_validates_arguments_on_the_host(S):
     """Error paths of spense_gemm_glu_fp8 and its workspace size, before the device."""
     import ctypes
