@@ -254,14 +254,16 @@ int64_t xcd_token_group(int64_t T) {
 
 // 256 x 256 kernel: the row blocks at the end of the last region that run as 256 x 128
 // tiles after every full tile.  Where the full tiles end in a nearly empty round of the 256
-// CUs, smaller tiles dispatched last fill it.  Measured (us, no half tiles / these / half
-// tiles also where the last round is a quarter full or more): 21632 x 4864 M = 562 (258
-// full tiles) 78 / 76, 11264 x 9728 M = 1283 (264) 147 / 140, gate / up M = 640 (300) 88 /
-// 86 and M = 2048 (800) 193 / 191, 9984 x 640 M = 2001 (312) 38.6 / 35.3; 22528 x 5120 M =
-// 768 (330) 94 / - / 96, 22912 x 3072 M = 1246 (450) 75 / - / 98, 20480 x 4096 M = 1536
-// (480) 89 / - / 110: there the half tiles start a round of their own.  As many as are worth
+// CUs, smaller tiles dispatched last fill it; never so many that they need a round of their
+// own.  Measured (us, no half tiles / these): 21632 x 4864 M = 562 (258 full tiles) 78 / 76,
+// 11264 x 9728 M = 1283 (264) 147 / 140, gate / up M = 640 (300) 88 / 86 and M = 2048 (800)
+// 193 / 191, 9984 x 640 M = 2001 (312) 38.6 / 35.3; a round of their own: 22912 x 3072 M =
+// 1246 (450) 75 against 98, 20480 x 4096 M = 1536 (480) 89 against 110.  As many as are worth
 // about an eighth of the work (a dense step costing 1.28 2:4 steps, a half tile 0.6 of a full
-// one), rounded up to whole XCD row classes; one row block where less than one is over.
+// one), rounded up to whole XCD row classes; one row block where less than one is over.  From
+// a quarter of a round on, eight 2:4 row blocks: 51200 x 5120 M = 512 (400) 109 / 103, gate /
+// up M = 1024 (400) 105 / 102, 36864 x 5120 M = 768 (432) 105 / 104, 38400 x 5120 M = 1024 (600)
+// 144 / 145 (dense ones lose: 16384 x 5120 M = 1400, 384, 114 against 117).
 int64_t choose_half_rows(const spense::Region* regs, int nreg, int64_t T, int64_t M, int64_t rc) {
   double W = 0;
   int64_t rbtot = 0;
@@ -276,11 +278,18 @@ int64_t choose_half_rows(const spense::Region* regs, int nreg, int64_t T, int64_
     rbl = rb;
   }
   const int64_t over = rbtot * T % kCUs;  // full tiles of the last round
-  if (rbtot * T <= kCUs || wl <= 0 || over == 0 || over >= kCUs / 4) return 0;
+  if (rbtot * T <= kCUs || wl <= 0 || over == 0) return 0;
   if (over < T) return 1;
-  const double per_rb = (double)ceil_div(M, 128) * 0.6 * wl;
-  int64_t rh = (int64_t)std::ceil(W / 8.0 / per_rb);
-  if (rc > 1) rh = ceil_div(rh, rc) * rc;
+  const int64_t per = ceil_div(M, 128);  // half tiles of a row block
+  const int64_t fit = per > T ? (kCUs - over) / (per - T) : rbl;
+  int64_t rh;
+  if (over >= kCUs / 4) {
+    rh = regs[nreg - 1].kbound > 0 && fit >= 8 ? 8 : 0;
+  } else {
+    rh = (int64_t)std::ceil(W / 8.0 / ((double)per * 0.6 * wl));
+    if (rc > 1) rh = ceil_div(rh, rc) * rc;
+    rh = std::min(rh, fit);
+  }
   return std::min(rh, rbl);
 }
 
