@@ -518,16 +518,16 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   // 256 grid ends in 256 x 128 tiles, the 256 x 256 kernel wins there too (gate / up at
   // M = 257 / 300 / 513 / 576 / 700: 65.8 / 66.7 / 82.9 / 84.4 / 87.0 against 68.2 / 67.9
   // / 100.3 / 102.8 / 108.8 us; Seed-OSS gate alike).
+  // With the step pipelines of now it also wins below that where the 128 x 256 grid needs a
+  // second round: 5120 x 8192 at M = 1700 (280 tiles, 140 of 256 rows) 101 -> 71; in one round
+  // that grid stays ahead (8192 x 5120 at M = 1024, 256 tiles, 44 against 51; 10752 x 2816 at M =
+  // 690, 252, 26.5 against 34; 5120 x 25600 at M = 1300, 240, 158 against 178).
   if (big && tiled) {
-    const int64_t rb256 = split == SPENSE_SPLIT_OUTPUT
-                              ? ceil_div(dense_begin, 256) + ceil_div(N - dense_begin, 256)
-                              : ceil_div(N, 256);
+    auto row_blocks = [&](int64_t h) {
+      return split == SPENSE_SPLIT_OUTPUT ? ceil_div(dense_begin, h) + ceil_div(N - dense_begin, h) : ceil_div(N, h);
+    };
     const int64_t tb256 = ceil_div(M, 256);
-    // With the step pipelines of now the line is where the 128 x 256 grid needs a second
-    // round: 5120 x 8192 at M = 1700 (140 tiles) 101 -> 71; at 128 and 120 tiles that grid
-    // stays ahead (8192 x 5120 at M = 1024 44 against 51, 5120 x 25600 at M = 1300 158
-    // against 178).
-    if (rb256 * tb256 > 128) big = 2;
+    if (row_blocks(256) * tb256 >= 160 || row_blocks(128) * tb256 > kCUs) big = 2;
   }
   // Two 64-token halves per row-split workgroup (spense_gemm_rows2_kernel: 128 tokens a
   // block, four token tiles, one row tile, eight waves).  Each weight chunk
