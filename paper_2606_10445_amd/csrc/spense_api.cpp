@@ -611,8 +611,9 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   //  - three token blocks up to 320 tokens: 152 (6060 x 7744 at M = 258, 144 tiles, 28 against 36,
   //    6080 x 8704 at 293, 144, 30 against 34; 6656 x 3328 at 257, 156, 25 -> 17) and on K from
   //    12288 not above 199 (8869 x 14880 at M = 262, 210, 76 against 87);
-  //  - four token blocks, K from 9600: 184 (4800 x 17984 at M = 385, 152 tiles, 75 against 87, 5504
-  //    x 25504 half dense at 407, 176, 108 against 132; 5760 x 19968 at 390, 184, 97 -> 90);
+  //  - four token blocks, K from 9600: 160 (4800 x 17984 at M = 385, 152 tiles, 75 against 87; 5120
+  //    x 25600 at 385 / 512, 160, 100 / 102 -> 94 / 92), half dense or more 184 (5504 x 25504 at 407,
+  //    176, 108 against 132, 4992 x 13280 all dense at 502, 156, 68 against 74);
   //  - above 1536 tokens 128 (1024 x 5120 at M = 2048, 128 tiles, 35 -> 29; 832 x 10240 at 2040,
   //    112, 38 against 45, 1024 x 25184 at 1728, 112, 88 against 115).
   // With fewer tiles and a long K (28 chunks of 512) it runs in K slices, the number that a model
@@ -629,9 +630,10 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
     const int64_t rb = split == SPENSE_SPLIT_OUTPUT ? ceil_div(dense_begin, 128) + ceil_div(N - dense_begin, 128)
                                                     : ceil_div(N, 128);
     const int64_t tb = ceil_div(M, 128), wgs = rb * tb, steps = ceil_div(K, 128);
+    const bool half_dense = 2 * dense_begin <= (split == SPENSE_SPLIT_OUTPUT ? N : K);
     const int64_t least = tb == 2 ? (M <= 192 && K >= 6400 ? 208 : 176)
                           : tb == 3 && M <= 320 ? 152
-                          : tb == 4 && K >= 9600 ? 184
+                          : tb == 4 && K >= 9600 ? (half_dense ? 184 : 160)
                           : M > 1536 ? 128
                                      : 144;
     const int64_t most = tb == 3 && M <= 320 && K >= 12288 ? 199 : kCUs;
