@@ -38,7 +38,7 @@ M_MAIN = 64
 MALL_BYTES = 256 << 20
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_spense_gemm_gate_up_m64.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2606_10445_amd", "csrc", f) for f in
-                  ("spense_gemm.hip", "spense_api.cpp", "spense_internal.h")]
+                  ("spense_gemm.hip", "spense_gemm_device.h", "spense_api.cpp", "spense_internal.h")]
 
 
 def log(*a):

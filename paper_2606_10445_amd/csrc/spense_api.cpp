@@ -167,7 +167,7 @@ int check_packed(const spense_packed_t* P, spense_layout_t* L) {
 struct Plan {
   spense::LaunchShape ls;
   spense::GemmArgs args;  // geometry part filled
-  size_t ws_bytes;        // device workspace needed (none at present)
+  size_t ws_bytes;        // device workspace: the partial sums of K slices
 };
 
 // Parts of the plan a caller forced (spense_gemm_planned); the defaults leave every
@@ -508,8 +508,8 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
              !(tiles128 < 160 && ceil_div(M, 64) <= 5))
                 ? 1
                 : 0;
-  // 256-row x 256-token tiles (tiled weights) once that grid has at least 160 workgroups:
-  // measured on MI355X (us, 128 x 256 tiles -> 256 x 256): gate / up at M = 1024 / 2048
+  // 256-row x 256-token tiles (tiled weights) once that grid has at least 160 workgroups, with
+  // the kernel's first version (us, 128 x 256 tiles -> 256 x 256): gate / up at M = 1024 / 2048
   // 177 / 312 -> 159 / 291, Seed-OSS gate 178 / 316 -> 168 / 290, down and o at M = 2048
   // (160 workgroups) 313 -> 267 and 120 -> 100, q at M = 2048 95 -> 91; with fewer
   // workgroups it loses (q at M = 1024, 128 workgroups: 49 -> 84; down at M = 1024, 80: 159
@@ -660,7 +660,7 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
   // round, in slices 3 + 0.65 per MB of partial sums more.  Measured, before -> this kernel:
   // 8192 x 5120 at M = 256 / 512 / 1024 / 2048 70 / 115 / 217 / 470 -> 42 / 51 / 95 / 190,
   // 25600 x 5120 at M = 65 / 128 / 256 / 1024 107 / 113 / 209 / 739 -> 56 / 62 / 105 / 342,
-  // 5120 x 8192 at M = 256 (2 slices) / 517 / 2048 56 / 124 / 408 -> 45 / 62 / 202, 5120 x
+  // 5120 x 8192 at M = 256 (3 slices) / 517 / 2048 56 / 124 / 408 -> 37 / 62 / 202, 5120 x
   // 25600 at M = 256 (3 slices) 180 -> 108, 1024 x 5120 at M = 2048 (2 slices) 76 -> 35; the
   // row-split kernel stays at 1024 x 5120 up to M = 512 (13 at M = 128 against 19).
   // The 256 x 256 kernel takes over where a model of it (per step 0.83 a round and 0.54 for a
@@ -945,7 +945,7 @@ int gemm_common(const void* X, int64_t M, int64_t ldx, int32_t dtype, int32_t sp
   if ((int64_t)M * ldy > (int64_t)1 << 40) return fail(SPENSE_ERR_ARG, "Y too large");
   Plan pl = cached_plan(dtype, M, N, split, K, dense_begin, tiled, ov);
   // The K slices of the 128 x 128 kernel are a matter of speed: a caller without their workspace
-  // gets the plan that does without them (bf16 5120 x 8192 at M = 256 57 us against 45).
+  // gets the plan that does without them (bf16 5120 x 8192 at M = 256 56 us against 37).
   if (pl.ls.big == 3 && pl.ws_bytes > 0 && (!ws || ws_bytes < pl.ws_bytes || !aligned16(ws))) {
     Override one = ov;
     one.no_mid_slices = true;
@@ -1560,9 +1560,8 @@ int spense_gemm_grouped(const void* X, int64_t M, int64_t ldx, int32_t count, co
       slice_cuts(r, 1, kc, 1, sparse_cost);
       regs[nreg++] = r;
     }
-  // Many tokens: the 256 x 256 large-M kernel over every weight's regions in one grid, on
-  // the single-weight rule (at least 160 tiles; with two or three token blocks the last
-  // one full), with its tail tiles and XCD-aware order; small weights such as k and v then
+  // Many tokens: the 256 x 256 large-M kernel over every weight's regions in one grid, from
+  // 160 tiles, with its tail tiles and XCD-aware order; small weights such as k and v then
   // ride in q's grid instead of leaving most CUs idle (alone at M = 2048 they run 37 us on
   // the row-split kernel).
   const int64_t T256 = ceil_div(M, 256);
