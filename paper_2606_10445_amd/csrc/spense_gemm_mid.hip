@@ -10,8 +10,9 @@ namespace {
 // bf16 weights row-major.
 //
 // Eight waves compute, the rows split over four of them and the tokens in two 64-token halves
-// (32 rows x 64 tokens each), and four (one per SIMD) only copy.  A wave that issues a copy into LDS is held there until
-// the CU's load path takes it (~18 clocks per kilobyte, all waves together), and LDS reads
+// (32 rows x 64 tokens each), and four (one per SIMD) only copy.  A wave that issues a copy
+// into LDS is held there until the CU's load path takes it (~18 clocks per kilobyte, all waves
+// together), and LDS reads
 // behind it in the same wave wait too, while copies and reads of different waves do not slow
 // each other (measured: 32 KB copied in 606 clocks and 64 KB read in 690 at once, 585 and 687
 // alone).  With every wave copying its share, a 128-column step took 1370 clocks.
@@ -29,7 +30,7 @@ namespace {
 // Measured (graph replay, us, the planner's choice before -> this kernel): 5120 x 8192
 // input-split M = 448 / 640 / 768 37 / 46 / 45 -> 34 / 35 / 38, 8192 x 5120 M = 288 / 448 /
 // 512 31 / 37 / 40 -> 28 / 27 / 29, 5120 x 25600 M = 512 / 640 103 / 124 -> 94 / 94 and in
-// 6 / 3 / 2 slices at M = 128 / 224 / 352 39 / 57 / 76 -> 35 / 49 / 64.  A step takes 0.43 us,
+// 6 / 3 / 2 slices at M = 128 / 224 / 288 39 / 57 / 75 -> 35 / 49 / 64.  A step takes 0.43 us,
 // of which the copies alone take 0.40 (26 loads issued behind one barrier) and the barrier,
 // reads and MMAs alone 0.25.  64 x 64 tokens a wave instead of 64 x 32 (256-token blocks)
 // does not fit the registers of twelve waves.

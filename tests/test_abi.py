@@ -487,6 +487,34 @@ def test_192_token_blocks_rule(S, capfd):
         S.spense_set_log(prev)
 
 
+def test_large_m_grid_rules(S, capfd):
+    """Which large-M grid a tiled fp8 weight takes (256 x 256 from 160 tiles, or where 128 x 256
+    ones need a second round) and the half tiles at its end: none in whole rounds or where they
+    would need a round of their own, one row block where less is over, an eighth of the work below
+    a quarter of a round, eight row blocks above, seen through the dispatch log."""
+    def plan(N, K, split, db, M):
+        L = S.spense_layout(N, K, 1, split, db)
+        p = S.spense_packed_t(1, split, N, K, db, 4096, L.values_ld, 8192, L.meta_ld, 16384, L.dense_ld,
+                              S.SPENSE_LAYOUT_TILED)
+        capfd.readouterr()
+        S.spense_gemm_workspace_size(M, p)
+        line = capfd.readouterr().err.strip().splitlines()[-1]
+        return line.split("large-M ")[1].split()[0], int(line.split("half_tile_groups=")[1].split()[0])
+    prev = S.spense_set_log(1)
+    try:  # token counts no other test plans on these weights
+        assert plan(10752, 2816, 0, 9408, 690) == ("128x256", 0)  # 252 tiles of 128 rows, 129 of 256
+        assert plan(5120, 8192, 1, 6144, 1700) == ("256x256", 0)  # 280, 140
+        assert plan(21760, 5120, 0, 16384, 766) == ("256x256", 0)  # 85 row blocks, 255 tiles
+        assert plan(21632, 4864, 0, 16224, 562) == ("256x256", 5)  # 258 tiles: one row block
+        assert plan(25600, 5120, 0, 19200, 641) == ("256x256", 16 * 6)  # 300
+        assert plan(51200, 5120, 0, 38400, 511) == ("256x256", 8 * 4)  # 400
+        assert plan(16384, 5120, 0, 0, 1400) == ("256x256", 0)  # 384, all dense
+        assert plan(20480, 4096, 0, 15360, 1535) == ("256x256", 0)  # 480: five row blocks would fit
+        assert plan(32768, 4096, 0, 24576, 1024) == ("256x256", 0)  # 512
+    finally:
+        S.spense_set_log(prev)
+
+
 def _down_desc(S, layout=0, dtype=1):
     L = S.spense_layout(5120, 25600, dtype, 1, 19200)
     return S.spense_packed_t(dtype, 1, 5120, 25600, 19200, 4096, L.values_ld, 8192, L.meta_ld, 16384, L.dense_ld,

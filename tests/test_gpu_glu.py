@@ -230,7 +230,9 @@ def test_gemm_glu_validates_arguments(S):
 # block, 192-token blocks, ragged rows and tokens, regions that end inside a tile and off
 # multiples of 4, all 2:4, all dense, 256 x 128 tail tiles, partial last steps of K.
 @pytest.mark.parametrize("M,N,K,db", [(65, 20480, 160, 15360), (300, 10203, 672, 5002), (513, 7000, 512, 7000),
-                                      (700, 9000, 288, 0), (2100, 5000, 416, 3744)])
+                                      (700, 9000, 288, 0), (2100, 5000, 416, 3744),
+                                      # one row block of half tiles (261 tiles), an eighth (288)
+                                      (2100, 3712, 160, 2816), (2100, 4096, 160, 3008)])
 def test_gemm_glu_tiles_exact(S, M, N, K, db, capfd):
     say(f"[gemm-glu tiles] M={M} N={N} K={K} dense_begin={db}")
     (Wg, mg, sg), (Wu, mu, su), X, sx = exact_pair(61 + M, M, N, K, db)
