@@ -358,6 +358,19 @@ class _CallScratch:
         return self.buf.data_ptr(), nbytes
 
 
+_workspaces: dict = {}
+
+
+def workspace_for(device) -> Workspace:
+    """One workspace per device, for callers whose calls with it do not overlap (a call that is
+    given none does not take this one)."""
+    d = torch.device(device)
+    key = (d.type, d.index if d.index is not None else torch.cuda.current_device())
+    if key not in _workspaces:
+        _workspaces[key] = Workspace(torch.device("cuda", key[1]))
+    return _workspaces[key]
+
+
 class PackedWeight:
     """A weight in the Spense format: device buffers (values, meta, dense) + descriptor.
     ``kind`` is the storage order: SPENSE_LAYOUT_ROWMAJOR (as spense_compress writes it;
