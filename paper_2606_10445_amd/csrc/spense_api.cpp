@@ -651,6 +651,20 @@ void make_plan(int32_t dtype, int64_t M, int64_t N, int32_t split, int64_t K, in
           mid_ks = (int)S;
         }
       }
+      // Where N is no multiple of 4, above 256 tokens and 60 tiles, not in place of a row-split grid
+      // that fills the chip and spreads evenly over the 8 XCDs (48 x 5 or 80 x 3 workgroups): row-split
+      // against slices 3837 x 14336 at M = 299 41 against 54, 4547 x 15616 at M = 262 47 / 58, 5029 x
+      // 22080 at M = 313 72 / 77.  Other grids gain from slices or are mixed (4603 x 15616 at M = 320,
+      // 51 x 5, 67 -> 52; 3462 x 18176 at M = 287, 44 x 5, 54 -> 50), and so do few tiles; where N is a
+      // multiple of 4 the layers' own shapes gain on even grids too (5120 x 25600 at M = 288 above).
+      if (mid_ks > 1 && N % 4 != 0 && M > 256 && wgs > 60) {
+        Override whole = ov;
+        whole.no_mid_slices = true;
+        Plan row;
+        make_plan(dtype, M, N, split, K, dense_begin, tiled, whole, &row);
+        const int64_t grid = (int64_t)row.args.groups * row.ls.mblocks;
+        if (row.ls.rows && !row.ls.big && row.args.groups % 8 == 0 && grid >= 240) mid_ks = 0;
+      }
     }
   }
   // bf16 above 64 tokens: the same kernel on row-major weights (64 columns a step) against the

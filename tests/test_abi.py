@@ -614,3 +614,28 @@ def test_dispatch_log_names_the_plan_and_changes_nothing(S, capfd):
         assert S.spense_gemm_workspace_size(M, pk) == quiet  # the log does not change the plan
     finally:
         S.spense_set_log(prev)
+
+
+def test_slices_leave_even_row_split_grids(S, capfd):
+    """K slices of the 128 x 128 kernel where N is no multiple of 4, above 256 tokens and 60 tiles:
+    not where the row-split grid has a multiple of 8 workgroups a token block and fills the chip;
+    seen through the dispatch log."""
+    def kernel(N, K, split, db, M):
+        L = S.spense_layout(N, K, 1, split, db)
+        p = S.spense_packed_t(1, split, N, K, db, 4096, L.values_ld, 8192, L.meta_ld, 16384, L.dense_ld,
+                              S.SPENSE_LAYOUT_TILED)
+        capfd.readouterr()
+        S.spense_gemm_workspace_size(M, p)
+        return capfd.readouterr().err.strip().splitlines()[-1].split(" -> ")[1].split(" act_tiles")[0]
+    prev = S.spense_set_log(1)
+    try:
+        assert kernel(3837, 14336, 1, 1888, 299) == "row-split"  # 48 x 5 workgroups
+        assert kernel(5029, 22080, 1, 3744, 313) == "row-split, two 64-token halves"  # 80 x 3
+        mid = "large-M 128x128"
+        assert kernel(4603, 15616, 0, 1120, 320) == mid  # 51 x 5
+        assert kernel(3462, 18176, 1, 672, 287) == mid  # 44 x 5
+        assert kernel(2299, 21568, 1, 448, 258) == mid  # 48 x 5, 54 tiles
+        assert kernel(3837, 14336, 1, 1888, 256) == mid  # 256 tokens
+        assert kernel(5120, 25600, 1, 19200, 289) == mid  # 80 x 3, N a multiple of 4
+    finally:
+        S.spense_set_log(prev)
