@@ -345,7 +345,9 @@ class Workspace:
 class _CallScratch:
     """The scratch of one call that was given no workspace: from torch's allocator, so that
     calls on other streams or threads hold other memory and a captured call's belongs to its
-    graph.  The allocator hands it out again only in this stream's order."""
+    graph.  The allocator hands it out again only in this stream's order.  It costs 0.4 to 0.8 us
+    of host time, seen where the host bounds the call (fp8 2176 x 20416 at M = 9, eager: 14.7 us
+    against 13.9 with one buffer kept per device); a caller's own ``Workspace`` spares it."""
 
     def __init__(self, device):
         self.device = device
